@@ -586,8 +586,8 @@ lsqr_status lsqr_trainer_create(int max_batch, const float *params, void *stream
 
 /*
  * lsqr_trainer_grad — loss = mean over the batch of (log softplus(z_b) -
- * target_b)^2 and its gradient (FP32 forward/backward per sample, per-parameter
- * sums over the batch in sample order).  x: device [batch][6] standardised
+ * target_b)^2 and its gradient (FP32 forward/backward per sample, FP64
+ * sums over the batch in a fixed order).  x: device [batch][6] standardised
  * features; target: device [batch] log multipliers; grad: device
  * [LSQR_MLP_NPARAMS] or NULL; loss: host or NULL.
  */

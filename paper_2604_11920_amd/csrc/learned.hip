@@ -178,94 +178,196 @@ __global__ __launch_bounds__(256) void k_mlp_infer(int n, const float *params, N
 }
 
 // ----------------------------------------------------------------- training --
-// Per sample (FP32): forward, loss term and the deltas needed for the weight
-// gradients.  Stored per sample: h1, h2, d1, d2 [H] and dz; per-workgroup
-// partial sums of the squared residual.
-__global__ __launch_bounds__(256) void k_mlp_fwd_bwd(int B, const float *params, const float *x,
-                                                     const float *target, float *h1o, float *h2o,
-                                                     float *d1o, float *d2o, float *dzo,
-                                                     double *part)
+// Forward and backward of a minibatch and its weight gradient in one kernel:
+// a workgroup takes tiles of kTile samples, 8 to a wave, lane k of a wave
+// owning neuron k of both hidden layers (the 8 samples' activations are read
+// from LDS as broadcasts, W2 by row and by column with a padded row, both
+// without bank conflicts; per neuron the sums run over the inputs in order).
+// The tile's activations and deltas stay in LDS, and every thread then adds
+// its 16 entries of d2 h1^T (and the smaller blocks) over the tile's samples
+// in FP64; k_mlp_reduce adds the workgroups' partial gradients in order.
+// What bounds it is latency, a chain of ~20 LDS phases per tile: at the
+// default minibatch of 4,096, 99 us (one thread per sample on 16 workgroups)
+// plus 1,043 us for the weight gradient (one thread per parameter walking
+// the whole batch) became 24.5 us plus 4.8 us for k_mlp_reduce.  Tiles of 16
+// samples measured 22.0 + 7.3 us: the same.
+constexpr int kTile = 32;                 // samples per workgroup and tile
+constexpr int kTW = kTile / 4;            // samples per wave
+constexpr int kW2S = H + 1;               // padded row of W2 in LDS
+constexpr int kTS = kTW + 4;              // padded row of the per-neuron sample arrays
+constexpr int kMaxTileGroups = 512;       // workgroups (partial gradients) at most
+
+// the kTW samples of one neuron (or feature) of a wave
+__device__ __forceinline__ void ld_samples(const float *p, float (&v)[kTW])
 {
-    __shared__ float W[NP];
+#pragma unroll
+    for (int q = 0; q < kTW / 4; ++q) {
+        const float4 a = *(const float4 *)(p + 4 * q);
+        v[4 * q] = a.x; v[4 * q + 1] = a.y; v[4 * q + 2] = a.z; v[4 * q + 3] = a.w;
+    }
+}
+__device__ __forceinline__ void st_samples(float *p, const float (&v)[kTW])
+{
+#pragma unroll
+    for (int q = 0; q < kTW / 4; ++q)
+        *(float4 *)(p + 4 * q) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+}
+
+// Partial gradient of workgroup b in gpart[b][NP] (FP64), its part of the
+// squared residuals in part[b].
+__global__ __launch_bounds__(256) void k_mlp_grad(int B, const float *params, const float *x,
+                                                  const float *target, double *gpart, double *part)
+{
+    static_assert(kTW % 4 == 0, "whole float4s of samples");
+    __shared__ float w2[H * kW2S];
+    __shared__ __align__(16) float h1s[4][H * kTS], h2s[4][H * kTS], d1s[4][H * kTS], d2s[4][H * kTS];
+    // per wave and sample: the features, then dz and 1, as rows of kTS like the
+    // neurons', so that a product of two rows covers every small parameter
+    __shared__ __align__(16) float xs[4][(NF + 2) * kTS];
     __shared__ double lds[4];
-    for (int i = threadIdx.x; i < NP; i += blockDim.x) W[i] = params[i];
-    __syncthreads();
+    const int k = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    for (int i = threadIdx.x; i < H * H; i += 256) w2[(i / H) * kW2S + i % H] = params[OW2 + i];
+    float w1[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) w1[f] = params[OW1 + k * NF + f];
+    const float b1 = params[OB1 + k], b2 = params[OB2 + k], w3 = params[OW3 + k], b3 = params[OB3];
+    // the thread's entries of W2: rows tk + 16 i, columns tl + 16 j
+    const int tk = threadIdx.x >> 4, tl = threadIdx.x & 15;
+    double g2[4][4] = {}, gs[3] = {0.0, 0.0, 0.0};
+    // the thread's parameters outside W2 (W1 and b1, the first OW2, then b2, W3,
+    // b3): each the sum over the samples of one row times another
+    constexpr int NS = NP - H * H;
+    const float *ra[3], *rb[3];
+    int sa[3], sb[3];                     // strides from wave to wave
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+        const int q = threadIdx.x + 256 * u, p = q < OW2 ? q : q + H * H;
+        ra[u] = rb[u] = &xs[0][(NF + 1) * kTS];
+        sa[u] = sb[u] = (NF + 2) * kTS;
+        if (p < OB1) { ra[u] = &d1s[0][p / NF * kTS]; sa[u] = H * kTS; rb[u] = &xs[0][p % NF * kTS]; }
+        else if (p < OW2) { ra[u] = &d1s[0][(p - OB1) * kTS]; sa[u] = H * kTS; }
+        else if (p < OW3) { ra[u] = &d2s[0][(p - OB2) * kTS]; sa[u] = H * kTS; }
+        else if (p < OB3) { ra[u] = &h2s[0][(p - OW3) * kTS]; sa[u] = H * kTS; rb[u] = &xs[0][NF * kTS]; }
+        else if (p < NP) rb[u] = &xs[0][NF * kTS];
+    }
     double sq = 0.0;
-    for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < B; b += gridDim.x * blockDim.x) {
-        float xv[NF];
-        for (int f = 0; f < NF; ++f) xv[f] = x[(int64_t)b * NF + f];
-        float a1[H], h1[H];
-        for (int k = 0; k < H; ++k) {
-            float a = W[OB1 + k];
-            for (int f = 0; f < NF; ++f) a = fmaf(W[OW1 + k * NF + f], xv[f], a);
-            a1[k] = a;
-            h1[k] = gelu(a);
-            h1o[(int64_t)b * H + k] = h1[k];
+    const int tiles = (B + kTile - 1) / kTile;
+    for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+        __syncthreads();                  // w2 is in place, the previous tile's reads are done
+        if (threadIdx.x < kTile * NF) {
+            const int i = threadIdx.x / NF, f = threadIdx.x % NF, b = t * kTile + i;
+            xs[i / kTW][f * kTS + i % kTW] = b < B ? x[(int64_t)b * NF + f] : 0.0f;
         }
-        float a2[H];
-        float z = W[OB3];
-        for (int k = 0; k < H; ++k) {
-            float a = W[OB2 + k];
-            for (int l = 0; l < H; ++l) a = fmaf(W[OW2 + k * H + l], h1[l], a);
-            a2[k] = a;
-            const float h2 = gelu(a);
-            h2o[(int64_t)b * H + k] = h2;
-            z = fmaf(W[OW3 + k], h2, z);
+        if (threadIdx.x < kTile) xs[threadIdx.x / kTW][(NF + 1) * kTS + threadIdx.x % kTW] = 1.0f;
+        __syncthreads();
+        const int s0 = wid * kTW;
+        float a1[kTW], a2[kTW], h[kTW];
+#pragma unroll
+        for (int s = 0; s < kTW; ++s) {
+            float a = b1;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) a = fmaf(w1[f], xs[wid][f * kTS + s], a);
+            a1[s] = a;
+            h[s] = gelu(a);
+            a2[s] = b2;
         }
-        const float sp = softplus(z);
-        const float r = logf(sp) - target[b];
-        sq += (double)r * (double)r;
-        const float dz = 2.0f * r / (float)B * sigmoid(z) / sp;
-        dzo[b] = dz;
-        for (int k = 0; k < H; ++k) {
-            a2[k] = dz * W[OW3 + k] * gelu_grad(a2[k]);      // d2
-            d2o[(int64_t)b * H + k] = a2[k];
-        }
+        st_samples(&h1s[wid][k * kTS], h);
+        __syncthreads();
+#pragma unroll 8
         for (int l = 0; l < H; ++l) {
-            float s = 0.0f;
-            for (int k = 0; k < H; ++k) s = fmaf(W[OW2 + k * H + l], a2[k], s);
-            d1o[(int64_t)b * H + l] = s * gelu_grad(a1[l]);
+            ld_samples(&h1s[wid][l * kTS], h);
+            const float w = w2[k * kW2S + l];
+#pragma unroll
+            for (int s = 0; s < kTW; ++s) a2[s] = fmaf(w, h[s], a2[s]);
         }
+        float d[kTW];
+#pragma unroll
+        for (int s = 0; s < kTW; ++s) {
+            h[s] = gelu(a2[s]);
+            const float z = b3 + group_sum<64>(w3 * h[s]);
+            const int b = t * kTile + s0 + s;
+            const float sp = softplus(z);
+            const float r = b < B ? logf(sp) - target[b] : 0.0f;
+            const float dz = b < B ? 2.0f * r / (float)B * sigmoid(z) / sp : 0.0f;
+            if (k == 0) {
+                sq += (double)r * (double)r;
+                xs[wid][NF * kTS + s] = dz;
+            }
+            d[s] = dz * w3 * gelu_grad(a2[s]);
+        }
+        st_samples(&h2s[wid][k * kTS], h);
+        st_samples(&d2s[wid][k * kTS], d);
+        __syncthreads();
+        float e[kTW] = {};
+#pragma unroll 8
+        for (int q = 0; q < H; ++q) {
+            ld_samples(&d2s[wid][q * kTS], h);
+            const float w = w2[q * kW2S + k];
+#pragma unroll
+            for (int s = 0; s < kTW; ++s) e[s] = fmaf(w, h[s], e[s]);
+        }
+#pragma unroll
+        for (int s = 0; s < kTW; ++s) e[s] *= gelu_grad(a1[s]);
+        st_samples(&d1s[wid][k * kTS], e);
+        __syncthreads();
+        // the tile's weight gradient, samples in order
+        for (int w = 0; w < 4; ++w) {
+            float dv[4][kTW], hv[4][kTW];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                ld_samples(&d2s[w][(tk + 16 * i) * kTS], dv[i]);
+                ld_samples(&h1s[w][(tl + 16 * i) * kTS], hv[i]);
+            }
+#pragma unroll
+            for (int s = 0; s < kTW; ++s)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) g2[i][j] = fma((double)dv[i][s], (double)hv[j][s], g2[i][j]);
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {
+                if (threadIdx.x + 256 * u >= NS) continue;
+                float av[kTW], bv[kTW];
+                ld_samples(ra[u] + w * sa[u], av);
+                ld_samples(rb[u] + w * sb[u], bv);
+#pragma unroll
+                for (int s = 0; s < kTW; ++s) gs[u] += (double)av[s] * (double)bv[s];
+            }
+        }
+    }
+    double *g = gpart + (int64_t)blockIdx.x * NP;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) g[OW2 + (tk + 16 * i) * H + tl + 16 * j] = g2[i][j];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+        const int q = threadIdx.x + 256 * u;
+        if (q < NS) g[q < OW2 ? q : q + H * H] = gs[u];
     }
     const double tot = block_sum(sq, lds);
     if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
 
-// One thread per parameter: its gradient as a sum over the batch in sample
-// order (FP64 accumulation).
-__global__ void k_mlp_wgrad(int B, const float *x, const float *h1, const float *h2,
-                            const float *d1, const float *d2, const float *dz, float *grad)
+// Gradient = sum of the np partial gradients (16 runs of workgroups in order,
+// then the runs in order: fixed), rounded to FP32; with lr > 0 also the Adam
+// step.  16 parameters to a workgroup, so 293 workgroups share the read.
+__global__ __launch_bounds__(256) void k_mlp_reduce(int np, const double *gpart, float *grad,
+                                                    float *params, float *m, float *v, float lr,
+                                                    float b1c, float b2c)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= NP) return;
+    __shared__ double acc[16][16];
+    const int c = threadIdx.x & 15, q = threadIdx.x >> 4, p = blockIdx.x * 16 + c;
     double s = 0.0;
-    if (p < OB1) {
-        const int k = p / NF, f = p % NF;
-        for (int b = 0; b < B; ++b) s += (double)d1[(int64_t)b * H + k] * (double)x[(int64_t)b * NF + f];
-    } else if (p < OW2) {
-        const int k = p - OB1;
-        for (int b = 0; b < B; ++b) s += (double)d1[(int64_t)b * H + k];
-    } else if (p < OB2) {
-        const int k = (p - OW2) / H, l = (p - OW2) % H;
-        for (int b = 0; b < B; ++b) s += (double)d2[(int64_t)b * H + k] * (double)h1[(int64_t)b * H + l];
-    } else if (p < OW3) {
-        const int k = p - OB2;
-        for (int b = 0; b < B; ++b) s += (double)d2[(int64_t)b * H + k];
-    } else if (p < OB3) {
-        const int k = p - OW3;
-        for (int b = 0; b < B; ++b) s += (double)dz[b] * (double)h2[(int64_t)b * H + k];
-    } else {
-        for (int b = 0; b < B; ++b) s += (double)dz[b];
-    }
-    grad[p] = (float)s;
-}
-
-__global__ void k_adam(float *params, float *m, float *v, const float *g, float lr, float b1c,
-                       float b2c)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= NP) return;
-    const float gi = g[p];
+    if (p < NP)
+        for (int b = np * q / 16; b < np * (q + 1) / 16; ++b) s += gpart[(int64_t)b * NP + p];
+    acc[q][c] = s;
+    __syncthreads();
+    if (q != 0 || p >= NP) return;
+    for (int r = 1; r < 16; ++r) s += acc[r][c];
+    const float gi = (float)s;
+    grad[p] = gi;
+    if (!(lr > 0.0f)) return;
     const float mi = 0.9f * m[p] + 0.1f * gi;
     const float vi = 0.999f * v[p] + 0.001f * gi * gi;
     m[p] = mi;
@@ -281,32 +383,34 @@ struct lsqr_trainer {
     int max_batch = 0;
     int t = 0;
     float *params = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr;
-    float *h1 = nullptr, *h2 = nullptr, *d1 = nullptr, *d2 = nullptr, *dz = nullptr;
-    double *part = nullptr, *sum = nullptr;
+    double *gpart = nullptr, *part = nullptr, *sum = nullptr;
     double *hsum = nullptr;
-    int grid = 1;
     std::string err;
 };
 
 // Device buffers of a trainer and their sizes (bytes), in one place so that
 // creation and release agree.
-static void trainer_buffers(lsqr_trainer *t, void **(&ptrs)[11], size_t (&bytes)[11])
+constexpr int kTrainerBuffers = 7;
+
+static int tile_groups(int batch) { return std::min(kMaxTileGroups, (batch + kTile - 1) / kTile); }
+
+static void trainer_buffers(lsqr_trainer *t, void **(&ptrs)[kTrainerBuffers],
+                            size_t (&bytes)[kTrainerBuffers])
 {
-    const size_t B = (size_t)t->max_batch;
-    void **p[11] = {(void **)&t->params, (void **)&t->m, (void **)&t->v, (void **)&t->grad,
-                    (void **)&t->h1, (void **)&t->h2, (void **)&t->d1, (void **)&t->d2,
-                    (void **)&t->dz, (void **)&t->part, (void **)&t->sum};
-    const size_t b[11] = {NP * 4, NP * 4, NP * 4, NP * 4, B * H * 4, B * H * 4, B * H * 4,
-                          B * H * 4, B * 4, 1024 * 8, 8};
-    for (int i = 0; i < 11; ++i) { ptrs[i] = p[i]; bytes[i] = b[i]; }
+    const size_t G = (size_t)tile_groups(t->max_batch);
+    void **p[kTrainerBuffers] = {(void **)&t->params, (void **)&t->m, (void **)&t->v,
+                                 (void **)&t->grad, (void **)&t->gpart, (void **)&t->part,
+                                 (void **)&t->sum};
+    const size_t b[kTrainerBuffers] = {NP * 4, NP * 4, NP * 4, NP * 4, G * NP * 8, G * 8, 8};
+    for (int i = 0; i < kTrainerBuffers; ++i) { ptrs[i] = p[i]; bytes[i] = b[i]; }
 }
 
 static void trainer_free(lsqr_trainer *t)
 {
-    void **ptrs[11];
-    size_t bytes[11];
+    void **ptrs[kTrainerBuffers];
+    size_t bytes[kTrainerBuffers];
     trainer_buffers(t, ptrs, bytes);
-    for (int i = 0; i < 11; ++i)
+    for (int i = 0; i < kTrainerBuffers; ++i)
         if (*ptrs[i]) t->al.put(*ptrs[i], bytes[i]);
     if (t->hsum) (void)hipHostFree(t->hsum);
     delete t;
@@ -445,12 +549,11 @@ lsqr_status lsqr_trainer_create(int max_batch, const float *params, void *stream
     t->al.dealloc = dealloc;
     t->al.user = alloc_user;
     t->max_batch = max_batch;
-    t->grid = std::min(1024, (max_batch + 255) / 256);
-    void **ptrs[11];
-    size_t bytes[11];
+    void **ptrs[kTrainerBuffers];
+    size_t bytes[kTrainerBuffers];
     trainer_buffers(t, ptrs, bytes);
     bool ok = true;
-    for (int i = 0; i < 11 && ok; ++i) ok = (*ptrs[i] = t->al.get(bytes[i])) != nullptr;
+    for (int i = 0; i < kTrainerBuffers && ok; ++i) ok = (*ptrs[i] = t->al.get(bytes[i])) != nullptr;
     ok = ok && hipHostMalloc((void **)&t->hsum, 8, hipHostMallocDefault) == hipSuccess;
     if (!ok) {
         trainer_free(t);
@@ -467,15 +570,17 @@ lsqr_status lsqr_trainer_create(int max_batch, const float *params, void *stream
     return LSQR_OK;
 }
 
+// The gradient of a minibatch into t->grad; with lr > 0 the Adam step too.
 static lsqr_status trainer_grad(lsqr_trainer *t, int batch, const float *x, const float *target,
-                                double *loss)
+                                double *loss, float lr, float b1c, float b2c)
 {
-    hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3(t->grid), dim3(256), 0, t->st, batch, t->params, x,
-                       target, t->h1, t->h2, t->d1, t->d2, t->dz, t->part);
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3((NP + 255) / 256), dim3(256), 0, t->st, batch, x, t->h1,
-                       t->h2, t->d1, t->d2, t->dz, t->grad);
+    const int groups = tile_groups(batch);
+    hipLaunchKernelGGL(k_mlp_grad, dim3(groups), dim3(256), 0, t->st, batch, t->params, x, target,
+                       t->gpart, t->part);
+    hipLaunchKernelGGL(k_mlp_reduce, dim3((NP + 15) / 16), dim3(256), 0, t->st, groups, t->gpart,
+                       t->grad, t->params, t->m, t->v, lr, b1c, b2c);
     if (loss) {
-        launch_sum_partials(t->st, t->part, t->grid, t->sum);
+        launch_sum_partials(t->st, t->part, groups, t->sum);
         if (hipMemcpyAsync(t->hsum, t->sum, 8, hipMemcpyDeviceToHost, t->st) != hipSuccess ||
             hipStreamSynchronize(t->st) != hipSuccess) {
             t->err = "device copy failed";
@@ -494,7 +599,7 @@ lsqr_status lsqr_trainer_grad(lsqr_trainer *t, int batch, const float *x, const 
                               float *grad, double *loss)
 {
     if (!t || !x || !target || batch < 1 || batch > t->max_batch) return LSQR_E_INVALID_ARG;
-    lsqr_status s = trainer_grad(t, batch, x, target, loss);
+    lsqr_status s = trainer_grad(t, batch, x, target, loss, 0.0f, 1.0f, 1.0f);
     if (s != LSQR_OK) return s;
     if (grad && hipMemcpyAsync(grad, t->grad, NP * 4, hipMemcpyDeviceToDevice, t->st) != hipSuccess)
         return LSQR_E_DEVICE;
@@ -505,13 +610,11 @@ lsqr_status lsqr_trainer_step(lsqr_trainer *t, int batch, const float *x, const 
                               float lr, double *loss)
 {
     if (!t || !x || !target || batch < 1 || batch > t->max_batch || !(lr > 0.0f)) return LSQR_E_INVALID_ARG;
-    lsqr_status s = trainer_grad(t, batch, x, target, loss);
-    if (s != LSQR_OK) return s;
-    t->t += 1;
-    const float b1c = 1.0f - powf(0.9f, (float)t->t), b2c = 1.0f - powf(0.999f, (float)t->t);
-    hipLaunchKernelGGL(k_adam, dim3((NP + 255) / 256), dim3(256), 0, t->st, t->params, t->m, t->v,
-                       t->grad, lr, b1c, b2c);
-    return hipGetLastError() == hipSuccess ? LSQR_OK : LSQR_E_DEVICE;
+    const int n = t->t + 1;
+    const float b1c = 1.0f - powf(0.9f, (float)n), b2c = 1.0f - powf(0.999f, (float)n);
+    lsqr_status s = trainer_grad(t, batch, x, target, loss, lr, b1c, b2c);
+    if (s == LSQR_OK) t->t = n;
+    return s;
 }
 
 lsqr_status lsqr_trainer_params(const lsqr_trainer *t, float *params, float *params_device)
