@@ -217,8 +217,8 @@ typedef struct {
  * sort by column so rows stay ascending within a column), the stored formats
  * opts.row_format / opts.col_format select (by default, where the matrix fits
  * them, row groups for the forward product and node runs in the depth-pair
- * layout for the transposed product, both built from the CSR structure on
- * the host) and the column scaling.  damp >= 0 and smooth_weight >= 0 (damp > 0 is required by
+ * layout for the transposed product, both planned from the CSR structure on
+ * the device) and the column scaling.  damp >= 0 and smooth_weight >= 0 (damp > 0 is required by
  * the mixed forms, whose refinement folds the FP64 correction into the damping
  * block).  opts may be NULL (FP64, no scaling, default stream, hipMalloc).
  * On success *out owns every derived buffer; free it with lsqr_destroy.

@@ -100,26 +100,20 @@ constexpr int kQDepths = LSQR_Q_DEPTHS;
 // The node-run values of `src` (CSR order, elem_bytes each) in the layout of
 // W depths to a word: every run from a position that is a multiple of W,
 // zeros before its first depth's offset in the word and after its end, W
-// zeros after the last run; the layout's quarter offsets and destinations
-// are kept in the context.
-static lsqr_status build_four_depth(lsqr_ctx *c, const NodeRuns &NR, int nz, const void *src,
-                                    int elem_bytes, int W, void **out)
+// zeros after the last run (total positions before them).  *vals and *nvq
+// (the layout's quarter offsets) are kept in the context; start is scratch
+// for nr positions.
+static lsqr_status build_layout(lsqr_ctx *c, const RunPlan &R, int W, int64_t total, uint32_t *start,
+                                const void *src, int elem_bytes, int64_t **nvq, void **vals)
 {
     hipStream_t st = c->st;
-    const int64_t nn = c->P.n / nz;
-    std::vector<uint32_t> dst4;
-    std::vector<int64_t> nvq4;
-    if (!pair_layout_host(NR, nn, dst4, nvq4, c->npad4, W))
-        return fail(c, LSQR_E_UNSUPPORTED, "the wide depth layout needs fewer than 2^32 padded values");
-    c->nvqp4 = ctx_alloc<int64_t>(c, 4 * nn + 1);
-    c->ndstp4 = ctx_alloc<uint32_t>(c, c->nnruns);
-    void *vals = ctx_alloc_bytes(c, (size_t)(c->npad4 + W) * elem_bytes);
-    if (!c->nvqp4 || !c->ndstp4 || !vals) return fail(c, LSQR_E_OOM, "device allocation failed");
-    *out = vals;
-    HIP_TRY(c, hipMemcpy(c->nvqp4, nvq4.data(), (4 * nn + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(c->ndstp4, dst4.data(), c->nnruns * sizeof(uint32_t), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemsetAsync(vals, 0, (size_t)(c->npad4 + W) * elem_bytes, st));
-    launch_gather_runs(st, c->nnruns, c->nsrc, c->ndstp4, c->ndesc, src, vals, elem_bytes);
+    const int64_t nn = c->P.n / c->P.nz;
+    *nvq = ctx_alloc<int64_t>(c, 4 * nn + 1);
+    *vals = ctx_alloc_bytes(c, (size_t)(total + W) * elem_bytes);
+    if (!*nvq || !*vals) return fail(c, LSQR_E_OOM, "device allocation failed");
+    HIP_TRY(c, plan_layout(st, c->al, nn, R, W, total, start, *nvq));
+    launch_gather_runs(st, R.nr, R.nsrc, start, R.ndesc, W, src, *vals, elem_bytes);
+    HIP_TRY(c, hipMemsetAsync((char *)*vals + (size_t)total * elem_bytes, 0, (size_t)W * elem_bytes, st));
     return LSQR_OK;
 }
 
@@ -371,7 +365,6 @@ void lsqr_destroy(lsqr_ctx *c)
     if (c->cap_st) (void)hipStreamDestroy(c->cap_st);
     for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
     for (auto &pr : c->owned) c->al.put(pr.first, pr.second);
-    if (c->hctl) (void)hipHostFree(c->hctl);
     if (c->hsum) (void)hipHostFree(c->hsum);
     delete c;
 }
@@ -480,8 +473,9 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
     if (!c->rp || !c->ci || !c->va || !c->cp || !c->ri || !c->cv || !c->d || !c->ones ||
         !c->dtbuf || !c->dmbuf || !c->flag || !c->ybuf || !c->Pr || !c->Pa || !c->Pf || !c->sums)
         return bail(LSQR_E_OOM, "device allocation failed");
-    CR_TRY(hipHostMalloc((void **)&c->hctl, C_WORDS * sizeof(int), hipHostMallocDefault));
-    CR_TRY(hipHostMalloc((void **)&c->hsum, 4 * sizeof(double), hipHostMallocDefault));
+    // one pinned block: 4 reductions, then the control words
+    CR_TRY(hipHostMalloc((void **)&c->hsum, 4 * sizeof(double) + C_WORDS * sizeof(int), hipHostMallocDefault));
+    c->hctl = (int *)(c->hsum + 4);
 
     hipStream_t st = c->st;
     const hipMemcpyKind kind = G->mem == LSQR_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
@@ -491,34 +485,119 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
         CR_TRY(hipMemcpyAsync(c->va, G->val, nnz * sizeof(double), kind, st));
     }
     CR_TRY(hipMemsetAsync(c->va + nnz, 0, 8 * sizeof(double), st));
-    std::vector<int64_t> hrp;
-    std::vector<int32_t> hci;
-    const int64_t *hrow = G->row_ptr;
-    const int32_t *hcol = G->col_idx;
-    if (G->mem == LSQR_MEM_DEVICE) {
+    // the row scan: validation of a device CSR, runs per row, longest row
+    const int nz = G->nz;
+    const bool plan = nnz > 0 && nnz < ((int64_t)1 << 32) && nz <= 64;   // run formats can hold G
+    std::vector<void *> tmp;             // planning arrays, released when the stream is done
+    auto temp = [&](size_t bytes) {
+        void *p = ctx_alloc_bytes(c, bytes);
+        if (p) tmp.push_back(p);
+        return p;
+    };
+    int64_t longest = 0;
+    uint32_t *cnt = nullptr;
+    if (G->mem == LSQR_MEM_DEVICE || plan) {
+        cnt = (uint32_t *)temp((size_t)(m + 1) * sizeof(uint32_t));
+        if (!cnt) return bail(LSQR_E_OOM, "device allocation failed");
+        CR_TRY(plan_scan_rows(st, m, n, nnz, nz, c->rp, c->ci,
+                              G->mem == LSQR_MEM_DEVICE ? c->va : nullptr, cnt, c->flag));
         int64_t ends[2] = {0, 0};
+        int info[2] = {0, 0};
         CR_TRY(hipMemcpyAsync(&ends[0], c->rp, sizeof(int64_t), hipMemcpyDeviceToHost, st));
         CR_TRY(hipMemcpyAsync(&ends[1], c->rp + m, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+        CR_TRY(hipMemcpyAsync(info, c->flag, sizeof(info), hipMemcpyDeviceToHost, st));
         CR_TRY(hipStreamSynchronize(st));
         if (ends[0] != 0 || ends[1] != nnz)
             return bail(LSQR_E_BAD_CSR, "row_ptr[0] must be 0 and row_ptr[m] must equal nnz");
-        CR_TRY(hipMemsetAsync(c->flag, 0, sizeof(int), st));
-        launch_check_csr(st, m, n, c->rp, c->ci, c->va, c->flag);
-        int f = 0;
-        CR_TRY(hipMemcpyAsync(&f, c->flag, sizeof(int), hipMemcpyDeviceToHost, st));
-        CR_TRY(hipStreamSynchronize(st));
-        if (f & 1) return bail(LSQR_E_BAD_CSR, "row_ptr is not non-decreasing");
-        if (f & 2) return bail(LSQR_E_BAD_CSR, "column index out of range");
-        if (f & 4) return bail(LSQR_E_BAD_CSR, "columns not strictly increasing within a row");
-        if (f & 8) return bail(LSQR_E_NONFINITE, "non-finite value in G");
-        hrp.resize((size_t)m + 1);
-        hci.resize((size_t)nnz);
-        CR_TRY(hipMemcpy(hrp.data(), c->rp, (m + 1) * sizeof(int64_t), hipMemcpyDeviceToHost));
-        if (nnz) CR_TRY(hipMemcpy(hci.data(), c->ci, nnz * sizeof(int32_t), hipMemcpyDeviceToHost));
-        hrow = hrp.data();
-        hcol = hci.data();
+        if (info[0] & 1) return bail(LSQR_E_BAD_CSR, "row_ptr is not non-decreasing");
+        if (info[0] & 2) return bail(LSQR_E_BAD_CSR, "column index out of range");
+        if (info[0] & 4) return bail(LSQR_E_BAD_CSR, "columns not strictly increasing within a row");
+        if (info[0] & 8) return bail(LSQR_E_NONFINITE, "non-finite value in G");
+        longest = info[1];
+    } else if (nnz > 0) {
+        for (int64_t i = 0; i < m; ++i) longest = std::max(longest, G->row_ptr[i + 1] - G->row_ptr[i]);
     }
-    {
+    const double avg_row = m > 0 ? (double)nnz / (double)m : 0.0;
+    const double avg_col = (double)nnz / (double)n;
+    // node runs of the data block for the transposed product
+    // (auto: node runs whenever the format can hold the matrix; the faster
+    // transposed product measured on gfx950)
+    const bool use_nruns = plan && (o.col_format == 0 || o.col_format == 2 || o.col_format == 4);
+    if ((o.col_format == 2 || o.col_format == 4) && nnz > 0 && !plan)
+        return bail(LSQR_E_UNSUPPORTED, "node runs need nz <= 64, m < 2^32 and nnz < 2^32");
+    // row groups with local columns (index the CSR values directly).  auto:
+    // for rows of the pipelined length (64 lanes) when the groups' column
+    // lists hold at most half as many columns as there are stored entries
+    // (the staging pass then costs well under the per-entry gathers it
+    // replaces; measured faster on gfx950 for the tomography rows).  The group
+    // size is the longest row rounded up to a multiple of 1024.
+    const bool groups_auto = o.row_format == 0 && !o.lanes_per_row && pick_lanes(avg_row) == 64;
+    const bool want_groups = (o.row_format == 4 || groups_auto) && nnz > 0;
+    const int64_t cap = std::max<int64_t>(1024, (longest + 1023) / 1024 * 1024);
+    const bool groups_fit = want_groups && cap <= kLcolMaxCap;
+    if (want_groups && !groups_fit && o.row_format == 4)
+        return bail(LSQR_E_UNSUPPORTED, "row groups need rows of at most 7168 entries and m < 2^31");
+    const bool device_groups = groups_fit && plan && plan_groups_fit(n, nz);
+    RunPlan R;
+    uint64_t padded[3] = {0, 0, 0};
+    const int64_t nn = n / nz;
+    if (use_nruns || device_groups) {
+        const bool keep_rows = use_nruns && nz <= 32;   // row order of the runs: batched forward product
+        R.rrp = keep_rows ? (c->rrp = ctx_alloc<int64_t>(c, m + 1)) : (int64_t *)temp((m + 1) * sizeof(int64_t));
+        if (!R.rrp) return bail(LSQR_E_OOM, "device allocation failed");
+        CR_TRY(plan_row_runs(st, c->al, m, cnt, R.rrp, &R.nr));
+        const int64_t nr = R.nr;
+        R.src = (uint32_t *)temp(nr * sizeof(uint32_t));
+        R.row = (uint32_t *)temp(nr * sizeof(uint32_t));
+        R.col0 = (uint32_t *)temp(nr * sizeof(uint32_t));
+        R.len = (uint8_t *)temp(nr);
+        uint32_t *key = (uint32_t *)temp(nr * sizeof(uint32_t));   // later the layouts' run positions
+        uint32_t *idx = (uint32_t *)temp(nr * sizeof(uint32_t));
+        if (!R.src || !R.row || !R.col0 || !R.len || !key || !idx) return bail(LSQR_E_OOM, "device allocation failed");
+        CR_TRY(plan_emit_runs(st, m, nz, c->rp, c->ci, R, key, idx));
+        if (use_nruns) {
+            c->nnruns = nr;
+            R.nrp = c->nrp = ctx_alloc<int64_t>(c, nn + 1);
+            R.nrow = c->nrow = ctx_alloc<uint32_t>(c, nr);
+            R.ndesc = c->ndesc = ctx_alloc<uint16_t>(c, nr);
+            R.norder = c->norder = ctx_alloc<int32_t>(c, nn);
+            R.nsrc = (uint32_t *)temp(nr * sizeof(uint32_t));
+            if (keep_rows) R.rrid = c->rrid = ctx_alloc<uint32_t>(c, nr);
+            if (!R.nrp || !R.nrow || !R.ndesc || !R.norder || !R.nsrc || (keep_rows && !R.rrid))
+                return bail(LSQR_E_OOM, "device allocation failed");
+            CR_TRY(plan_node_runs(st, c->al, nn, nz, R, key, idx, padded));
+            lsqr_status q = build_layout(c, R, 1, nnz, key, c->va, 8, &c->nvq, (void **)&c->nval);
+            // depth-pair layout (auto and col_format 4): runs padded to aligned
+            // pairs of depths, the faster transposed product measured on gfx950
+            const bool pairs_ok = o.col_format != 2 && padded[0] + 2 < ((uint64_t)1 << 32);
+            if (o.col_format == 4 && !pairs_ok)
+                return bail(LSQR_E_UNSUPPORTED, "the depth-pair layout needs fewer than 2^32 padded values");
+            if (q == LSQR_OK && pairs_ok) {
+                c->npad = (int64_t)padded[0];
+                q = build_layout(c, R, 2, c->npad, key, c->va, 8, &c->nvqp, (void **)&c->nvalp);
+            }
+            if (q != LSQR_OK) { const std::string msg = c->err; return bail(q, msg); }
+            CR_TRY(plan_csc(st, c->al, n, nz, nnz, R, c->va, c->cp, c->ri, c->cv));
+        }
+        if (device_groups) {
+            std::vector<int32_t> gp;
+            CR_TRY(plan_group_bounds(st, c->al, m, n, (int)cap, R, gp));
+            c->gcap = (int)cap;
+            c->ngroups = (int)(gp.size() - 1);
+            c->gp = ctx_alloc<int32_t>(c, c->ngroups + 1);
+            c->gcp = ctx_alloc<int64_t>(c, c->ngroups + 1);
+            if (!c->gp || !c->gcp) return bail(LSQR_E_OOM, "device allocation failed");
+            CR_TRY(hipMemcpyAsync(c->gp, gp.data(), (c->ngroups + 1) * sizeof(int32_t), hipMemcpyHostToDevice, st));
+            CR_TRY(plan_group_sizes(st, c->al, n, c->ngroups, c->gp, R, c->gcp, &c->ngcols));
+            if (o.row_format == 4 || 2 * c->ngcols <= nnz) {
+                c->gcol = ctx_alloc<int32_t>(c, std::max<int64_t>(c->ngcols, 1));
+                c->slot = ctx_alloc<uint16_t>(c, nnz + 8);
+                if (!c->gcol || !c->slot) return bail(LSQR_E_OOM, "device allocation failed");
+                CR_TRY(plan_group_lists(st, n, c->ngroups, c->gp, R, c->rp, c->ci, c->gcp, c->gcol, c->slot));
+            }
+        }
+    }
+    if (!use_nruns) {
         std::string terr;
         hipError_t e = build_transpose(st, c->al, m, n, nnz, c->rp, c->ci, c->va, c->cp, c->ri,
                                        c->cv, terr);
@@ -526,81 +605,22 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
             return bail(e == hipErrorOutOfMemory ? LSQR_E_OOM : LSQR_E_DEVICE,
                         terr + ": " + hipGetErrorString(e));
     }
-    const double avg_row = m > 0 ? (double)nnz / (double)m : 0.0;
-    const double avg_col = (double)nnz / (double)n;
-    // node runs of the data block for the transposed product
-    // (auto: node runs whenever the format can hold the matrix; the faster
-    // transposed product measured on gfx950)
-    bool use_nruns = false;
-    NodeRuns NR;
-    const bool nruns_ok = (o.col_format == 2 || o.col_format == 0 || o.col_format == 4) && nnz > 0 &&
-                          build_node_runs_host(m, n, G->nz, hrow, hcol, NR);
-    if ((o.col_format == 2 || o.col_format == 4) && nnz > 0 && !nruns_ok)
-        return bail(LSQR_E_UNSUPPORTED, "node runs need nz <= 64, m < 2^32 and nnz < 2^32");
-    if (nruns_ok) {
-        const int64_t nr = NR.nrp.back(), nn = n / G->nz;
-        c->nnruns = nr;
-        c->nrp = ctx_alloc<int64_t>(c, nn + 1);
-        c->nvq = ctx_alloc<int64_t>(c, 4 * nn + 1);
-        c->nrow = ctx_alloc<uint32_t>(c, nr);
-        c->ndesc = ctx_alloc<uint16_t>(c, nr);
-        c->norder = ctx_alloc<int32_t>(c, nn);
-        c->nsrc = ctx_alloc<uint32_t>(c, nr);
-        c->ndst = ctx_alloc<uint32_t>(c, nr);
-        c->nval = ctx_alloc<double>(c, nnz);
-        if (!c->nrp || !c->nvq || !c->nrow || !c->ndesc || !c->norder || !c->nsrc || !c->ndst || !c->nval)
-            return bail(LSQR_E_OOM, "device allocation failed");
-        CR_TRY(hipMemcpy(c->nrp, NR.nrp.data(), (nn + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-        CR_TRY(hipMemcpy(c->nvq, NR.nvq.data(), (4 * nn + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-        CR_TRY(hipMemcpy(c->nrow, NR.row.data(), nr * sizeof(uint32_t), hipMemcpyHostToDevice));
-        CR_TRY(hipMemcpy(c->ndesc, NR.desc.data(), nr * sizeof(uint16_t), hipMemcpyHostToDevice));
-        CR_TRY(hipMemcpy(c->norder, NR.order.data(), nn * sizeof(int32_t), hipMemcpyHostToDevice));
-        CR_TRY(hipMemcpy(c->nsrc, NR.src.data(), nr * sizeof(uint32_t), hipMemcpyHostToDevice));
-        CR_TRY(hipMemcpy(c->ndst, NR.dst.data(), nr * sizeof(uint32_t), hipMemcpyHostToDevice));
-        launch_gather_runs(st, nr, c->nsrc, c->ndst, c->ndesc, c->va, c->nval, 8);
-        // depth-pair layout (auto and col_format 4): runs padded to aligned
-        // pairs of depths, the faster transposed product measured on gfx950
-        std::vector<uint32_t> dstp;
-        std::vector<int64_t> nvqp;
-        const bool pairs_ok = (o.col_format == 4 || o.col_format == 0) &&
-                              pair_layout_host(NR, nn, dstp, nvqp, c->npad);
-        if (o.col_format == 4 && !pairs_ok)
-            return bail(LSQR_E_UNSUPPORTED, "the depth-pair layout needs fewer than 2^32 padded values");
-        if (pairs_ok) {
-            c->nvqp = ctx_alloc<int64_t>(c, 4 * nn + 1);
-            c->ndstp = ctx_alloc<uint32_t>(c, nr);
-            c->nvalp = ctx_alloc<double>(c, c->npad + 2);
-            if (!c->nvqp || !c->ndstp || !c->nvalp) return bail(LSQR_E_OOM, "device allocation failed");
-            CR_TRY(hipMemcpy(c->nvqp, nvqp.data(), (4 * nn + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-            CR_TRY(hipMemcpy(c->ndstp, dstp.data(), nr * sizeof(uint32_t), hipMemcpyHostToDevice));
-            CR_TRY(hipMemsetAsync(c->nvalp, 0, (c->npad + 2) * sizeof(double), st));
-            launch_gather_runs(st, nr, c->nsrc, c->ndstp, c->ndesc, c->va, c->nvalp, 8);
+    if (groups_fit && !device_groups) {   // grids past the device planner's: grouped on the host
+        std::vector<int64_t> hrp;
+        std::vector<int32_t> hci;
+        const int64_t *hrow = G->row_ptr;
+        const int32_t *hcol = G->col_idx;
+        if (G->mem == LSQR_MEM_DEVICE) {
+            hrp.resize((size_t)m + 1);
+            hci.resize((size_t)nnz);
+            CR_TRY(hipMemcpyAsync(hrp.data(), c->rp, (m + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, st));
+            CR_TRY(hipMemcpyAsync(hci.data(), c->ci, nnz * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+            CR_TRY(hipStreamSynchronize(st));
+            hrow = hrp.data();
+            hcol = hci.data();
         }
-        if (G->nz <= 32) {        // row order of the runs, for the batched forward product
-            std::vector<int64_t> rrp;
-            std::vector<uint32_t> rrid;
-            row_order_of_runs(NR, m, rrp, rrid);
-            c->rrp = ctx_alloc<int64_t>(c, m + 1);
-            c->rrid = ctx_alloc<uint32_t>(c, nr);
-            if (!c->rrp || !c->rrid) return bail(LSQR_E_OOM, "device allocation failed");
-            CR_TRY(hipMemcpy(c->rrp, rrp.data(), (m + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-            CR_TRY(hipMemcpy(c->rrid, rrid.data(), nr * sizeof(uint32_t), hipMemcpyHostToDevice));
-        }
-        use_nruns = true;
-    }
-    // row groups with local columns (index the CSR values directly).  auto:
-    // for rows of the pipelined length (64 lanes) when the groups' column
-    // lists hold at most half as many columns as there are stored entries
-    // (the staging pass then costs well under the per-entry gathers it
-    // replaces; measured faster on gfx950 for the tomography rows)
-    const bool groups_auto = o.row_format == 0 && !o.lanes_per_row && pick_lanes(avg_row) == 64;
-    if ((o.row_format == 4 || groups_auto) && nnz > 0) {
-        // the group size: the longest row rounded up to a multiple of 1024
-        int64_t longest = 0;
-        for (int64_t i = 0; i < m; ++i) longest = std::max<int64_t>(longest, hrow[i + 1] - hrow[i]);
-        const int64_t cap = std::max<int64_t>(1024, (longest + 1023) / 1024 * 1024);
         RowGroups RG;
-        const bool built = cap <= kLcolMaxCap && build_row_groups_host(m, n, hrow, hcol, (int)cap, RG);
+        const bool built = build_row_groups_host(m, n, hrow, hcol, (int)cap, RG);
         if (!built && o.row_format == 4)
             return bail(LSQR_E_UNSUPPORTED, "row groups need rows of at most 7168 entries and m < 2^31");
         if (built && (o.row_format == 4 || 2 * RG.gcp.back() <= nnz)) {
@@ -617,9 +637,9 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
             if (c->ngcols)
                 CR_TRY(hipMemcpy(c->gcol, RG.gcol.data(), c->ngcols * sizeof(int32_t), hipMemcpyHostToDevice));
             CR_TRY(hipMemcpy(c->slot, RG.slot.data(), nnz * sizeof(uint16_t), hipMemcpyHostToDevice));
-            CR_TRY(hipMemset(c->slot + nnz, 0, 8 * sizeof(uint16_t)));
         }
     }
+    if (c->slot) CR_TRY(hipMemsetAsync(c->slot + nnz, 0, 8 * sizeof(uint16_t), st));
     // FP64 formats
     c->R64.vt = VT_F64; c->R64.rp = c->rp; c->R64.ci = c->ci; c->R64.val = c->va;
     c->R64.lpr = o.lanes_per_row ? o.lanes_per_row : pick_lanes(avg_row);
@@ -649,8 +669,24 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
         if (use_jacobi) launch_jacobi(st, c->P, c->C64, c->d);
     }
     // the solver's formats
-    RowFmt R = c->R64;
+    RowFmt F = c->R64;
     ColFmt C = c->C64;
+    uint32_t *start = nullptr;           // run positions of one more layout
+    if (use_nruns && o.precision != LSQR_FP64) {
+        start = (uint32_t *)temp(R.nr * sizeof(uint32_t));
+        if (!start) return bail(LSQR_E_OOM, "device allocation failed");
+    }
+    // the values `src` (elem bytes each) W depths to a word, as the solver's
+    auto wide_layout = [&](int W, const void *src, int elem, void **vals) -> lsqr_status {
+        c->npad4 = (int64_t)padded[W == 4 ? 1 : 2];
+        if (c->npad4 + 2 >= ((int64_t)1 << 32))
+            return fail(c, LSQR_E_UNSUPPORTED, "the wide depth layout needs fewer than 2^32 padded values");
+        const lsqr_status q = build_layout(c, R, W, c->npad4, start, src, elem, &c->nvqp4, vals);
+        C.nvq = c->nvqp4;
+        C.val = *vals;
+        C.pairs = W;
+        return q;
+    };
     if (use_nruns) {
         C.nrp = c->nrp; C.nvq = c->nvq; C.nrow = c->nrow; C.ndesc = c->ndesc;
         C.norder = c->norder; C.val = c->nval;
@@ -663,7 +699,7 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
         if (!c->va32 || !c->cv32) return bail(LSQR_E_OOM, "device allocation failed");
         launch_convert_f32(st, nnz + 8, c->va, c->va32);
         launch_convert_f32(st, nnz, c->cv, c->cv32);
-        R.vt = VT_F32; R.val = c->va32;
+        F.vt = VT_F32; F.val = c->va32;
         C.vt = VT_F32; C.val = c->cv32;
         if (use_nruns) {
             c->nval32 = ctx_alloc<float>(c, nnz);
@@ -671,11 +707,8 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
             launch_convert_f32(st, nnz, c->nval, c->nval32);
             C.val = c->nval32;
             if (c->nvalp && kF32FourDepths) {   // four depths to a word (one 16-byte load)
-                lsqr_status q4 = build_four_depth(c, NR, G->nz, c->va32, 4, 4, (void **)&c->nvalp4f);
-                if (q4 != LSQR_OK) { const std::string m = c->err; return bail(q4, m); }
-                C.val = c->nvalp4f;
-                C.nvq = c->nvqp4;
-                C.pairs = 4;
+                lsqr_status q4 = wide_layout(4, c->va32, 4, (void **)&c->nvalp4f);
+                if (q4 != LSQR_OK) { const std::string msg = c->err; return bail(q4, msg); }
             } else if (c->nvalp) {
                 c->nvalp32 = ctx_alloc<float>(c, c->npad + 2);
                 if (!c->nvalp32) return bail(LSQR_E_OOM, "device allocation failed");
@@ -699,32 +732,27 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
         CR_TRY(hipMemsetAsync(c->qrow + nnz, 0, 8 * sizeof(uint16_t), st));
         launch_quantise_rows(st, m, c->rp, c->va, c->sigma, vt, c->qrow);
         launch_quantise_cols(st, nnz, c->ri, c->cv, c->sigma, vt, c->qcol);
-        R.vt = vt; R.val = c->qrow; R.sigma = c->sigma;
+        F.vt = vt; F.val = c->qrow; F.sigma = c->sigma;
         C.vt = vt; C.val = c->qcol;
         if (use_nruns) {      // the same codes, node-major
-            c->nvalq = ctx_alloc<uint16_t>(c, nnz);
-            if (!c->nvalq) return bail(LSQR_E_OOM, "device allocation failed");
-            launch_gather_runs(st, c->nnruns, c->nsrc, c->ndst, c->ndesc, c->qrow, c->nvalq, 2);
-            C.val = c->nvalq;
-            if (c->nvalp) {   // the codes kQDepths depths to a word (one 8- or 16-byte load)
-                lsqr_status q4 = build_four_depth(c, NR, G->nz, c->qrow, 2, kQDepths, (void **)&c->nvalpq);
-                if (q4 != LSQR_OK) { const std::string m = c->err; return bail(q4, m); }
-                C.val = c->nvalpq;
-                C.nvq = c->nvqp4;
-                C.pairs = kQDepths;
+            if (c->nvalp) {   // kQDepths depths to a word (one 8- or 16-byte load)
+                lsqr_status q4 = wide_layout(kQDepths, c->qrow, 2, (void **)&c->nvalpq);
+                if (q4 != LSQR_OK) { const std::string msg = c->err; return bail(q4, msg); }
+            } else {          // as the plain node-run values, whose offsets C.nvq holds
+                c->nvalq = ctx_alloc<uint16_t>(c, nnz);
+                if (!c->nvalq) return bail(LSQR_E_OOM, "device allocation failed");
+                CR_TRY(plan_layout(st, c->al, nn, R, 1, nnz, start, c->nvq));
+                launch_gather_runs(st, R.nr, R.nsrc, start, R.ndesc, 1, c->qrow, c->nvalq, 2);
+                C.val = c->nvalq;
             }
         }
         vec = VT_F32;
     }
-    lsqr_status s = setup_engine(c, c->eng, vec, R, C);
+    lsqr_status s = setup_engine(c, c->eng, vec, F, C);
     if (s != LSQR_OK) return bail(s, g_err);
     CR_TRY(hipGetLastError());
     CR_TRY(hipStreamSynchronize(st));
-    if (use_nruns) {          // the run map is only needed for the value gathers
-        ctx_release(c, c->nsrc);
-        ctx_release(c, c->ndst);
-        c->nsrc = c->ndst = nullptr;
-    }
+    for (void *p : tmp) ctx_release(c, p);
     *out = c;
     return LSQR_OK;
 #undef CR_TRY

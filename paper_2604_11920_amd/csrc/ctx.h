@@ -86,13 +86,13 @@ struct lsqr_ctx {
     int64_t *nrp = nullptr, *nvq = nullptr; uint32_t *nrow = nullptr; uint16_t *ndesc = nullptr;
     int32_t *norder = nullptr; double *nval = nullptr; float *nval32 = nullptr;
     int64_t *rrp = nullptr; uint32_t *rrid = nullptr;   // row order of the node runs (batched forward)
-    uint16_t *nvalq = nullptr; uint32_t *nsrc = nullptr, *ndst = nullptr;
+    uint16_t *nvalq = nullptr;
     int64_t nnruns = 0;
     // depth-pair layout of the node-run values (k_adj_npair)
-    int64_t *nvqp = nullptr; uint32_t *ndstp = nullptr; int64_t npad = 0;
+    int64_t *nvqp = nullptr; int64_t npad = 0;
     double *nvalp = nullptr; float *nvalp32 = nullptr; uint16_t *nvalpq = nullptr;
-    // the 16-bit codes in the four-depth layout (mixed forms)
-    int64_t *nvqp4 = nullptr; uint32_t *ndstp4 = nullptr; int64_t npad4 = 0;
+    // the solver's values four (FP32) or eight (16-bit codes) depths to a word
+    int64_t *nvqp4 = nullptr; int64_t npad4 = 0;
     float *nvalp4f = nullptr;     // FP32 node-run values in the four-depth layout
     // row groups with local columns (forward product over va)
     int32_t *gp = nullptr, *gcol = nullptr; int64_t *gcp = nullptr; uint16_t *slot = nullptr;

@@ -193,12 +193,12 @@ void launch_finalize(hipStream_t st, const Problem &P, int grid, const double *d
 void launch_scale_vec(hipStream_t st, int64_t n, const double *d, const double *x, double *z);
 void launch_fill(hipStream_t st, int64_t n, double value, double *x);
 void launch_jacobi(hipStream_t st, const Problem &P, const ColFmt &C, double *d);
-void launch_check_csr(hipStream_t st, int64_t m, int64_t n, const int64_t *row_ptr,
-                      const int32_t *col, const double *val, int *flag);
 void launch_check_vec(hipStream_t st, int64_t n, const double *x, int positive, int *flag);
-// out[dst[r] + e] = in[src[r] + e] for e < len(desc[r]) (elements of elem_bytes = 2, 4 or 8)
-void launch_gather_runs(hipStream_t st, int64_t nr, const uint32_t *src, const uint32_t *dst,
-                        const uint16_t *desc, const void *in, void *out, int elem_bytes);
+// The values of the node runs in the layout of W depths to a word (W = 1:
+// plain), run r from start[r] on: iz0 mod W zeros, its len values in[src[r]
+// ..], zeros up to a multiple of W (elements of elem_bytes = 2, 4 or 8).
+void launch_gather_runs(hipStream_t st, int64_t nr, const uint32_t *src, const uint32_t *start,
+                        const uint16_t *desc, int W, const void *in, void *out, int elem_bytes);
 void launch_convert_f32(hipStream_t st, int64_t nnz, const double *src, float *dst);
 void launch_row_scales(hipStream_t st, int64_t m, const int64_t *rp, const double *val, int vt,
                        float *sigma);
@@ -222,5 +222,54 @@ struct Allocator {
 hipError_t build_transpose(hipStream_t st, Allocator &al, int64_t m, int64_t n, int64_t nnz,
                            const int64_t *rp, const int32_t *ci, const double *val,
                            int64_t *col_ptr, int32_t *row_idx, double *cval, std::string &err);
+
+// ptr[c] = first position whose key is >= c, c = 0 .. n (keys ascending).
+void launch_key_ptr(hipStream_t st, int64_t count, int64_t n, const uint32_t *keys, int64_t *ptr);
+
+// Planning of the stored formats on the device (plan.hip).  The runs of a
+// CSR structure (maximal stretches of consecutive columns inside one lateral
+// node), in row order and in node-major order (rows ascending); nz <= 64,
+// nnz < 2^32.
+struct RunPlan {
+    int64_t nr = 0;
+    int64_t *rrp = nullptr;                        // [m+1] runs of row i: rrp[i] .. rrp[i+1]-1
+    uint32_t *src = nullptr, *row = nullptr;       // [nr] position of the first value, row
+    uint32_t *col0 = nullptr;                      // [nr] first column
+    uint8_t *len = nullptr;                        // [nr]
+    int64_t *nrp = nullptr;                        // [nnodes+1]
+    uint32_t *nsrc = nullptr, *nrow = nullptr;     // [nr] node-major: src, row
+    uint16_t *ndesc = nullptr;                     // [nr] (iz0 << 8) | len
+    uint32_t *rrid = nullptr;                      // [nr] node-major index of the row order's runs, or nullptr
+    int32_t *norder = nullptr;                     // [nnodes] by decreasing run count, stable
+};
+// Columns a device-planned row group can index (its column set sits in LDS as
+// bits, 32 KB, with a rank per word, 16 KB); larger grids group on the host.
+constexpr int64_t kPlanMaxCols = (int64_t)1 << 18;
+bool plan_groups_fit(int64_t n, int nz);
+// cnt[i] = runs of row i; info[0] = validation flags of the CSR (when check
+// holds its values: 1 row_ptr, 2 column range, 4 column order, 8 non-finite),
+// info[1] = longest row.
+hipError_t plan_scan_rows(hipStream_t st, int64_t m, int64_t n, int64_t nnz, int nz, const int64_t *rp,
+                          const int32_t *ci, const double *check, uint32_t *cnt, int *info);
+hipError_t plan_row_runs(hipStream_t st, Allocator &al, int64_t m, const uint32_t *cnt, int64_t *rrp, int64_t *nr);
+// Fills R's row order and key / idx (node and position of every run).
+hipError_t plan_emit_runs(hipStream_t st, int64_t m, int nz, const int64_t *rp, const int32_t *ci,
+                          const RunPlan &R, uint32_t *key, uint32_t *idx);
+// Fills R's node-major order; padded[0..2] = value positions of the layouts of
+// 2, 4 and 8 depths to a word.  key and idx are overwritten.
+hipError_t plan_node_runs(hipStream_t st, Allocator &al, int64_t nn, int nz, RunPlan &R, uint32_t *key,
+                          uint32_t *idx, uint64_t *padded);
+// Value position of every run (start) and of every node's quarters (nvq) in
+// the layout of W depths to a word, `total` positions in all.
+hipError_t plan_layout(hipStream_t st, Allocator &al, int64_t nn, const RunPlan &R, int W, int64_t total,
+                       uint32_t *start, int64_t *nvq);
+hipError_t plan_csc(hipStream_t st, Allocator &al, int64_t n, int nz, int64_t nnz, const RunPlan &R,
+                    const double *va, int64_t *cp, int32_t *ri, double *cv);
+hipError_t plan_group_bounds(hipStream_t st, Allocator &al, int64_t m, int64_t n, int cap, const RunPlan &R,
+                             std::vector<int32_t> &gp);
+hipError_t plan_group_sizes(hipStream_t st, Allocator &al, int64_t n, int ng, const int32_t *gp, const RunPlan &R,
+                            int64_t *gcp, int64_t *total);
+hipError_t plan_group_lists(hipStream_t st, int64_t n, int ng, const int32_t *gp, const RunPlan &R,
+                            const int64_t *rp, const int32_t *ci, const int64_t *gcp, int32_t *gcol, uint16_t *slot);
 
 }  // namespace lsqr

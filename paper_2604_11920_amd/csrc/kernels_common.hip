@@ -281,33 +281,6 @@ void launch_jacobi(hipStream_t st, const Problem &P, const ColFmt &C, double *d)
                        (int)P.n, P.nx, P.ny, P.nz, P.w, P.damp, C.cp, (const double *)C.val, d);
 }
 
-// Validation of a device-resident CSR: bit 1 row_ptr decreasing, bit 2 column
-// out of range, bit 4 columns not strictly increasing, bit 8 non-finite value.
-__global__ void k_check_csr(int64_t m, int64_t n, const int64_t *rp, const int32_t *ci,
-                            const double *va, int *flag)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t s = rp[i], e = rp[i + 1];
-        int f = 0;
-        if (e < s) f |= 1;
-        for (int64_t p = s; p < e && !(f & 1); ++p) {
-            const int c = ci[p];
-            if (c < 0 || c >= n) f |= 2;
-            if (p > s && c <= ci[p - 1]) f |= 4;
-            if (!isfinite(va[p])) f |= 8;
-        }
-        if (f) atomicOr(flag, f);
-    }
-}
-
-void launch_check_csr(hipStream_t st, int64_t m, int64_t n, const int64_t *row_ptr,
-                      const int32_t *col, const double *val, int *flag)
-{
-    hipLaunchKernelGGL(k_check_csr, dim3(blocks_for(m, kBlock, 8192)), dim3(kBlock), 0, st, m, n,
-                       row_ptr, col, val, flag);
-}
-
 // bit 1 non-finite, bit 2 not positive (when positive != 0).
 __global__ void k_check_vec(int64_t n, const double *x, int positive, int *flag)
 {
@@ -490,35 +463,40 @@ void launch_sum_partials(hipStream_t st, const double *part, int np, double *out
 
 namespace lsqr {
 
+// 16 lanes per run: a run's values leave and arrive as one segment (a thread
+// per run wrote 64 segments at a time: 2.4 ms for 100 M FP64 values, now
+// 0.97 ms), and the zeros of its padding are written on the way.
 template <class T>
-__global__ void k_gather_runs(int64_t nr, const uint32_t *src, const uint32_t *dst,
-                              const uint16_t *desc, const T *in, T *out)
+__global__ __launch_bounds__(256) void k_gather_runs(int64_t nr, const uint32_t *src, const uint32_t *start,
+                                                     const uint16_t *desc, int W, const T *in, T *out)
 {
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < nr;
-         r += (int64_t)gridDim.x * blockDim.x) {
-        const int len = desc[r] & 255;
-        const int64_t s = src[r], d = dst[r];
-        for (int e = 0; e < len; ++e) out[d + e] = in[s + e];
+    const int e0 = threadIdx.x & 15;
+    for (int64_t r = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 4; r < nr; r += (int64_t)gridDim.x * 16) {
+        const int d = desc[r], len = d & 255, pre = (d >> 8) & (W - 1);
+        const int tot = (len + pre + W - 1) & ~(W - 1);
+        const T *s = in + src[r];
+        T *o = out + start[r];
+        for (int e = e0; e < tot; e += 16) o[e] = (unsigned)(e - pre) < (unsigned)len ? s[e - pre] : (T)0;
     }
 }
 
-void launch_gather_runs(hipStream_t st, int64_t nr, const uint32_t *src, const uint32_t *dst,
-                        const uint16_t *desc, const void *in, void *out, int elem_bytes)
+void launch_gather_runs(hipStream_t st, int64_t nr, const uint32_t *src, const uint32_t *start,
+                        const uint16_t *desc, int W, const void *in, void *out, int elem_bytes)
 {
     if (nr <= 0) return;
-    const int grid = (int)std::min<int64_t>((nr + 255) / 256, 65536);
+    const int grid = (int)std::min<int64_t>((nr + 15) / 16, 65536);
     switch (elem_bytes) {
     case 8:
-        hipLaunchKernelGGL(k_gather_runs<uint64_t>, dim3(grid), dim3(256), 0, st, nr, src, dst,
-                           desc, (const uint64_t *)in, (uint64_t *)out);
+        hipLaunchKernelGGL(k_gather_runs<uint64_t>, dim3(grid), dim3(256), 0, st, nr, src, start,
+                           desc, W, (const uint64_t *)in, (uint64_t *)out);
         break;
     case 4:
-        hipLaunchKernelGGL(k_gather_runs<uint32_t>, dim3(grid), dim3(256), 0, st, nr, src, dst,
-                           desc, (const uint32_t *)in, (uint32_t *)out);
+        hipLaunchKernelGGL(k_gather_runs<uint32_t>, dim3(grid), dim3(256), 0, st, nr, src, start,
+                           desc, W, (const uint32_t *)in, (uint32_t *)out);
         break;
     default:
-        hipLaunchKernelGGL(k_gather_runs<uint16_t>, dim3(grid), dim3(256), 0, st, nr, src, dst,
-                           desc, (const uint16_t *)in, (uint16_t *)out);
+        hipLaunchKernelGGL(k_gather_runs<uint16_t>, dim3(grid), dim3(256), 0, st, nr, src, start,
+                           desc, W, (const uint16_t *)in, (uint16_t *)out);
         break;
     }
 }

@@ -1,4 +1,5 @@
-// Device transpose CSR -> CSC.
+// Device transpose CSR -> CSC, for matrices without node runs (those derive
+// the CSC from the runs, plan.hip).
 //
 // The transposed product of LSQR reads G^T from a stored copy instead of
 // scattering with atomics.  The copy is built once per system: a stable LSD
@@ -84,6 +85,13 @@ static int grid_for(int64_t work)
     return (int)(b < 1 ? 1 : (b > 65536 ? 65536 : b));
 }
 
+void launch_key_ptr(hipStream_t st, int64_t count, int64_t n, const uint32_t *keys, int64_t *ptr)
+{
+    if (count > 0)
+        hipLaunchKernelGGL(k_col_ptr, dim3(grid_for(count)), dim3(256), 0, st, count, n, keys, ptr);
+    hipLaunchKernelGGL(k_col_ptr_tail, dim3(grid_for(n + 1)), dim3(256), 0, st, count, n, keys, ptr);
+}
+
 hipError_t build_transpose(hipStream_t st, Allocator &al, int64_t m, int64_t n, int64_t nnz,
                            const int64_t *rp, const int32_t *ci, const double *val,
                            int64_t *col_ptr, int32_t *row_idx, double *cval, std::string &err)
@@ -93,8 +101,7 @@ hipError_t build_transpose(hipStream_t st, Allocator &al, int64_t m, int64_t n, 
         return hipErrorInvalidValue;
     }
     if (nnz == 0) {
-        hipLaunchKernelGGL(k_col_ptr_tail, dim3(grid_for(n + 1)), dim3(256), 0, st, nnz, n,
-                           (const uint32_t *)nullptr, col_ptr);
+        launch_key_ptr(st, nnz, n, nullptr, col_ptr);
         return hipGetLastError();
     }
     const size_t kb = (size_t)nnz * sizeof(uint32_t);
@@ -124,10 +131,7 @@ hipError_t build_transpose(hipStream_t st, Allocator &al, int64_t m, int64_t n, 
         if (rc != hipSuccess) { err = "transpose: radix sort failed"; goto out; }
         hipLaunchKernelGGL(k_gather_csc, dim3(grid_for(nnz)), dim3(256), 0, st, nnz,
                            vals.current(), rowid, val, row_idx, cval);
-        hipLaunchKernelGGL(k_col_ptr, dim3(grid_for(nnz)), dim3(256), 0, st, nnz, n,
-                           keys.current(), col_ptr);
-        hipLaunchKernelGGL(k_col_ptr_tail, dim3(grid_for(n + 1)), dim3(256), 0, st, nnz, n,
-                           keys.current(), col_ptr);
+        launch_key_ptr(st, nnz, n, keys.current(), col_ptr);
         rc = hipGetLastError();
         if (rc == hipSuccess) rc = hipStreamSynchronize(st);
         if (rc != hipSuccess) err = "transpose: kernel launch failed";
