@@ -189,7 +189,9 @@ typedef struct lsqr_ctx lsqr_ctx;
 
 /* Kernel timing (LSQR_FLAG_TIMING): totals over the last solve. */
 typedef struct {
-    double fwd_ms;              /* forward products Abar D v                          */
+    double fwd_ms;              /* forward products Abar D v (grids of at most 6,144   */
+                                /* unknowns with short rows: with the previous         */
+                                /* iteration's update, which shares their launch)      */
     double adj_ms;              /* transposed products D Abar^T u                      */
     int fwd_launches;
     int adj_launches;

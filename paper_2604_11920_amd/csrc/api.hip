@@ -101,14 +101,12 @@ constexpr int kQDepths = LSQR_Q_DEPTHS;
 // W depths to a word: every run from a position that is a multiple of W,
 // zeros before its first depth's offset in the word and after its end, W
 // zeros after the last run (total positions before them).  *vals and *nvq
-// (the layout's quarter offsets) are kept in the context; start is scratch
-// for nr positions.
 static lsqr_status build_layout(lsqr_ctx *c, const RunPlan &R, int W, int64_t total, uint32_t *start,
                                 const void *src, int elem_bytes, int64_t **nvq, void **vals)
 {
     hipStream_t st = c->st;
     const int64_t nn = c->P.n / c->P.nz;
-    *nvq = ctx_alloc<int64_t>(c, 4 * nn + 1);
+    *nvq = ctx_alloc<int64_t>(c, kNodeParts * nn + 1);
     *vals = ctx_alloc_bytes(c, (size_t)(total + W) * elem_bytes);
     if (!*nvq || !*vals) return fail(c, LSQR_E_OOM, "device allocation failed");
     HIP_TRY(c, plan_layout(st, c->al, nn, R, W, total, start, *nvq));
@@ -170,10 +168,29 @@ lsqr_status setup_engine(lsqr_ctx *c, Engine &E, int vec, const RowFmt &R, const
         E.hbar = ctx_alloc<double>(c, n);
         if (!E.hbar) return fail(c, LSQR_E_OOM, "device allocation failed");
     }
-    E.P1 = ctx_alloc<double>(c, E.g_fwd);
+    E.P1 = ctx_alloc<double>(c, std::max(E.g_fwd, 1024));
     E.P2 = ctx_alloc<double>(c, E.g_adj);
     E.P3 = ctx_alloc<double>(c, E.g_upd);
     E.ctl = ctx_alloc<int>(c, C_WORDS);
+    if (c->col16 && m > 0 && !R.slot) {
+        // fused iterations: workgroups of 256 threads where all rows fit one
+        // turn of them (and n their 6 elements per thread), else of 1,024; one
+        // per compute unit at most, rows balanced in entries, at most one
+        // unknown per thread in the sweeps
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) {
+            E.l_small = small_lanes(R.vt, (double)c->P.nnz / (double)m);
+            E.t_small = n <= 6 * 256 && m <= 2 * (256 / E.l_small) * (int64_t)cus ? 256 : 1024;
+            const int64_t rows = 2 * (E.t_small / E.l_small);
+            E.g_small = (int)std::max<int64_t>(std::min<int64_t>((m + rows - 1) / rows, cus),
+                                               (n + E.t_small - 1) / E.t_small);
+            E.cur = ctx_alloc<double>(c, 2 * kStateWords);
+            E.srow = ctx_alloc<int32_t>(c, E.g_small + 1);
+            if (!E.cur || !E.srow) return fail(c, LSQR_E_OOM, "device allocation failed");
+            launch_wave_rows(c->st, R.rp, m, E.g_small, E.srow);
+        }
+    }
     if (!E.T[0] || !E.T[1] || (R.sigma && !E.Ts) || !E.q || !E.v || !E.z || !E.vzero || !E.w ||
         !E.y || !E.P1 || !E.P2 || !E.P3 || !E.ctl)
         return fail(nullptr, LSQR_E_OOM, "device allocation failed");
@@ -199,16 +216,30 @@ void launch_iteration(lsqr_ctx *c, Engine &E, hipStream_t st, int p, double tol,
 {
     const Problem &P = c->P;
     void *Tprev = E.T[p], *Tcur = E.T[1 - p];
-    if (timing) (void)hipEventRecord(c->ev[4 * slot + 0], st);
-    launch_fwd(st, P, E.g_fwd, E.vec, E.R, E.z, Tprev, Tcur, E.Ts, E.P1, E.P3, E.g_upd, E.S,
-               E.ctl, p, tol, MODE_ITER);
-    if (timing) (void)hipEventRecord(c->ev[4 * slot + 1], st);
-    if (timing) (void)hipEventRecord(c->ev[4 * slot + 2], st);
+    const bool fused = E.g_small > 0;    // the update of the previous iteration is in the forward launch
+    auto mark = [&](int i) { if (timing) (void)hipEventRecord(c->ev[4 * slot + i], st); };
+    mark(0);
+    if (fused) {
+        SmallStep q;
+        q.R = &E.R; q.col16 = c->col16; q.wrow = E.srow; q.grid = E.g_small;
+        q.threads = E.t_small; q.lanes = E.l_small;
+        q.d = c->d; q.z = E.z; q.q = E.q; q.v = E.v; q.w = E.w; q.y = E.y; q.hbar = E.hbar;
+        q.Tprev = Tprev; q.Tcur = Tcur; q.Ts = E.Ts;
+        q.part_t = E.P1; q.part_q = E.P2; q.np_q = E.g_adj; q.part_v = E.P3; q.np_v = E.g_upd;
+        q.S = E.S; q.cur = E.cur; q.ctl = E.ctl; q.parity = p; q.tol = tol;
+        launch_small(st, P, E.vec, q);
+    } else {
+        launch_fwd(st, P, E.g_fwd, E.vec, E.R, E.z, Tprev, Tcur, E.Ts, E.P1, E.P3, E.g_upd, E.S,
+                   E.ctl, p, tol, MODE_ITER);
+    }
+    mark(1);
+    mark(2);
     launch_adj(st, P, E.g_adj, E.vec, E.C, c->d, Tcur, E.Ts ? E.Ts : Tcur, E.v, E.q, E.P2, E.P1,
-               E.g_fwd, E.S, E.ctl, p, MODE_ITER, 0);
-    if (timing) (void)hipEventRecord(c->ev[4 * slot + 3], st);
-    launch_update(st, P, E.g_upd, E.vec, c->d, E.q, E.v, E.w, E.y, E.z, E.P3, E.P2, E.g_adj, E.S,
-                  E.ctl, p, MODE_ITER, E.hbar);
+               fused ? E.g_small : E.g_fwd, E.S, E.ctl, p, MODE_ITER, 0, fused ? E.cur : nullptr);
+    mark(3);
+    if (!fused)
+        launch_update(st, P, E.g_upd, E.vec, c->d, E.q, E.v, E.w, E.y, E.z, E.P3, E.P2, E.g_adj, E.S,
+                      E.ctl, p, MODE_ITER, E.hbar);
 }
 
 lsqr_status build_graph(lsqr_ctx *c, Engine &E, int iters, double tol)
@@ -254,9 +285,9 @@ lsqr_status engine_solve(lsqr_ctx *c, Engine &E, const double *rhs, int full, in
     launch_init(st, P, E.g_fwd, E.vec, rhs, full, E.T[0], E.R.sigma, E.Ts, E.y, E.vzero, E.P1,
                 E.ctl, iters);
     launch_adj(st, P, E.g_adj, E.vec, E.C, c->d, E.T[0], E.Ts ? E.Ts : E.T[0], E.vzero, E.q, E.P2,
-               E.P1, E.g_fwd, E.S, E.ctl, 0, MODE_INIT, 0);
+               E.P1, E.g_fwd, E.S, E.ctl, 0, MODE_INIT, 0, E.cur);
     launch_update(st, P, E.g_upd, E.vec, c->d, E.q, E.v, E.w, E.y, E.z, E.P3, E.P2, E.g_adj, E.S,
-                  E.ctl, 0, MODE_INIT, E.hbar);
+                  E.ctl, 0, MODE_INIT, E.hbar, E.cur);
     HIP_TRY(c, hipGetLastError());
     // iterations: blocks of an even number of iterations replayed as one graph
     // (parity returns to 0 after each block); with tol > 0 the host reads the
@@ -286,6 +317,9 @@ lsqr_status engine_solve(lsqr_ctx *c, Engine &E, const double *rhs, int full, in
         if (tol > 0.0 && done % c->check_every == 0 && done < iters && (s = poll()) != LSQR_OK)
             return s;
     }
+    if (E.g_small && done > 0)    // the last iteration's update (nothing to do after a stop)
+        launch_update(st, P, E.g_upd, E.vec, c->d, E.q, E.v, E.w, E.y, E.z, E.P3, E.P2, E.g_adj, E.S,
+                      E.ctl, (done - 1) & 1, MODE_ITER, E.hbar);
     launch_finalize(st, P, E.g_upd, c->d, E.y, out, E.P3, E.g_upd, E.S, E.ctl, tol, accumulate);
     HIP_TRY(c, hipGetLastError());
     if (timing) {
@@ -649,6 +683,14 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
     }
     c->C64.vt = VT_F64; c->C64.cp = c->cp; c->C64.ri = c->ri; c->C64.val = c->cv;
     c->C64.lpc = o.lanes_per_col ? o.lanes_per_col : pick_lanes(avg_col);
+    // rows too short for the pipelined kernels of a small grid: the fused step's
+    // 16-bit columns (col_format and lanes_per_col do not matter to it)
+    if (o.row_format == 0 && !o.lanes_per_row && c->R64.lpr < 64 && nnz > 0 && n <= kSmallCols) {
+        c->col16 = ctx_alloc<uint16_t>(c, nnz + 8);   // zeros past the end (entries four at a time)
+        if (!c->col16) return bail(LSQR_E_OOM, "device allocation failed");
+        launch_col16(st, nnz, c->ci, c->col16);
+        CR_TRY(hipMemsetAsync(c->col16 + nnz, 0, 8 * sizeof(uint16_t), st));
+    }
     // column scaling
     launch_fill(st, n, 1.0, c->ones);
     if (o.precond == LSQR_PRECOND_NONE) {
@@ -691,6 +733,7 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
         C.nrp = c->nrp; C.nvq = c->nvq; C.nrow = c->nrow; C.ndesc = c->ndesc;
         C.norder = c->norder; C.val = c->nval;
         if (c->nvalp) { C.nvq = c->nvqp; C.val = c->nvalp; C.pairs = 2; }
+        C.waves = adj_node_waves(nn, c->nnruns);
     }
     int vec = VT_F64;
     if (o.precision == LSQR_FP32) {
@@ -1183,6 +1226,7 @@ lsqr_status lsqr_apply_t(lsqr_ctx *c, const double *y, double *x)
         C.nrp = c->nrp; C.nvq = c->nvq; C.nrow = c->nrow; C.ndesc = c->ndesc;
         C.norder = c->norder; C.val = c->nval;
         if (c->nvalp) { C.nvq = c->nvqp; C.val = c->nvalp; C.pairs = 2; }
+        C.waves = adj_node_waves(c->P.n / c->P.nz, c->nnruns);
     }
     launch_adj(c->st, c->P, std::min(2048, c->eng.g_adj), VT_F64, C, c->d, y, y, nullptr, x,
                c->Pa, nullptr, 0, nullptr, nullptr, 0, MODE_OPERATOR, 0);

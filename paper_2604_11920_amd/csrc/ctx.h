@@ -27,6 +27,11 @@ struct Engine {
     double *S = nullptr;
     int64_t s_rows = 0;
     int *ctl = nullptr;
+    // fused iterations of small systems (k_fwd_small): the state rows of the
+    // last two iterations by parity, workgroups and their row ranges
+    double *cur = nullptr;
+    int g_small = 0, t_small = 0, l_small = 0;   // workgroups, threads, lanes per row
+    int32_t *srow = nullptr;
     hipGraphExec_t gexec = nullptr;
     int graph_iters = 0;
     double graph_tol = -1.0;
@@ -96,6 +101,7 @@ struct lsqr_ctx {
     float *nvalp4f = nullptr;     // FP32 node-run values in the four-depth layout
     // row groups with local columns (forward product over va)
     int32_t *gp = nullptr, *gcol = nullptr; int64_t *gcp = nullptr; uint16_t *slot = nullptr;
+    uint16_t *col16 = nullptr;      // 16-bit columns of the fused small step
     int ngroups = 0, gcap = 0;
     int64_t ngcols = 0;
     double *d = nullptr, *ones = nullptr;

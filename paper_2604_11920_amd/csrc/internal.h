@@ -54,6 +54,7 @@ enum CtlField {
     C_CNT0 = 4,     // iteration counter read by iterations of parity 0
     C_CNT1 = 5,     // ... parity 1
     C_KMAX = 6,     // iteration limit of the current solve
+    C_REQ = 7,      // fused iterations: a stop the forward kernel asked for
     C_WORDS = 8,
 };
 
@@ -137,6 +138,33 @@ static inline bool lcol_octs_ok(const RowFmt &R)
            ((uintptr_t)R.slot & 15u) == 0;
 }
 
+// Parts of a node's runs with a stored value offset: a kernel whose 4 or 16
+// waves share a node starts them there.
+constexpr int kNodeParts = 16;
+// Waves that share a node's runs in the transposed product (depth-pair
+// layouts): 16 on grids of up to kWideNodes nodes, where a workgroup of 4 waves
+// per node leaves most of the device idle, if a node has runs for more than 4
+// waves of one chunk (64 runs) each; else 4.  Transposed product, 4 -> 16 waves
+// (us): 256 nodes, 5,300 runs each, FP64 65 -> 30, BF16 51 -> 19; 484 nodes,
+// 1,340 runs 24 -> 17, 17 -> 14; 729 nodes 45 -> 36, 32 -> 27; 1,024 nodes 60 -> 60,
+// 34 -> 40; 3,136 nodes 152 -> 179, 69 -> 106.
+constexpr int64_t kWideNodes = 800;
+static inline int adj_node_waves(int64_t nodes, int64_t runs)
+{
+    return nodes <= kWideNodes && runs > 4 * 64 * nodes ? 16 : 4;
+}
+
+// Unknowns of the fused small step (k_fwd_small): D v sits in LDS (48 KB in
+// FP64) and every workgroup forms all of it, 6 elements per thread.
+constexpr int kSmallCols = 6144;
+// Lanes per row of the fused small step, four entries each (eight 16-bit codes:
+// the longest class takes 32 lanes): a row past the lanes' reach of 256, 64 or 16
+// entries is loaded in further turns.
+static inline int small_lanes(int vt, double avg_row)
+{
+    return avg_row > 32 ? (vt_size(vt) == 2 ? 32 : 64) : avg_row > 8 ? 16 : 4;
+}
+
 // Stored transpose (CSC) for the transposed product.
 struct ColFmt {
     int vt = VT_F64;
@@ -147,10 +175,12 @@ struct ColFmt {
     // Node runs (used instead of the CSC when nrp is set; val then holds the
     // values in node-major run order).  Node k = columns [k nz, (k+1) nz).
     const int64_t *nrp = nullptr;      // [nnodes+1] runs of node k: [nrp[k], nrp[k+1])
-    const int64_t *nvq = nullptr;      // [4 nnodes+1] value offset of each quarter of a node's runs
+    const int64_t *nvq = nullptr;      // [kNodeParts nnodes+1] value offset of each part of a node's
+                                       // runs (part w from run r0 + c w / kNodeParts on)
     const uint32_t *nrow = nullptr;    // [nruns] data row of the run
     const uint16_t *ndesc = nullptr;   // [nruns] (iz0 << 8) | len
     const int32_t *norder = nullptr;   // [nnodes] nodes by decreasing work
+    int waves = 4;                     // per node (adj_node_waves)
     int pairs = 0;                     // W = 2, 4 or 8: val / nvq in the layout of W
                                        // depths to a word (k_adj_npair<W>)
 };
@@ -179,12 +209,35 @@ void launch_fwd(hipStream_t st, const Problem &P, int grid, int vec, const RowFm
 void launch_adj(hipStream_t st, const Problem &P, int grid, int vec, const ColFmt &C,
                 const double *d, const void *T, const void *Tg, const void *v, void *q,
                 double *part_out, const double *part_t, int np_t, double *S, int *ctl,
-                int parity, int mode, int data_only);
+                int parity, int mode, int data_only, double *cur = nullptr);
 // hbar != nullptr selects the LSMR step (w then holds LSMR's h).
 void launch_update(hipStream_t st, const Problem &P, int grid, int vec, const double *d,
                    const void *q, void *v, double *w, double *y, void *z, double *part_out,
                    const double *part_q, int np_q, double *S, int *ctl, int parity, int mode,
-                   double *hbar);
+                   double *hbar, double *cur = nullptr);
+// The fused step of small systems (k_fwd_small): iteration k's forward product
+// after the update of iteration k - 1.
+struct SmallStep {
+    const RowFmt *R = nullptr;         // CSR rows (value type, lanes per row)
+    const uint16_t *col16 = nullptr;   // [nnz + 8] columns
+    const int32_t *wrow = nullptr;     // [grid+1] balanced row ranges
+    int grid = 1, threads = 1024, lanes = 64;
+    const double *d = nullptr;
+    const void *z = nullptr, *q = nullptr;
+    void *v = nullptr;
+    double *w = nullptr, *y = nullptr, *hbar = nullptr;
+    const void *Tprev = nullptr;
+    void *Tcur = nullptr, *Ts = nullptr;
+    double *part_t = nullptr;          // out
+    const double *part_q = nullptr, *part_v = nullptr;
+    int np_q = 0, np_v = 0;
+    double *S = nullptr, *cur = nullptr;
+    int *ctl = nullptr;
+    int parity = 0;
+    double tol = 0.0;
+};
+void launch_small(hipStream_t st, const Problem &P, int vec, const SmallStep &q);
+void launch_col16(hipStream_t st, int64_t nnz, const int32_t *ci, uint16_t *col16);
 
 // Helpers (kernels_common.hip).
 void launch_finalize(hipStream_t st, const Problem &P, int grid, const double *d,
@@ -259,7 +312,7 @@ hipError_t plan_emit_runs(hipStream_t st, int64_t m, int nz, const int64_t *rp, 
 // 2, 4 and 8 depths to a word.  key and idx are overwritten.
 hipError_t plan_node_runs(hipStream_t st, Allocator &al, int64_t nn, int nz, RunPlan &R, uint32_t *key,
                           uint32_t *idx, uint64_t *padded);
-// Value position of every run (start) and of every node's quarters (nvq) in
+// Value position of every run (start) and of every node's parts (nvq) in
 // the layout of W depths to a word, `total` positions in all.
 hipError_t plan_layout(hipStream_t st, Allocator &al, int64_t nn, const RunPlan &R, int W, int64_t total,
                        uint32_t *start, int64_t *nvq);

@@ -16,14 +16,16 @@ hipError_t fwd_launch(hipStream_t, const Problem &, int, const RowFmt &, const v
 template <class V>
 hipError_t adj_launch(hipStream_t, const Problem &, int, const ColFmt &, const double *,
                       const void *, const void *, const void *, void *, double *, const double *,
-                      int, double *, int *, int, int, int);
+                      int, double *, int *, int, int, int, double *);
 template <class V>
 hipError_t init_launch(hipStream_t, const Problem &, int, const double *, int, void *,
                        const float *, void *, double *, void *, double *, int *, int);
 template <class V>
 hipError_t update_launch(hipStream_t, const Problem &, int, const double *, const void *, void *,
                          double *, double *, void *, double *, const double *, int, double *,
-                         int *, int, int, double *);
+                         int *, int, int, double *, double *);
+template <class V>
+hipError_t small_launch(hipStream_t, const Problem &, const SmallStep &);
 
 template <class V>
 int fwd_pipe_blocks_per_cu(const RowFmt &);
@@ -155,25 +157,44 @@ void launch_fwd(hipStream_t st, const Problem &P, int grid, int vec, const RowFm
 void launch_adj(hipStream_t st, const Problem &P, int grid, int vec, const ColFmt &C,
                 const double *d, const void *T, const void *Tg, const void *v, void *q,
                 double *part_out, const double *part_t, int np_t, double *S, int *ctl,
-                int parity, int mode, int data_only)
+                int parity, int mode, int data_only, double *cur)
 {
     if (vec == VT_F64)
-        adj_launch<double>(st, P, grid, C, d, T, Tg, v, q, part_out, part_t, np_t, S, ctl, parity, mode, data_only);
+        adj_launch<double>(st, P, grid, C, d, T, Tg, v, q, part_out, part_t, np_t, S, ctl, parity, mode, data_only, cur);
     else
-        adj_launch<float>(st, P, grid, C, d, T, Tg, v, q, part_out, part_t, np_t, S, ctl, parity, mode, data_only);
+        adj_launch<float>(st, P, grid, C, d, T, Tg, v, q, part_out, part_t, np_t, S, ctl, parity, mode, data_only, cur);
 }
 
 void launch_update(hipStream_t st, const Problem &P, int grid, int vec, const double *d,
                    const void *q, void *v, double *w, double *y, void *z, double *part_out,
                    const double *part_q, int np_q, double *S, int *ctl, int parity, int mode,
-                   double *hbar)
+                   double *hbar, double *cur)
 {
     if (vec == VT_F64)
         update_launch<double>(st, P, grid, d, q, v, w, y, z, part_out, part_q, np_q, S, ctl, parity,
-                              mode, hbar);
+                              mode, hbar, cur);
     else
         update_launch<float>(st, P, grid, d, q, v, w, y, z, part_out, part_q, np_q, S, ctl, parity,
-                             mode, hbar);
+                             mode, hbar, cur);
+}
+
+void launch_small(hipStream_t st, const Problem &P, int vec, const SmallStep &q)
+{
+    if (vec == VT_F64) small_launch<double>(st, P, q);
+    else small_launch<float>(st, P, q);
+}
+
+__global__ void k_col16(int64_t nnz, const int32_t *ci, uint16_t *col16)
+{
+    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz;
+         p += (int64_t)gridDim.x * blockDim.x)
+        col16[p] = (uint16_t)ci[p];
+}
+
+void launch_col16(hipStream_t st, int64_t nnz, const int32_t *ci, uint16_t *col16)
+{
+    hipLaunchKernelGGL(k_col16, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((nnz + 255) / 256, 65536))),
+                       dim3(256), 0, st, nnz, ci, col16);
 }
 
 // --------------------------------------------------------------- finalize --

@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kBlock) void k_bfwd_pr32(BArgs a)
         }
         const int64_t rs0 = a.nrp[node], cnt = a.nrp[node + 1] - rs0;
         const int64_t rs = rs0 + cnt * wid / 4, re = rs0 + cnt * (wid + 1) / 4;
-        int64_t vb = a.nvq[4 * (int64_t)node + wid];
+        int64_t vb = a.nvq[kNodeParts * (int64_t)node + 4 * wid];
         for (int64_t base = rs; base < re; base += 64) {
             const int nr = (int)(re - base < 64 ? re - base : 64);
             // every lane loads (lanes past the chunk its last run, masked
@@ -530,7 +530,7 @@ __global__ __launch_bounds__(kBlock) void k_badj_mfma32(BArgs a)
         const int node = a.norder[idx];
         const int64_t rs0 = a.nrp[node], cnt = a.nrp[node + 1] - rs0;
         const int64_t rs = rs0 + cnt * wid / 4, re = rs0 + cnt * (wid + 1) / 4;
-        int64_t vb = a.nvq[4 * (int64_t)node + wid];
+        int64_t vb = a.nvq[kNodeParts * (int64_t)node + 4 * wid];
         floatx16 acc = {};
         for (int64_t base = rs; base < re; base += 64) {
             const int nr = (int)(re - base < 64 ? re - base : 64);
@@ -670,7 +670,7 @@ __global__ __launch_bounds__(kBlock) void k_badj_nruns(BArgs a)
         const int node = a.norder[idx];
         const int64_t rs0 = a.nrp[node], cnt = a.nrp[node + 1] - rs0;
         const int64_t rs = rs0 + cnt * wid / 4, re = rs0 + cnt * (wid + 1) / 4;
-        int64_t vb = a.nvq[4 * (int64_t)node + wid];
+        int64_t vb = a.nvq[kNodeParts * (int64_t)node + 4 * wid];
         float acc[RT];
 #pragma unroll
         for (int r = 0; r < RT; ++r) acc[r] = 0.f;

@@ -167,25 +167,44 @@ __device__ __forceinline__ T group_sum(T v)
     return v;
 }
 
-// Sum over the workgroup (kBlock threads) in a fixed order; every thread
-// receives the same value.
+// As group_sum, in the last lane of each group of W lanes (any W from 2 to 64),
+// on the VALU: row shifts by 1 .. W / 2 leave in lane l the sum of the W lanes
+// up to it (within its row of 16 lanes), the row broadcasts join the rows.
+template <int W, class T>
+__device__ __forceinline__ T group_sum_last(T v)
+{
+    if constexpr (W >= 2) v += dpp_move<0x111, 0xf, true>(v);
+    if constexpr (W >= 4) v += dpp_move<0x112, 0xf, true>(v);
+    if constexpr (W >= 8) v += dpp_move<0x114, 0xf, true>(v);
+    if constexpr (W >= 16) v += dpp_move<0x118, 0xf, true>(v);
+    if constexpr (W >= 32) v += dpp_move<0x142, 0xa, false>(v);
+    if constexpr (W >= 64) v += dpp_move<0x143, 0xc, false>(v);
+    return v;
+}
+
+// Sum over the workgroup (NW waves) in a fixed order; every thread receives
+// the same value.  lds holds NW doubles.
+template <int NW = kBlock / 64>
 __device__ __forceinline__ double block_sum(double v, double *lds)
 {
     v = group_sum<64>(v);
     const int wid = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) lds[wid] = v;
     __syncthreads();
-    double r = ((lds[0] + lds[1]) + lds[2]) + lds[3];
+    double r = lds[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) r += lds[w];
     __syncthreads();
     return r;
 }
 
 // Total of a producer's per-workgroup partials, identical in every workgroup.
+template <int NW = kBlock / 64>
 __device__ __forceinline__ double reduce_partials(const double *p, int np, double *lds)
 {
     double acc = 0.0;
-    for (int i = threadIdx.x; i < np; i += kBlock) acc += p[i];
-    return block_sum(acc, lds);
+    for (int i = threadIdx.x; i < np; i += 64 * NW) acc += p[i];
+    return block_sum<NW>(acc, lds);
 }
 
 // (L x)_p for the 7-point Laplacian, neighbours in the order -x +x -y +y -z +z,
@@ -232,7 +251,7 @@ __global__ __launch_bounds__(kBlock) void k_init_rhs(int64_t m, int64_t n, const
     if (threadIdx.x == 0) part[blockIdx.x] = tot;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         ctl[C_STOP] = 0; ctl[C_ISTOP] = 2; ctl[C_ITERS] = 0; ctl[C_ERR] = 0;
-        ctl[C_CNT0] = 1; ctl[C_CNT1] = 0; ctl[C_KMAX] = kmax;
+        ctl[C_CNT0] = 1; ctl[C_CNT1] = 0; ctl[C_KMAX] = kmax; ctl[C_REQ] = 0;
     }
 }
 
@@ -940,50 +959,91 @@ struct AdjArgs {
     const uint32_t *nrow;
     const uint16_t *ndesc;
     const int32_t *norder;
+    double *cur;             // fused iterations (k_fwd_small): the current state rows, else nullptr
 };
 
 // beta_{k+1} from the forward partials (FP64, fixed order); false when the
 // workgroup has nothing to do (stopped, past the last iteration, breakdown).
+// Fused iterations: a stop the forward kernel asked for takes effect here, and
+// this kernel advances the iteration counter (the update is part of the next
+// forward kernel).
+template <int NW = kBlock / 64>
 __device__ __forceinline__ bool adj_prologue(const AdjArgs &a, double &beta, double *lds)
 {
     beta = 1.0;
     if (a.mode == MODE_OPERATOR) return true;
-    if (a.ctl[C_STOP]) return false;
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    const int4 c0 = ((const int4 *)a.ctl)[0], c1 = ((const int4 *)a.ctl)[1];
+    const double acc = reduce_partials<NW>(a.part_t, a.np_t, lds);
+    if (c0.x) return false;                                   // C_STOP
+    if (a.cur && c1.w) {                                      // C_REQ
+        if (lead) a.ctl[C_STOP] = 1;
+        return false;
+    }
     int k = 0;
     if (a.mode == MODE_ITER) {
-        k = a.ctl[C_CNT0 + a.parity];
-        if (k > a.ctl[C_KMAX]) return false;
+        k = a.parity ? c1.y : c1.x;                           // C_CNT1, C_CNT0
+        if (k > c1.z) return false;                           // C_KMAX
     }
-    beta = sqrt(reduce_partials(a.part_t, a.np_t, lds));
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    beta = sqrt(acc);
+    if (lead) {
         a.S[(int64_t)k * kStateWords + S_BETA] = beta;
+        if (a.cur) {
+            a.cur[(a.mode == MODE_ITER ? 1 - a.parity : 0) * kStateWords + S_BETA] = beta;
+            if (a.mode == MODE_ITER) a.ctl[C_CNT0 + (1 - a.parity)] = k + 1;
+        }
         if (a.mode == MODE_INIT && beta == 0.0) { a.ctl[C_ISTOP] = 0; a.ctl[C_STOP] = 1; }
     }
     return beta != 0.0;      // breakdown: the update kernel sets alpha = 0
 }
 
-// Column j of q from g = (G^T t)_j: adds the smoothing and damping blocks,
-// applies the scale and the -beta v term, stores q_j and returns q_j^2.
+// What column j of q needs besides g = (G^T t)_j: its smoothing and damping
+// terms, scale and v.
 template <class V>
-__device__ __forceinline__ double adj_col_out(const AdjArgs &a, int j,
-                                              typename AccOf<V>::type g, double beta)
+struct ColPre {
+    typename AccOf<V>::type lap, damp;
+    double d, v;
+};
+template <class V>
+__device__ __forceinline__ ColPre<V> adj_col_load(const AdjArgs &a, int j)
 {
 #pragma clang fp contract(off)
     using A = typename AccOf<V>::type;
     const V *T = (const V *)a.T;
-    const V *vv = (const V *)a.v;
+    ColPre<V> c{};
+    if (a.data_only) return c;
+    c.lap = stencil<V>(T + a.m, j, a.nx, a.ny, a.nz);
+    c.damp = (A)T[a.m + a.n + j];
+    c.d = a.d[j];
+    c.v = a.v ? (double)((const V *)a.v)[j] : 0.0;
+    return c;
+}
+
+// Column j of q: adds the smoothing and damping blocks, applies the scale and
+// the -beta v term, stores q_j and returns q_j^2.
+template <class V>
+__device__ __forceinline__ double adj_col_finish(const AdjArgs &a, int j, typename AccOf<V>::type g,
+                                                 double beta, const ColPre<V> &c)
+{
+#pragma clang fp contract(off)
+    using A = typename AccOf<V>::type;
     double qj;
     if (a.data_only) {
         qj = (double)g;
     } else {
-        const A lap = stencil<V>(T + a.m, j, a.nx, a.ny, a.nz);
-        const A sj = g + (A)a.w * lap + (A)a.damp * (A)T[a.m + a.n + j];
-        const double xj = a.d[j] * (double)sj;
-        qj = vv ? xj / beta - beta * (double)vv[j] : xj / beta;
+        const A sj = g + (A)a.w * c.lap + (A)a.damp * c.damp;
+        const double xj = c.d * (double)sj;
+        qj = a.v ? xj / beta - beta * c.v : xj / beta;
     }
     const V qv = (V)qj;
     ((V *)a.q)[j] = qv;
     return (double)qv * (double)qv;
+}
+
+template <class V>
+__device__ __forceinline__ double adj_col_out(const AdjArgs &a, int j, typename AccOf<V>::type g, double beta)
+{
+    return adj_col_finish<V>(a, j, g, beta, adj_col_load<V>(a, j));
 }
 
 template <class M, class V, int LPC>
@@ -1091,7 +1151,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_nruns(AdjArgs a)
         const int node = a.norder[idx];
         const int64_t rs0 = a.nrp[node], cnt = a.nrp[node + 1] - rs0;
         const int64_t rs = rs0 + cnt * wid / 4, re = rs0 + cnt * (wid + 1) / 4;
-        int64_t vb = a.nvq[4 * (int64_t)node + wid];
+        int64_t vb = a.nvq[kNodeParts * (int64_t)node + 4 * wid];
         A acc = 0;
         // first chunk's descriptors and t
         int64_t base = rs;
@@ -1210,20 +1270,19 @@ __device__ __forceinline__ void ld_word(const M *p, A (&x)[W])
 // the load, shuffle and multiply-add instructions per value of k_adj_nruns,
 // for about one padding element per run.  Per column the sum order is fixed
 // (chunks, runs of a group, groups, waves): no atomics.
-// Runs per group and chunk.  A chunk holds at most 64 runs (one descriptor
-// per lane), so with W = 4 (12 groups per wave at nz = 20) 6 runs per group
-// already cover it and more only issue masked loads; with the wave-uniform
-// wave index 5 measured best (FP32 571 -> 545 us on the paper-shaped system;
-// 4: 736 us), and 3 at W = 8 (21 groups per wave).
-#ifndef LSQR_PAIR_RPG2
-#define LSQR_PAIR_RPG2 10
-#endif
-#ifndef LSQR_PAIR_RPG4
-#define LSQR_PAIR_RPG4 5
-#endif
-#ifndef LSQR_PAIR_RPG8
-#define LSQR_PAIR_RPG8 3
-#endif
+// Runs per group and chunk (RPG).  A chunk holds at most 64 runs (one
+// descriptor per lane), so ceil(64 / groups) cover it and more only issue masked
+// loads (nz = 9, 16 waves: FP64 10 -> 6); above these limits more measured
+// slower on the paper-shaped system: 10 for depth pairs, 5 for four depths (FP32
+// 571 -> 545 us against 6), 3 for eight.
+static inline int pair_rpg(int W, int nz)
+{
+    const int ngr = 64 / ((nz + W - 1) / W), most = W == 2 ? 10 : W == 4 ? 5 : 3;
+    const int r = (60 + ngr - 1) / ngr;                   // covers 60 of 64 runs or more
+    if (W == 2) return r > 8 ? most : r > 6 ? 8 : r > 4 ? 6 : 4;
+    if (W == 4) return r > 4 ? most : r > 2 ? r : 2;
+    return r > 2 ? most : r;
+}
 // Inclusive prefix sum over the 64 lanes of a wave, on the VALU with DPP:
 // row shifts by 1, 2, 4 and 8 within rows of 16 lanes (a lane shifted in
 // from outside its row adds zero), then the broadcast of lane 15 into rows 1
@@ -1241,25 +1300,30 @@ __device__ __forceinline__ int wave_incl_scan(int x)
     return x;
 }
 
-template <int W> struct PairRPG {
-    static constexpr int value = W == 2 ? LSQR_PAIR_RPG2 : W == 4 ? LSQR_PAIR_RPG4 : LSQR_PAIR_RPG8;
-};
-
-template <class M, class V, int W>
-__global__ __launch_bounds__(kBlock) void k_adj_npair(AdjArgs a)
+// NW waves share a node's runs: 4, or 16 where the nodes alone leave the device
+// mostly idle (adj_node_waves).  A chunk's descriptors and rows are loaded one or
+// two chunks ahead and its T values one chunk ahead, so that a chunk waits for
+// its own values only.  The first node's first chunks (and, for 16 waves, what its
+// columns need besides the runs) are loaded before the prologue, whose scalars
+// they do not depend on.  The waves' group sums meet in LDS and the waves share
+// the depths of the final sums: with one shuffle per group, depth and element
+// that step took 4.6 us (FP64, 21 groups, 16 waves) to 11 us (16-bit codes) of the
+// small systems' launches, in LDS 0.4 us.
+template <class M, class V, int W, int NW, int RPG>
+__global__ __launch_bounds__(64 * NW) void k_adj_npair(AdjArgs a)
 {
 #pragma clang fp contract(off)
     using A = typename AccOf<V>::type;
-    constexpr int RPG = PairRPG<W>::value;
-    __shared__ double lds[4];
-    __shared__ A wsum[kBlock / 64][64];
-    double beta;
-    if (!adj_prologue(a, beta, lds)) return;
+    // chunks ahead of the descriptors: two, but one for depth pairs on 4 waves
+    // (FP64 924 -> 932 us on the paper-shaped system with two)
+    constexpr bool two = NW == 16 || W > 2;
+    __shared__ double lds[NW];
+    __shared__ __align__(16) A red[NW * 64 * W];
     const M *nv = (const M *)a.cv;
     const V *Tg = (const V *)a.Tg;
     const int nz = a.nz, hz = (nz + W - 1) / W, ngr = 64 / hz;
     const int ch = ngr * RPG < 64 ? ngr * RPG : 64;       // runs per chunk
-    // the wave index as a wave-uniform value: the quarter bounds, the value
+    // the wave index as a wave-uniform value: the part bounds, the value
     // offset and the chunk loop are then scalar (BF16 codes: 459 -> 416 us on
     // the paper-shaped system; FP64 and FP32 unchanged)
     const int lane = threadIdx.x & 63;
@@ -1267,35 +1331,62 @@ __global__ __launch_bounds__(kBlock) void k_adj_npair(AdjArgs a)
     const int grp = lane / hz, k2 = W * (lane - grp * hz);  // the lane's depths k2 .. k2 + W - 1
     const bool live = grp < ngr;
     const int G = gridDim.x, slot = blockIdx.x, nnodes = a.n / nz;
+    // depths l0 .. l1 - 1 of a node are this wave's, one per lane
+    const int per = (nz + NW - 1) / NW, l0 = min(nz, wid * per), l1 = min(nz, l0 + per);
+    const int mine = l0 + lane < l1 ? l0 + lane : nz;
+    // a chunk's descriptors, rows and T values
+    struct Pre {
+        uint32_t dsc, row;
+        A tr;
+    };
+    Pre s0, s1, s2;
+    int node = 0;
+    int64_t base = 0, re = 0, vb = 0;
+    ColPre<V> pre{};
+    // every lane loads (lanes past the chunk its last run), so no load sits
+    // under a divergent branch; lanes past the chunk are masked where the
+    // descriptors are used.  b < re.
+    auto load_runs = [&](Pre &p, int64_t b) {
+        const int c = (int)(re - b < ch ? re - b : ch);
+        const int64_t li = b + (lane < c ? lane : c - 1);
+        p.dsc = __builtin_nontemporal_load(a.ndesc + li);
+        p.row = __builtin_nontemporal_load(a.nrow + li);
+    };
+    auto start_node = [&](int idx) {
+        node = a.norder[idx];
+        const int64_t rs0 = a.nrp[node], cnt = a.nrp[node + 1] - rs0;
+        base = rs0 + cnt * wid / NW;
+        re = rs0 + cnt * (wid + 1) / NW;
+        vb = a.nvq[kNodeParts * (int64_t)node + wid * (kNodeParts / NW)];   // a multiple of W
+        if (base < re) {
+            load_runs(s0, base);
+            if (two) load_runs(s1, base + ch < re ? base + ch : base);
+        }
+        if (NW == 16 && mine < nz) pre = adj_col_load<V>(a, node * nz + mine);
+        if (base < re) s0.tr = (A)Tg[s0.row];
+    };
+    start_node(slot);                        // slot < nnodes: no more workgroups than nodes
+    double beta;
+    if (!adj_prologue<NW>(a, beta, lds)) return;
     double sq = 0.0;
     for (int s = 0; s * G < nnodes; ++s) {
         const int idx = s * G + ((s & 1) ? G - 1 - slot : slot);
         if (idx >= nnodes) continue;         // uniform over the workgroup
-        const int node = a.norder[idx];
-        const int64_t rs0 = a.nrp[node], cnt = a.nrp[node + 1] - rs0;
-        const int64_t rs = rs0 + cnt * wid / 4, re = rs0 + cnt * (wid + 1) / 4;
-        int64_t vb = a.nvq[4 * (int64_t)node + wid];        // a multiple of W
+        if (s > 0) start_node(idx);
         A acc[W];
 #pragma unroll
         for (int h = 0; h < W; ++h) acc[h] = 0;
-        if (re > rs) {
-            // a chunk's descriptors and T values, loaded one chunk ahead
-            struct Pre {
-                uint32_t dsc;
-                A tr;
-            };
-            Pre s0, s1;
-            int64_t base = rs;
-            int nr = (int)(re - base < ch ? re - base : ch);
-            {
-                // every lane loads (lanes past the chunk reload its first
-                // run), so no load sits under a divergent branch; lanes past
-                // the chunk are masked where the descriptors are used
-                const int64_t li = lane < nr ? base + lane : base;
-                s0.dsc = __builtin_nontemporal_load(a.ndesc + li);
-                s0.tr = (A)Tg[__builtin_nontemporal_load(a.nrow + li)];
-            }
-            auto step = [&](const Pre &cur, Pre &nxt) -> bool {
+        if (base < re) {
+            auto step = [&](Pre &cur, Pre &nxt, Pre &far) -> bool {
+                const int nr = (int)(re - base < ch ? re - base : ch);
+                const int64_t nb = base + nr, fb = nb + ch;
+                // with no chunk left, this one's runs again (in bounds, never used)
+                if (two) {
+                    load_runs(far, fb < re ? fb : base);
+                    nxt.tr = (A)Tg[nxt.row];
+                } else {
+                    load_runs(nxt, nb < re ? nb : base);
+                }
                 const uint32_t dsc = lane < nr ? cur.dsc : 0u;
                 // padded length: iz0 mod W zeros before, and up to a multiple of W
                 const int iz0l = (int)((dsc >> 8) & 255u);
@@ -1304,13 +1395,6 @@ __global__ __launch_bounds__(kBlock) void k_adj_npair(AdjArgs a)
                 // (padded offset in the chunk << 16) | (iz0 << 8) | len; offsets < 64 * 68
                 const uint32_t pk = ((uint32_t)(incl - plen) << 16) | dsc;
                 const int tot = __builtin_amdgcn_readlane(incl, 63);
-                const int64_t nb = base + nr;
-                const int nn = nb < re ? (int)(re - nb < ch ? re - nb : ch) : 0;
-                // the next chunk's runs; with none left, this chunk's last
-                // run again (in bounds, never used)
-                const int64_t li = lane < nn ? nb + lane : nb - 1;
-                nxt.dsc = __builtin_nontemporal_load(a.ndesc + li);
-                const uint32_t row_n = __builtin_nontemporal_load(a.nrow + li);
                 A v[RPG][W];
 #pragma unroll
                 for (int u = 0; u < RPG; ++u) {
@@ -1324,7 +1408,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_npair(AdjArgs a)
 #pragma unroll
                     for (int h = 0; h < W; ++h) v[u][h] = in ? v[u][h] : (A)0;
                 }
-                nxt.tr = (A)Tg[row_n];
+                if (!two) nxt.tr = (A)Tg[nxt.row];
                 // runs past the chunk carry a finite T value and zero values
 #pragma unroll
                 for (int u = 0; u < RPG; ++u) {
@@ -1334,35 +1418,42 @@ __global__ __launch_bounds__(kBlock) void k_adj_npair(AdjArgs a)
                 }
                 vb += tot;
                 base = nb;
-                nr = nn;
-                return nn == 0;
+                return nb >= re;
             };
             for (;;) {
-                if (step(s0, s1)) break;
-                if (step(s1, s0)) break;
+                if (two) {
+                    if (step(s0, s1, s2)) break;
+                    if (step(s1, s2, s0)) break;
+                    if (step(s2, s0, s1)) break;
+                } else {
+                    if (step(s0, s1, s1)) break;
+                    if (step(s1, s0, s0)) break;
+                }
             }
         }
-        // lane l < nz: depth l = word l / W, element l mod W, summed over groups
-        const int kk = lane / W, hh = lane % W;
-        A col = 0;
-        for (int g = 0; g < ngr; ++g) {
-            A c = 0;
+        if (NW != 16 && mine < nz) pre = adj_col_load<V>(a, node * nz + mine);
 #pragma unroll
-            for (int h = 0; h < W; ++h) {
-                const A ch_ = __shfl(acc[h], (g * hz + kk) & 63);
-                c = h == hh ? ch_ : c;
-            }
-            col += c;
-        }
-        if (lane < nz) wsum[wid][lane] = col;
+        for (int h = 0; h < W; ++h) red[(wid * 64 + lane) * W + h] = acc[h];
         __syncthreads();
-        if (wid == 0 && lane < nz) {
-            const A g = ((wsum[0][lane] + wsum[1][lane]) + wsum[2][lane]) + wsum[3][lane];
-            sq += adj_col_out<V>(a, node * nz + lane, g, beta);
+        // depth l: the groups (lanes) of every wave, waves in order, then the
+        // lanes' sum; kept by the lane that stores the column
+        A g = 0;
+        for (int l = l0; l < l1; ++l) {
+            A c = 0;
+            if (lane < ngr) {
+#pragma unroll
+                for (int w = 0; w < NW; ++w) c += red[(w * 64 + lane * hz + l / W) * W + l % W];
+            }
+            c = group_sum<64>(c);
+            g = lane == l - l0 ? c : g;
+        }
+        if (mine < nz) {
+            const int j = node * nz + mine;
+            sq += adj_col_finish<V>(a, j, g, beta, pre);
         }
         __syncthreads();
     }
-    const double tot = block_sum(sq, lds);
+    const double tot = block_sum<NW>(sq, lds);
     if (threadIdx.x == 0) a.part_out[blockIdx.x] = tot;
 }
 
@@ -1382,7 +1473,85 @@ struct UpdArgs {
     int parity;
     int mode;
     double *hbar;            // LSMR only: hbar [n] (w holds h)
+    double *cur;             // fused iterations (k_fwd_small): state rows of the last two
+                             // iterations by parity, else nullptr
 };
+
+// The Givens step of LSQR (Paige & Saunders) from the previous state row and
+// beta (rotate: what does not wait for alpha), then alpha: the coefficients of
+// the x and w sweeps and, through put(field, value), the new state row.  False
+// when a scalar is not finite.
+struct Givens { double rho, c, s, phi, phibar, t1; };
+__device__ __forceinline__ Givens lsqr_rotate(double rhobar, double phibar, double beta)
+{
+#pragma clang fp contract(off)
+    Givens g;
+    g.rho = sqrt(rhobar * rhobar + beta * beta);
+    g.c = rhobar / g.rho;
+    g.s = beta / g.rho;
+    g.phi = g.c * phibar;
+    g.phibar = g.s * phibar;
+    g.t1 = g.phi / g.rho;
+    return g;
+}
+template <class Put>
+__device__ __forceinline__ bool lsqr_scalars(const Givens &g, double alpha, double beta, double &t1,
+                                             double &t2, Put put)
+{
+#pragma clang fp contract(off)
+    const double theta = g.s * alpha;
+    const double rhobar_n = -g.c * alpha;
+    t1 = g.t1;
+    t2 = theta / g.rho;
+    const double psi = g.phibar * alpha * fabs(g.c);
+    if (!isfinite(alpha) || !isfinite(beta) || !isfinite(g.rho) || !isfinite(g.phi)) return false;
+    put(S_ALPHA, alpha); put(S_RHOBAR, rhobar_n); put(S_PHIBAR, g.phibar); put(S_RHO, g.rho);
+    put(S_C, g.c); put(S_S, g.s); put(S_THETA, theta); put(S_PHI, g.phi); put(S_PSI, psi);
+    return true;
+}
+
+// The LSMR step's scalars (see k_update_lsmr): the coefficients of the hbar, y
+// and h sweeps and the new state row.
+template <class Put>
+__device__ __forceinline__ bool lsmr_scalars(const double *Sp, double alpha, double beta, double &c1,
+                                             double &c2, double &c3, Put put)
+{
+#pragma clang fp contract(off)
+    // rotation P_k
+    const double rhoold = Sp[S_RHO], alphabar = Sp[S_ALPHABAR];
+    const double rho = sqrt(alphabar * alphabar + beta * beta);
+    const double c = alphabar / rho, s = beta / rho;
+    const double thetanew = s * alpha, alphabar_n = c * alpha;
+    // rotation Pbar_k
+    const double rhobarold = Sp[S_RHOBAR], zetaold = Sp[S_ZETA], zetabar = Sp[S_ZETABAR];
+    const double thetabar = Sp[S_SBAR] * rho, rhotemp = Sp[S_CBAR] * rho;
+    const double rhobar = sqrt(rhotemp * rhotemp + thetanew * thetanew);
+    const double cbar = rhotemp / rhobar, sbar = thetanew / rhobar;
+    const double zeta = cbar * zetabar, zetabar_n = -sbar * zetabar;
+    c1 = thetabar * rho / (rhoold * rhobarold);
+    c2 = zeta / (rho * rhobar);
+    c3 = thetanew / rho;
+    // |r_k| chain
+    const double betahat = c * Sp[S_BETADD], betadd = -s * Sp[S_BETADD];
+    const double thetatildeold = Sp[S_THETATILDE], rhodoldp = Sp[S_RHODOLD];
+    const double rhotildeold = sqrt(rhodoldp * rhodoldp + thetabar * thetabar);
+    const double ctildeold = rhodoldp / rhotildeold, stildeold = thetabar / rhotildeold;
+    const double thetatilde = stildeold * rhobar, rhodold = ctildeold * rhobar;
+    const double betad = -stildeold * Sp[S_BETAD] + ctildeold * betahat;
+    const double tautilde = (zetaold - thetatildeold * Sp[S_TAUTILDE]) / rhotildeold;
+    const double taud = (zeta - thetatilde * tautilde) / rhodold;
+    const double normr = sqrt((betad - taud) * (betad - taud) + betadd * betadd);
+    const double normar = fabs(zetabar_n);
+    if (!isfinite(alpha) || !isfinite(rho) || !isfinite(rhobar) || !isfinite(zeta) || !isfinite(normr))
+        return false;
+    put(S_ALPHA, alpha); put(S_ALPHABAR, alphabar_n); put(S_RHO, rho); put(S_RHOBAR, rhobar);
+    put(S_CBAR, cbar); put(S_SBAR, sbar); put(S_ZETA, zeta); put(S_ZETABAR, zetabar_n);
+    put(S_BETADD, betadd); put(S_BETAD, betad); put(S_RHODOLD, rhodold);
+    put(S_TAUTILDE, tautilde); put(S_THETATILDE, thetatilde);
+    put(S_C, c); put(S_S, s); put(S_THETA, thetanew);
+    put(S_PHIBAR, normr); put(S_PSI, normar);
+    return true;
+}
 
 template <class V>
 __global__ __launch_bounds__(kBlock) void k_update(UpdArgs a)
@@ -1421,6 +1590,8 @@ __global__ __launch_bounds__(kBlock) void k_update(UpdArgs a)
             double *S0 = a.S;
             S0[S_ALPHA] = alpha; S0[S_RHOBAR] = alpha; S0[S_PHIBAR] = beta;
             S0[S_PSI] = alpha * beta; S0[S_ETA] = 1.0; S0[S_METHOD] = 0.0;
+            if (a.cur)
+                for (int f = 0; f < kStateWords; ++f) a.cur[f] = S0[f];
         }
         return;
     }
@@ -1430,18 +1601,9 @@ __global__ __launch_bounds__(kBlock) void k_update(UpdArgs a)
     double *Sk = a.S + (int64_t)k * kStateWords;
     const double beta = Sk[S_BETA];
     const double alpha = beta > 0.0 ? sqrt(reduce_partials(a.part_q, a.np_q, lds)) : 0.0;
-    const double rhobar = Sp[S_RHOBAR], phibar = Sp[S_PHIBAR];
-    const double rho = sqrt(rhobar * rhobar + beta * beta);
-    const double c = rhobar / rho;
-    const double s = beta / rho;
-    const double theta = s * alpha;
-    const double rhobar_n = -c * alpha;
-    const double phi = c * phibar;
-    const double phibar_n = s * phibar;
-    const double t1 = phi / rho;
-    const double t2 = theta / rho;
-    const double psi = phibar_n * alpha * fabs(c);
-    if (!isfinite(alpha) || !isfinite(beta) || !isfinite(rho) || !isfinite(phi)) {
+    double t1, t2;
+    const Givens rot = lsqr_rotate(Sp[S_RHOBAR], Sp[S_PHIBAR], beta);
+    if (!lsqr_scalars(rot, alpha, beta, t1, t2, [&](int f, double x) { if (lead) Sk[f] = x; })) {
         if (lead) { a.ctl[C_ERR] = 1; a.ctl[C_ISTOP] = -3; a.ctl[C_STOP] = 1; }
         return;
     }
@@ -1466,8 +1628,6 @@ __global__ __launch_bounds__(kBlock) void k_update(UpdArgs a)
     const double tot = block_sum(sq, lds);
     if (threadIdx.x == 0) a.part_out[blockIdx.x] = tot;
     if (lead) {
-        Sk[S_ALPHA] = alpha; Sk[S_RHOBAR] = rhobar_n; Sk[S_PHIBAR] = phibar_n; Sk[S_RHO] = rho;
-        Sk[S_C] = c; Sk[S_S] = s; Sk[S_THETA] = theta; Sk[S_PHI] = phi; Sk[S_PSI] = psi;
         a.ctl[C_ITERS] = k;
         a.ctl[C_CNT0 + (1 - a.parity)] = k + 1;
     }
@@ -1521,6 +1681,8 @@ __global__ __launch_bounds__(kBlock) void k_update_lsmr(UpdArgs a)
             S0[S_TAUTILDE] = 0.0; S0[S_THETATILDE] = 0.0;
             S0[S_PHIBAR] = beta; S0[S_PSI] = alpha * beta; S0[S_ETA] = 1.0;
             S0[S_ARNORM0] = alpha * beta; S0[S_METHOD] = 1.0;
+            if (a.cur)
+                for (int f = 0; f < kStateWords; ++f) a.cur[f] = S0[f];
         }
         return;
     }
@@ -1530,33 +1692,8 @@ __global__ __launch_bounds__(kBlock) void k_update_lsmr(UpdArgs a)
     double *Sk = a.S + (int64_t)k * kStateWords;
     const double beta = Sk[S_BETA];
     const double alpha = beta > 0.0 ? sqrt(reduce_partials(a.part_q, a.np_q, lds)) : 0.0;
-    // rotation P_k
-    const double rhoold = Sp[S_RHO], alphabar = Sp[S_ALPHABAR];
-    const double rho = sqrt(alphabar * alphabar + beta * beta);
-    const double c = alphabar / rho, s = beta / rho;
-    const double thetanew = s * alpha, alphabar_n = c * alpha;
-    // rotation Pbar_k
-    const double rhobarold = Sp[S_RHOBAR], zetaold = Sp[S_ZETA], zetabar = Sp[S_ZETABAR];
-    const double thetabar = Sp[S_SBAR] * rho, rhotemp = Sp[S_CBAR] * rho;
-    const double rhobar = sqrt(rhotemp * rhotemp + thetanew * thetanew);
-    const double cbar = rhotemp / rhobar, sbar = thetanew / rhobar;
-    const double zeta = cbar * zetabar, zetabar_n = -sbar * zetabar;
-    const double c1 = thetabar * rho / (rhoold * rhobarold);
-    const double c2 = zeta / (rho * rhobar);
-    const double c3 = thetanew / rho;
-    // |r_k| chain
-    const double betahat = c * Sp[S_BETADD], betadd = -s * Sp[S_BETADD];
-    const double thetatildeold = Sp[S_THETATILDE], rhodoldp = Sp[S_RHODOLD];
-    const double rhotildeold = sqrt(rhodoldp * rhodoldp + thetabar * thetabar);
-    const double ctildeold = rhodoldp / rhotildeold, stildeold = thetabar / rhotildeold;
-    const double thetatilde = stildeold * rhobar, rhodold = ctildeold * rhobar;
-    const double betad = -stildeold * Sp[S_BETAD] + ctildeold * betahat;
-    const double tautilde = (zetaold - thetatildeold * Sp[S_TAUTILDE]) / rhotildeold;
-    const double taud = (zeta - thetatilde * tautilde) / rhodold;
-    const double normr = sqrt((betad - taud) * (betad - taud) + betadd * betadd);
-    const double normar = fabs(zetabar_n);
-    if (!isfinite(alpha) || !isfinite(rho) || !isfinite(rhobar) || !isfinite(zeta) ||
-        !isfinite(normr)) {
+    double c1, c2, c3;
+    if (!lsmr_scalars(Sp, alpha, beta, c1, c2, c3, [&](int f, double x) { if (lead) Sk[f] = x; })) {
         if (lead) { a.ctl[C_ERR] = 1; a.ctl[C_ISTOP] = -3; a.ctl[C_STOP] = 1; }
         return;
     }
@@ -1582,15 +1719,254 @@ __global__ __launch_bounds__(kBlock) void k_update_lsmr(UpdArgs a)
     const double tot = block_sum(sq, lds);
     if (threadIdx.x == 0) a.part_out[blockIdx.x] = tot;
     if (lead) {
-        Sk[S_ALPHA] = alpha; Sk[S_ALPHABAR] = alphabar_n; Sk[S_RHO] = rho; Sk[S_RHOBAR] = rhobar;
-        Sk[S_CBAR] = cbar; Sk[S_SBAR] = sbar; Sk[S_ZETA] = zeta; Sk[S_ZETABAR] = zetabar_n;
-        Sk[S_BETADD] = betadd; Sk[S_BETAD] = betad; Sk[S_RHODOLD] = rhodold;
-        Sk[S_TAUTILDE] = tautilde; Sk[S_THETATILDE] = thetatilde;
-        Sk[S_C] = c; Sk[S_S] = s; Sk[S_THETA] = thetanew;
-        Sk[S_PHIBAR] = normr; Sk[S_PSI] = normar;
         a.ctl[C_ITERS] = k;
         a.ctl[C_CNT0 + (1 - a.parity)] = k + 1;
     }
+}
+
+// ------------------------------------------------------- fused small step --
+// Systems of at most kSmallCols unknowns with short rows: the forward product
+// of iteration k with the update of iteration k - 1 in front of it, so that an
+// iteration is two launches.  There a launch is a chain of dependent loads, not
+// bytes: the kernels above first read the stop flag and the counter, then the
+// state row the counter names, the partials, then the row bounds, columns and
+// z.  Here everything that depends on nothing (control words, state rows at
+// fixed places, q, d, the slice of w and y, the first rows' columns and values)
+// is loaded at once; every workgroup forms alpha and the scalars, stages D v of
+// all columns in LDS (16-bit columns index it), sums |D^-1 v|^2 in the same
+// order as all others, updates its slice of v, w, y and walks its rows.
+// A row's entries are taken four (16-bit codes: eight) at a time from positions
+// that are multiples of that (entries of other rows masked), LPR lanes to a row
+// and two rows to a turn; the next turn's entries and the bounds of the one after are in flight
+// meanwhile.  A stop is only asked for (C_REQ): the transposed kernel makes it
+// effective, since a late workgroup of this launch still has to update its
+// slice.  Per LSQR iteration, both launches: 2,304 unknowns and 1 M entries in
+// FP64 32 -> 24 us, 6 M entries in BF16 98 -> 45 us.
+constexpr int kSmallLoads = 6;                            // elements of q and d per thread
+// E entries of a row per lane: 4, or 8 for 16-bit codes (16 bytes of each).
+template <class M> struct SmallE { static constexpr int value = sizeof(M) == 2 ? 8 : 4; };
+template <class M, int E>
+struct Seg {
+    typename EntRaw<M, sizeof(M) == 8 ? 2 : E>::type r[sizeof(M) == 8 ? E / 2 : 1];
+    typename SlotRaw<E>::type c;
+};
+template <class M, int E>
+__device__ __forceinline__ void seg_load(Seg<M, E> &g, const M *va, const uint16_t *col)
+{
+    using W = typename EntRaw<M, sizeof(M) == 8 ? 2 : E>::type;
+#pragma unroll
+    for (int i = 0; i < (sizeof(M) == 8 ? E / 2 : 1); ++i) g.r[i] = ((const W *)va)[i];
+    g.c = *(const typename SlotRaw<E>::type *)col;
+}
+template <class A, class M, int E>
+__device__ __forceinline__ void seg_values(const Seg<M, E> &g, A (&x)[E])
+{
+    if constexpr (sizeof(M) == 8) {
+#pragma unroll
+        for (int i = 0; i < E / 2; ++i) { x[2 * i] = (A)g.r[i].x; x[2 * i + 1] = (A)g.r[i].y; }
+    } else {
+        ent_values<A, M, E>(g.r[0], x);
+    }
+}
+
+template <class M, class V, int LPR, int NT>
+__global__ __launch_bounds__(NT) void k_fwd_small(FwdArgs a, UpdArgs u)
+{
+    using A = typename AccOf<V>::type;
+    constexpr int E = SmallE<M>::value;
+    constexpr int64_t AL = ~(int64_t)(E - 1);
+    constexpr int NW = NT / 64, Q = 2, RS = NT / LPR;     // rows of a turn: row, row + RS
+    extern __shared__ double zdyn[];
+    A *zl = (A *)zdyn;                                    // [n]
+    __shared__ double lds[NW];
+    const int tid = threadIdx.x, n = a.n, lane = tid % LPR, G = gridDim.x;
+    const bool lead = blockIdx.x == 0 && tid == 0;
+    const V *q = (const V *)u.q, *tp = (const V *)a.Tprev;
+    V *v = (V *)u.v;
+    const int4 c0 = ((const int4 *)a.ctl)[0], c1 = ((const int4 *)a.ctl)[1];
+    const double *Sold = u.cur + (1 - a.parity) * kStateWords;   // state row k - 2
+    double *Snew = u.cur + a.parity * kStateWords;               // state row k - 1 (beta is there)
+    V qv[kSmallLoads];
+    double dv[kSmallLoads];
+#pragma unroll
+    for (int i = 0; i < kSmallLoads; ++i)
+        if (i * NT < n) {
+            const int j = min(tid + i * NT, n - 1);
+            qv[i] = q[j];
+            dv[i] = u.d[j];
+        }
+    double pq = 0.0;
+    for (int i = tid; i < u.np_q; i += NT) pq += u.part_q[i];
+    // the slice of the sweeps (at most NT elements)
+    const int j0 = (int)((int64_t)n * blockIdx.x / G), j1 = (int)((int64_t)n * (blockIdx.x + 1) / G);
+    const int js = j0 + tid;
+    double wj = 0.0, yj = 0.0, hj = 0.0, qj = 0.0;
+    if (js < j1) {
+        wj = u.w[js];
+        yj = u.y[js];
+        qj = (double)q[js];
+        if (u.hbar) hj = u.hbar[js];
+    }
+    // positions relative to the workgroup's first entry, rounded down to a
+    // multiple of E (a workgroup's entries number fewer than 2^31)
+    const int rbeg = a.wrow[blockIdx.x], rend = a.wrow[blockIdx.x + 1];
+    const int64_t pos0 = a.rp[rbeg] & AL;
+    const M *va = (const M *)a.va + pos0;
+    const uint16_t *col = a.slot + pos0;
+    struct Bounds { int s, e; };
+    auto bounds = [&](int row) {
+        return row < rend ? Bounds{(int)(a.rp[row] - pos0), (int)(a.rp[row + 1] - pos0)} : Bounds{0, 0};
+    };
+    auto load = [&](const Bounds &b, int p, Seg<M, E> &g) {  // p past the row: its first ones, not summed
+        const int pp = p < b.e ? p : (b.s & (int)AL);
+        seg_load<M, E>(g, va + pp, col + pp);
+    };
+    auto add = [&](const Bounds &b, int p, const Seg<M, E> &g, A acc) {
+        A x[E];
+        seg_values<A, M, E>(g, x);
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+            const A t = fma(x[k], zl[half_at<E>(g.c, k)], acc);
+            acc = (uint32_t)(p + k - b.s) < (uint32_t)(b.e - b.s) ? t : acc;
+        }
+        return acc;
+    };
+    int row = rbeg + tid / LPR;
+    struct Turn {
+        Bounds b[Q];
+        double up[Q];                                     // t_prev of the row, in its last lane
+        Seg<M, E> g[Q];
+    };
+    // in this order: what a turn uses first is loaded first, and no load of the
+    // current turn follows those of the next
+    auto load_turn = [&](Turn &t, int r) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+            t.up[i] = lane == LPR - 1 && r + i * RS < rend ? (double)tp[r + i * RS] : 0.0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) load(t.b[i], (t.b[i].s & (int)AL) + E * lane, t.g[i]);
+    };
+    Turn t0, t1;
+    Bounds far[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        t0.b[i] = bounds(row + i * RS);
+        t1.b[i] = bounds(row + (Q + i) * RS);
+    }
+    load_turn(t0, row);
+    const double beta = Snew[S_BETA];
+    const bool lsmr = u.hbar != nullptr;
+    const Givens rot = lsqr_rotate(Sold[S_RHOBAR], Sold[S_PHIBAR], beta);
+    if (c0.x) return;                                     // C_STOP (never set in this launch)
+    const int k = a.parity ? c1.y : c1.x;
+    if (k > c1.z) return;
+    double alpha, vn, arnorm0, eta = 1.0;
+    bool stop = false;
+    int istop = 2;
+    if (k == 1) {                                         // the start step made v, z and the state
+        alpha = Snew[S_ALPHA];
+        for (int j = tid; j < n; j += NT) zl[j] = (A)((const V *)a.z)[j];
+        vn = sqrt(reduce_partials<NW>(a.part_v, a.np_v, lds));
+        arnorm0 = lsmr ? a.S[S_ARNORM0] : (alpha * beta) * vn;
+        if (lead) { a.S[S_ARNORM0] = arnorm0; a.S[S_VNORM] = vn; }
+    } else {
+#pragma clang fp contract(off)
+        arnorm0 = a.S[S_ARNORM0];
+        const double aq = block_sum<NW>(pq, lds);
+        alpha = beta > 0.0 ? sqrt(aq) : 0.0;
+        const bool newv = alpha > 0.0;
+        double *Sk = a.S + (int64_t)(k - 1) * kStateWords;
+        double w1, w2, w3 = 0.0, psi = 0.0;
+        auto put = [&](int f, double x) {
+            if (f == S_PSI) psi = x;
+            if (lead) { Sk[f] = x; Snew[f] = x; }
+        };
+        const bool fine = lsmr ? lsmr_scalars(Sold, alpha, beta, w1, w2, w3, put)
+                               : lsqr_scalars(rot, alpha, beta, w1, w2, put);
+        if (!fine) {
+            if (lead) { a.ctl[C_ERR] = 1; a.ctl[C_ISTOP] = -3; a.ctl[C_REQ] = 1; }
+            return;
+        }
+        double sq = 0.0;
+#pragma unroll
+        for (int i = 0; i < kSmallLoads; ++i)
+            if (i * NT < n) {
+                const int j = tid + i * NT;
+                if (j < n) {
+                    const V vv = newv ? (V)((double)qv[i] / alpha) : v[j];
+                    zl[j] = (A)(V)(dv[i] * (double)vv);
+                    const double x = (double)vv / dv[i];
+                    sq += x * x;
+                }
+            }
+        if (js < j1) {
+            const V vv = newv ? (V)(qj / alpha) : v[js];
+            const double vj = (double)vv;
+            if (lsmr) {
+                const double hb = wj - w1 * hj;           // w holds h
+                u.hbar[js] = hb;
+                u.y[js] = yj + w2 * hb;
+                u.w[js] = vj - w3 * wj;
+            } else {
+                u.y[js] = yj + w1 * wj;
+                u.w[js] = vj - w2 * wj;
+            }
+            if (newv) v[js] = vv;
+        }
+        vn = sqrt(block_sum<NW>(sq, lds));
+        eta = lsmr ? psi / arnorm0 : psi * vn / arnorm0;
+        if (a.tol > 0.0 && eta <= a.tol) { stop = true; istop = 1; }
+        else if (alpha == 0.0 || beta == 0.0) { stop = true; istop = 3; }
+        if (lead) {
+            Sk[S_ETA] = eta;
+            Sk[S_VNORM] = vn;
+            a.ctl[C_ITERS] = k - 1;
+            if (stop) { a.ctl[C_ISTOP] = istop; a.ctl[C_REQ] = 1; }
+        }
+    }
+    if (stop) return;                                     // zl is in place: every path above ends in a barrier
+    double sq = 0.0;
+    auto turn = [&](Turn &cur, Turn &nxt) -> bool {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) far[i] = bounds(row + (2 * Q + i) * RS);
+        load_turn(nxt, row + Q * RS);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const Bounds b = cur.b[i];
+            int p = (b.s & (int)AL) + E * lane;
+            A acc = add(b, p, cur.g[i], (A)0);
+            for (p += E * LPR; p - E * lane < b.e; p += E * LPR) {   // rows of more than E LPR entries
+                Seg<M, E> g;
+                load(b, p, g);
+                acc = add(b, p, g, acc);
+            }
+            const A t = group_sum_last<LPR>(acc);
+            if (lane == LPR - 1 && row + i * RS < rend)
+                sq += fwd_row_out_u<V>(a, row + i * RS, (double)t, alpha, beta, cur.up[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < Q; ++i) cur.b[i] = far[i];
+        row += Q * RS;
+        // uniform over the wave's first row: every lane of a wave leaves together
+        return __builtin_amdgcn_readfirstlane(row) >= rend;
+    };
+    if (__builtin_amdgcn_readfirstlane(row) < rend)
+        for (;;) {
+            if (turn(t0, t1)) break;
+            if (turn(t1, t0)) break;
+        }
+    {   // smoothing and damping rows, D v from LDS
+#pragma clang fp contract(off)
+        for (int r = blockIdx.x * NT + tid; r < 2 * n; r += G * NT) {
+            const A yv = r < n ? stencil<A>(zl, r, a.nx, a.ny, a.nz) * (A)a.w : (A)a.damp * zl[r - n];
+            const double x = (double)tp[a.m + r] / beta;
+            const V t = (V)((double)yv - alpha * x);
+            ((V *)a.Tcur)[a.m + r] = t;
+            sq += (double)t * (double)t;
+        }
+    }
+    const double tot = block_sum<NW>(sq, lds);
+    if (tid == 0) a.part_out[blockIdx.x] = tot;
 }
 
 }  // namespace lsqr
@@ -1635,21 +2011,41 @@ static void fwd_launch_m(hipStream_t st, int grid, const RowFmt &R, const FwdArg
     }
 }
 
+template <class M, class V, int NW>
+static void adj_launch_pairs(hipStream_t st, int grid, const ColFmt &C, const AdjArgs &a)
+{
+    const dim3 g(grid), b(64 * NW);
+    const int rpg = pair_rpg(C.pairs, a.nz);
+    if constexpr (sizeof(M) == 2) {
+        if (C.pairs == 8) {
+            if (rpg == 3) hipLaunchKernelGGL((k_adj_npair<M, V, 8, NW, 3>), g, b, 0, st, a);
+            else if (rpg == 2) hipLaunchKernelGGL((k_adj_npair<M, V, 8, NW, 2>), g, b, 0, st, a);
+            else hipLaunchKernelGGL((k_adj_npair<M, V, 8, NW, 1>), g, b, 0, st, a);
+            return;
+        }
+    }
+    if constexpr (sizeof(M) <= 4) {
+        if (C.pairs == 4) {
+            if (rpg == 5) hipLaunchKernelGGL((k_adj_npair<M, V, 4, NW, 5>), g, b, 0, st, a);
+            else if (rpg == 4) hipLaunchKernelGGL((k_adj_npair<M, V, 4, NW, 4>), g, b, 0, st, a);
+            else if (rpg == 3) hipLaunchKernelGGL((k_adj_npair<M, V, 4, NW, 3>), g, b, 0, st, a);
+            else hipLaunchKernelGGL((k_adj_npair<M, V, 4, NW, 2>), g, b, 0, st, a);
+            return;
+        }
+    }
+    if (rpg == 10) hipLaunchKernelGGL((k_adj_npair<M, V, 2, NW, 10>), g, b, 0, st, a);
+    else if (rpg == 8) hipLaunchKernelGGL((k_adj_npair<M, V, 2, NW, 8>), g, b, 0, st, a);
+    else if (rpg == 6) hipLaunchKernelGGL((k_adj_npair<M, V, 2, NW, 6>), g, b, 0, st, a);
+    else hipLaunchKernelGGL((k_adj_npair<M, V, 2, NW, 4>), g, b, 0, st, a);
+}
+
 template <class M, class V>
 static void adj_launch_m(hipStream_t st, int grid, const ColFmt &C, const AdjArgs &a)
 {
     if (C.nrp) {
         if (C.pairs) {
-            if constexpr (sizeof(M) == 2) {
-                if (C.pairs == 8) hipLaunchKernelGGL((k_adj_npair<M, V, 8>), dim3(grid), dim3(kBlock), 0, st, a);
-                else if (C.pairs == 4) hipLaunchKernelGGL((k_adj_npair<M, V, 4>), dim3(grid), dim3(kBlock), 0, st, a);
-                else hipLaunchKernelGGL((k_adj_npair<M, V, 2>), dim3(grid), dim3(kBlock), 0, st, a);
-            } else if constexpr (sizeof(M) == 4) {
-                if (C.pairs == 4) hipLaunchKernelGGL((k_adj_npair<M, V, 4>), dim3(grid), dim3(kBlock), 0, st, a);
-                else hipLaunchKernelGGL((k_adj_npair<M, V, 2>), dim3(grid), dim3(kBlock), 0, st, a);
-            } else {
-                hipLaunchKernelGGL((k_adj_npair<M, V, 2>), dim3(grid), dim3(kBlock), 0, st, a);
-            }
+            if (C.waves == 16) adj_launch_pairs<M, V, 16>(st, grid, C, a);
+            else adj_launch_pairs<M, V, 4>(st, grid, C, a);
         }
         else hipLaunchKernelGGL((k_adj_nruns<M, V>), dim3(grid), dim3(kBlock), 0, st, a);
         return;
@@ -1664,8 +2060,7 @@ static void adj_launch_m(hipStream_t st, int grid, const ColFmt &C, const AdjArg
 }
 
 // The stored value types a vector type supports: FP64 vectors take FP64
-// values (and, in the transposed product of the refinements, FP32 and
-// quantised values); FP32 vectors take FP32 and quantised values.
+// values; FP32 vectors take FP32 and quantised values.
 template <class V> struct Wide { static constexpr bool value = false; };
 template <> struct Wide<double> { static constexpr bool value = true; };
 
@@ -1750,10 +2145,10 @@ int adj_nruns_blocks_per_cu(const ColFmt &C)
     hipError_t e = hipErrorInvalidValue;
     if (!C.nrp) return 0;
 #define LSQR_ADJ_OCC(M_) (C.pairs == 8 && sizeof(M_) == 2                                                              \
-                              ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_adj_npair<M_, V, (sizeof(M_) == 2 ? 8 : 2)>, kBlock, 0) \
+                              ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_adj_npair<M_, V, (sizeof(M_) == 2 ? 8 : 2), 4, (sizeof(M_) == 2 ? 3 : 10)>, kBlock, 0) \
                           : C.pairs == 4 && sizeof(M_) <= 4                                                              \
-                              ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_adj_npair<M_, V, (sizeof(M_) <= 4 ? 4 : 2)>, kBlock, 0) \
-                          : C.pairs ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_adj_npair<M_, V, 2>, kBlock, 0) \
+                              ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_adj_npair<M_, V, (sizeof(M_) <= 4 ? 4 : 2), 4, (sizeof(M_) <= 4 ? 5 : 10)>, kBlock, 0) \
+                          : C.pairs ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_adj_npair<M_, V, 2, 4, 10>, kBlock, 0) \
                               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_adj_nruns<M_, V>, kBlock, 0))
     switch (C.vt) {
     case VT_F64:
@@ -1762,8 +2157,12 @@ int adj_nruns_blocks_per_cu(const ColFmt &C)
     case VT_F32:
         if constexpr (!Wide<V>::value) e = LSQR_ADJ_OCC(float);
         break;
-    case VT_BF16: e = LSQR_ADJ_OCC(bf16_t); break;
-    case VT_F16: e = LSQR_ADJ_OCC(fp16_t); break;
+    case VT_BF16:
+        if constexpr (!Wide<V>::value) e = LSQR_ADJ_OCC(bf16_t);
+        break;
+    case VT_F16:
+        if constexpr (!Wide<V>::value) e = LSQR_ADJ_OCC(fp16_t);
+        break;
     default: break;
     }
 #undef LSQR_ADJ_OCC
@@ -1781,20 +2180,21 @@ template <class V>
 hipError_t adj_launch(hipStream_t st, const Problem &P, int grid, const ColFmt &C,
                       const double *d, const void *T, const void *Tg, const void *v, void *q,
                       double *part_out, const double *part_t, int np_t, double *S, int *ctl,
-                      int parity, int mode, int data_only)
+                      int parity, int mode, int data_only, double *cur)
 {
     AdjArgs a{C.cp, C.ri, C.val, P.m, (int)P.n, P.nx, P.ny, P.nz, P.w, P.damp, d, T, Tg, v, q,
               part_out, part_t, np_t, S, ctl, parity, mode, data_only,
-              C.nrp, C.nvq, C.nrow, C.ndesc, C.norder};
-    switch (C.vt) {
-    case VT_F64:
-        if constexpr (Wide<V>::value) adj_launch_m<double, V>(st, grid, C, a);
-        else return hipErrorInvalidValue;
-        break;
-    case VT_F32: adj_launch_m<float, V>(st, grid, C, a); break;
-    case VT_BF16: adj_launch_m<bf16_t, V>(st, grid, C, a); break;
-    case VT_F16: adj_launch_m<fp16_t, V>(st, grid, C, a); break;
-    default: return hipErrorInvalidValue;
+              C.nrp, C.nvq, C.nrow, C.ndesc, C.norder, cur};
+    if constexpr (Wide<V>::value) {
+        if (C.vt != VT_F64) return hipErrorInvalidValue;
+        adj_launch_m<double, V>(st, grid, C, a);
+    } else {
+        switch (C.vt) {
+        case VT_F32: adj_launch_m<float, V>(st, grid, C, a); break;
+        case VT_BF16: adj_launch_m<bf16_t, V>(st, grid, C, a); break;
+        case VT_F16: adj_launch_m<fp16_t, V>(st, grid, C, a); break;
+        default: return hipErrorInvalidValue;
+        }
     }
     return hipGetLastError();
 }
@@ -1813,11 +2213,53 @@ template <class V>
 hipError_t update_launch(hipStream_t st, const Problem &P, int grid, const double *d,
                          const void *q, void *v, double *w, double *y, void *z, double *part_out,
                          const double *part_q, int np_q, double *S, int *ctl, int parity, int mode,
-                         double *hbar)
+                         double *hbar, double *cur)
 {
-    UpdArgs a{(int)P.n, d, q, v, w, y, z, part_out, part_q, np_q, S, ctl, parity, mode, hbar};
+    UpdArgs a{(int)P.n, d, q, v, w, y, z, part_out, part_q, np_q, S, ctl, parity, mode, hbar, cur};
     if (hbar) hipLaunchKernelGGL((k_update_lsmr<V>), dim3(grid), dim3(kBlock), 0, st, a);
     else hipLaunchKernelGGL((k_update<V>), dim3(grid), dim3(kBlock), 0, st, a);
+    return hipGetLastError();
+}
+
+template <class M, class V, int NT>
+static void small_launch_t(hipStream_t st, const SmallStep &q, const FwdArgs &a, const UpdArgs &u)
+{
+    const dim3 g(q.grid), b(NT);
+    const size_t sh = (size_t)a.n * sizeof(typename AccOf<V>::type);
+    switch (q.lanes) {
+    case 4: hipLaunchKernelGGL((k_fwd_small<M, V, 4, NT>), g, b, sh, st, a, u); break;
+    case 16: hipLaunchKernelGGL((k_fwd_small<M, V, 16, NT>), g, b, sh, st, a, u); break;
+    default: hipLaunchKernelGGL((k_fwd_small<M, V, 256 / SmallE<M>::value, NT>), g, b, sh, st, a, u); break;
+    }
+}
+
+template <class M, class V>
+static void small_launch_m(hipStream_t st, const SmallStep &q, const FwdArgs &a, const UpdArgs &u)
+{
+    if (q.threads == 256) small_launch_t<M, V, 256>(st, q, a, u);
+    else small_launch_t<M, V, 1024>(st, q, a, u);
+}
+
+template <class V>
+hipError_t small_launch(hipStream_t st, const Problem &P, const SmallStep &q)
+{
+    const RowFmt &R = *q.R;
+    FwdArgs a{R.rp, nullptr, R.val, R.sigma, P.m, (int)P.n, P.nx, P.ny, P.nz, P.w, P.damp, q.z, q.Tprev,
+              q.Tcur, q.Ts, q.part_t, q.part_v, q.np_v, q.S, q.ctl, q.parity, MODE_ITER, q.tol, q.wrow,
+              q.grid, nullptr, nullptr, nullptr, q.col16, 0, 0};
+    UpdArgs u{(int)P.n, q.d, q.q, q.v, q.w, q.y, nullptr, nullptr, q.part_q, q.np_q, q.S, q.ctl,
+              1 - q.parity, MODE_ITER, q.hbar, q.cur};
+    if constexpr (Wide<V>::value) {
+        if (R.vt != VT_F64) return hipErrorInvalidValue;
+        small_launch_m<double, V>(st, q, a, u);
+    } else {
+        switch (R.vt) {
+        case VT_F32: small_launch_m<float, V>(st, q, a, u); break;
+        case VT_BF16: small_launch_m<bf16_t, V>(st, q, a, u); break;
+        case VT_F16: small_launch_m<fp16_t, V>(st, q, a, u); break;
+        default: return hipErrorInvalidValue;
+        }
+    }
     return hipGetLastError();
 }
 
@@ -1831,13 +2273,14 @@ hipError_t update_launch(hipStream_t st, const Problem &P, int grid, const doubl
     template hipError_t adj_launch<V>(hipStream_t, const Problem &, int, const ColFmt &,         \
                                       const double *, const void *, const void *, const void *,  \
                                       void *, double *, const double *, int, double *, int *,    \
-                                      int, int, int);                                            \
+                                      int, int, int, double *);                                  \
     template hipError_t init_launch<V>(hipStream_t, const Problem &, int, const double *, int,   \
                                        void *, const float *, void *, double *, void *,          \
                                        double *, int *, int);                                    \
     template hipError_t update_launch<V>(hipStream_t, const Problem &, int, const double *,      \
                                          const void *, void *, double *, double *, void *,       \
                                          double *, const double *, int, double *, int *, int,    \
-                                         int, double *);
+                                         int, double *, double *);                              \
+    template hipError_t small_launch<V>(hipStream_t, const Problem &, const SmallStep &);
 
 }  // namespace lsqr

@@ -174,17 +174,17 @@ __global__ __launch_bounds__(kBlock) void k_node_runs(int64_t nr, int nz, const 
     if (threadIdx.x < 3) atomicAdd(&tot[threadIdx.x], sh[threadIdx.x]);
 }
 
-// Value offset of each quarter of every node's runs (quarter w starts at run
-// r0 + c w / 4, as in the kernels); start[r] = value position of run r.
-__global__ void k_quarters(int64_t nn, int64_t nr, const int64_t *nrp, const uint32_t *start,
+// Value offset of each part of every node's runs (part w starts at run r0 + c
+// w / kNodeParts, as in the kernels); start[r] = value position of run r.
+__global__ void k_parts(int64_t nn, int64_t nr, const int64_t *nrp, const uint32_t *start,
                            int64_t total, int64_t *nvq)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= 4 * nn;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= kNodeParts * nn;
          i += (int64_t)gridDim.x * blockDim.x) {
         int64_t q = nr;
-        if (i < 4 * nn) {
-            const int64_t r0 = nrp[i >> 2], c = nrp[(i >> 2) + 1] - r0;
-            q = r0 + c * (i & 3) / 4;
+        if (i < kNodeParts * nn) {
+            const int64_t r0 = nrp[i / kNodeParts], c = nrp[i / kNodeParts + 1] - r0;
+            q = r0 + c * (i % kNodeParts) / kNodeParts;
         }
         nvq[i] = q < nr ? (int64_t)start[q] : total;
     }
@@ -510,7 +510,7 @@ hipError_t plan_layout(hipStream_t st, Allocator &al, int64_t nn, const RunPlan 
     case 4: PL_TRY((starts<4>(tm, R, start))); break;
     default: PL_TRY((starts<8>(tm, R, start))); break;
     }
-    hipLaunchKernelGGL(k_quarters, dim3(blocks(4 * nn + 1, 256, 4096)), dim3(256), 0, st, nn, R.nr, R.nrp,
+    hipLaunchKernelGGL(k_parts, dim3(blocks(kNodeParts * nn + 1, 256, 4096)), dim3(256), 0, st, nn, R.nr, R.nrp,
                        start, total, nvq);
     return hipGetLastError();
 }
