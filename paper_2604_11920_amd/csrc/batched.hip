@@ -33,6 +33,7 @@ BArgs base_args(lsqr_ctx *c, BatchEngine &B)
         a.norder = c->norder; a.nval = c->nval32;
         if (B.Pr) { a.rrp = c->rrp; a.rrid = c->rrid; a.Pr = B.Pr; a.g_pr = B.g_adj; }
     }
+    a.rb = c->rb; a.va64 = c->va; a.cv64 = c->cv;
     a.d = c->d;
     a.m = c->P.m; a.n = (int)c->P.n; a.nx = c->P.nx; a.ny = c->P.ny; a.nz = c->P.nz;
     a.w = c->P.w; a.damp = c->P.damp;
@@ -41,13 +42,36 @@ BArgs base_args(lsqr_ctx *c, BatchEngine &B)
     return a;
 }
 
+// Few nodes: 8 waves share a node's pairs.
+constexpr int kBatchWideNodes = 1024;
+
+template <int RT, int KS, int MT>
+void launch_fwd_rb(hipStream_t st, int grid, const BArgs &a)
+{
+    hipLaunchKernelGGL((k_bfwd_rb<RT, KS, MT>), dim3(grid), dim3(kBlock), 0, st, a);
+}
+
+template <int RT, int MT, int QM>
+void launch_adj_rb(hipStream_t st, int grid, const BArgs &a)
+{
+    if (a.n / a.nz <= kBatchWideNodes)
+        hipLaunchKernelGGL((k_badj_rb<RT, MT, QM, 8>), dim3(grid), dim3(512), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_badj_rb<RT, MT, QM, 4>), dim3(grid), dim3(256), 0, st, a);
+}
+
 template <int RT>
 void launch_tile(hipStream_t st, int kind, int grid, const BArgs &a)
 {
     switch (kind) {
     case 0: hipLaunchKernelGGL((k_binit<RT>), dim3(grid), dim3(kBlock), 0, st, a); break;
     case 1:
-        if (a.Pr && RT == 32) {       // two-phase product over the node runs
+        if (a.rb.nb) {                // row blocks
+            const bool two = a.rb.rows_max > 16;
+            if (a.nz <= 12) two ? launch_fwd_rb<RT, 3, 2>(st, grid, a) : launch_fwd_rb<RT, 3, 1>(st, grid, a);
+            else if (a.nz <= 20) two ? launch_fwd_rb<RT, 5, 2>(st, grid, a) : launch_fwd_rb<RT, 5, 1>(st, grid, a);
+            else two ? launch_fwd_rb<RT, 8, 2>(st, grid, a) : launch_fwd_rb<RT, 8, 1>(st, grid, a);
+        } else if (a.Pr && RT == 32) {       // two-phase product over the node runs
             hipLaunchKernelGGL(k_bfwd_pr32, dim3(a.g_pr), dim3(kBlock), 0, st, a);
             hipLaunchKernelGGL((k_bfwd<RT>), dim3(grid), dim3(kBlock), 0, st, a);
         } else {                      // entry-wise over the CSR rows
@@ -57,7 +81,11 @@ void launch_tile(hipStream_t st, int kind, int grid, const BArgs &a)
         }
         break;
     default:
-        if (a.nrp && RT == 32) hipLaunchKernelGGL(k_badj_mfma32, dim3(grid), dim3(kBlock), 0, st, a);
+        if (a.rb.nb) {
+            const bool two = a.rb.rows_max > 16;
+            if (a.nz <= 16) two ? launch_adj_rb<RT, 1, 5>(st, grid, a) : launch_adj_rb<RT, 1, 4>(st, grid, a);
+            else two ? launch_adj_rb<RT, 2, 5>(st, grid, a) : launch_adj_rb<RT, 2, 4>(st, grid, a);
+        } else if (a.nrp && RT == 32) hipLaunchKernelGGL(k_badj_mfma32, dim3(grid), dim3(kBlock), 0, st, a);
         else if (a.nrp) hipLaunchKernelGGL((k_badj_nruns<RT>), dim3(grid), dim3(kBlock), 0, st, a);
         else hipLaunchKernelGGL((k_badj<RT>), dim3(grid), dim3(kBlock), 0, st, a);
         break;
@@ -79,10 +107,32 @@ void launch_tiled(hipStream_t st, int kind, int grid, BArgs a, int R, int rt)
     }
 }
 
-// FP32 copies of the values (the batched kernels read FP32).
+// FP32 copies of the values (the batched kernels read FP32): in row blocks where
+// the rows share their nodes, else row-major, column-major and node-major.
 lsqr_status ensure_fp32(lsqr_ctx *c, hipStream_t st)
 {
     const int64_t nnz = c->P.nnz;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (!c->rb_tried) HIP_TRY(c, hipStreamIsCapturing(st, &cap));
+    if (!c->rb_tried && cap == hipStreamCaptureStatusNone) {      // the planning waits for the stream
+        std::vector<void *> kept;
+        if (nnz > 0 && nnz < ((int64_t)1 << 32) && c->P.m < ((int64_t)1 << 31)) {
+            const hipError_t e = plan_row_blocks(st, c->al, c->P.m, c->P.n, c->P.nz, c->rp, c->ci, c->va, c->rb,
+                                                 [&](size_t b) {
+                                                     void *p = ctx_alloc_bytes(c, b);
+                                                     if (p) kept.push_back(p);
+                                                     return p;
+                                                 });
+            if (e != hipSuccess) {
+                for (void *p : kept) ctx_release(c, p);
+                c->rb = RowBlocks{};
+                if (e != hipErrorOutOfMemory)              // out of memory: the other layouts
+                    return fail(c, LSQR_E_DEVICE, std::string("row blocks: ") + hipGetErrorString(e));
+            }
+        }
+        c->rb_tried = true;
+    }
+    if (c->rb.nb) return LSQR_OK;
     if (!c->va32 || !c->cv32) {
         c->va32 = ctx_alloc<float>(c, nnz);
         c->cv32 = ctx_alloc<float>(c, nnz);
@@ -122,7 +172,7 @@ lsqr_status ensure_batch(lsqr_ctx *c, hipStream_t st, int R, int iters)
         B = BatchEngine{};
         B.R = R;
         B.rt = keep_rt && keep_rt <= R ? keep_rt : std::min(R, 32);
-        B.grid = keep_grid ? keep_grid : 1024;
+        B.grid = keep_grid ? keep_grid : 2048;
         B.T[0] = ctx_alloc<float>(c, mb * R);
         B.T[1] = ctx_alloc<float>(c, mb * R);
         B.V = ctx_alloc<float>(c, n * R);
@@ -142,7 +192,7 @@ lsqr_status ensure_batch(lsqr_ctx *c, hipStream_t st, int R, int iters)
             !B.P1 || !B.P2 || !B.P3 || !B.act || !B.why || !B.ctl)
             return fail(c, LSQR_E_OOM, "device allocation failed");
         // per-run partial rows of the two-phase forward product (node runs)
-        if (c->rrid && c->nval32 && c->P.nz <= kMaxNzBatched) {
+        if (!c->rb.nb && c->rrid && c->nval32 && c->P.nz <= kMaxNzBatched) {
             B.Pr = ctx_alloc<float>(c, std::max<int64_t>(c->nnruns, 1) * R);
             if (!B.Pr) return fail(c, LSQR_E_OOM, "device allocation failed");
         }
@@ -155,7 +205,8 @@ lsqr_status ensure_batch(lsqr_ctx *c, hipStream_t st, int R, int iters)
         if (!B.S) return fail(c, LSQR_E_OOM, "state allocation failed");
     }
     B.g_fwd = cap(m * 64, kBlock, B.grid);
-    if (c->nval32 && c->P.nz <= kMaxNzBatched)      // a workgroup per lateral node
+    if (c->rb.nb) B.g_fwd = cap(c->rb.nb, 1, B.grid);             // a workgroup per row block
+    if (c->rb.nb || (c->nval32 && c->P.nz <= kMaxNzBatched))      // a workgroup per lateral node
         B.g_adj = (int)std::max<int64_t>(1, std::min<int64_t>(n / c->P.nz, B.grid));
     else
         B.g_adj = cap(n * 64, kBlock, B.grid);

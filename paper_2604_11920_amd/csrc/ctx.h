@@ -116,6 +116,8 @@ struct lsqr_ctx {
     bool have_eng32 = false;
     double stall_ratio = 0.5;       // refinement: a sweep must bring eta below this x the last
     lsqr::BatchEngine beng;         // the batched solver's buffers
+    lsqr::RowBlocks rb;             // its row blocks, built on first use
+    bool rb_tried = false;
     // refinement and operator scratch (FP64)
     double *xbuf = nullptr, *ybuf = nullptr, *rbar = nullptr, *gbuf = nullptr;
     double *fbuf = nullptr, *Pr = nullptr, *Pa = nullptr, *Pf = nullptr;

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -324,5 +325,33 @@ hipError_t plan_group_sizes(hipStream_t st, Allocator &al, int64_t n, int ng, co
                             int64_t *gcp, int64_t *total);
 hipError_t plan_group_lists(hipStream_t st, int64_t n, int ng, const int32_t *gp, const RunPlan &R,
                             const int64_t *rp, const int32_t *ci, const int64_t *gcp, int32_t *gcol, uint16_t *slot);
+
+// Row blocks of the batched products (nz <= 32): consecutive data rows that cross
+// the same lateral nodes, at most 20 to a block.  A pair is a (block, node) with
+// an entry, nodes ascending in a block.  Its FP32 values are a tile per quad of
+// rows, [depths d0 .. d0+nd_q-1][4 rows] with zeros where a row has no entry, one
+// quad after the other: periods reach down to different depths, so one window
+// for all rows of a block would store about two values per entry.
+constexpr int kBlockRows = 20, kQuads = kBlockRows / 4;
+constexpr int64_t kPlanMaxNodes = (int64_t)1 << 17;    // a block's node set sits in LDS
+struct RowBlocks {
+    int nb = 0;
+    int rows_max = 0;                  // most rows of a block
+    int64_t np = 0;
+    int32_t *row0 = nullptr;           // [nb+1] first row
+    uint32_t *pptr = nullptr;          // [nb+1] pairs of block b: pptr[b] .. pptr[b+1]-1
+    uint4 *pair = nullptr;             // [np] node | d0 << 20 | largest nd_q << 26, position of
+                                       // the tiles / 4 floats, nd_q << 6 q (30 bits), units of 4
+    float *val = nullptr;              // the tiles
+    int64_t *nptr = nullptr;           // [nnodes+1] node-major pairs (blocks ascending)
+    uint4 *nlist = nullptr;            // [np] position, first row, rows | d0 << 8 | units << 16, nd_q
+    int32_t *norder = nullptr;         // [nnodes] by decreasing number of pairs
+};
+// Builds B (buffers from keep, which returns nullptr when out of memory); sets
+// B.nb = 0, keeping nothing, when the rows share too few nodes for blocks to
+// pay or the structure is past a limit.
+hipError_t plan_row_blocks(hipStream_t st, Allocator &al, int64_t m, int64_t n, int nz, const int64_t *rp,
+                           const int32_t *ci, const double *va, RowBlocks &B,
+                           const std::function<void *(size_t)> &keep);
 
 }  // namespace lsqr

@@ -52,6 +52,8 @@ struct BArgs {
     const uint32_t *rrid;
     float *Pr;              // [node runs][R]
     int g_pr;               // workgroups of k_bfwd_pr
+    const double *va64, *cv64;   // FP64 values (CSR, CSC): sparse_dot
+    RowBlocks rb;           // row blocks (k_bfwd_rb, k_badj_rb); rb.nb == 0: none
     const double *d;
     int64_t m;
     int n, nx, ny, nz;
@@ -86,19 +88,35 @@ __device__ __forceinline__ double *srow(const BArgs &a, int k, int r)
     return a.S + ((int64_t)k * a.R + r) * kStateWords;
 }
 
-// out[r] = sum over b < np of p[b][r], for every r < R, in a fixed order; all
-// threads take part.  accs has kBlock entries.
+// out[r] = sum over b < np of p[b][r], for every r < R (a power of two <= 32), in
+// a fixed order; all threads (NW waves) take part.  accs has NW * kMaxRhs
+// entries.  Eight loads in flight per thread: one at a time, the 256 partials of
+// a small system's producer cost its consumers 10 us.
+template <int NW = kBlock / 64>
 __device__ __forceinline__ void sum_rhs_all(const double *p, int np, int R, double *accs,
                                             double *out)
 {
-    const int r = threadIdx.x % R, slot = threadIdx.x / R, per = kBlock / R;
+    const int r = threadIdx.x & (R - 1), per = 64 * NW / R;
     double acc = 0.0;
-    for (int b = slot; b < np; b += per) acc += p[(int64_t)b * R + r];
-    accs[threadIdx.x] = acc;
+    int b = threadIdx.x / R;
+    for (; b + 7 * per < np; b += 8 * per) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = p[(int64_t)(b + u * per) * R + r];
+        acc += tree_sum<8>(x);
+    }
+    double x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = b + u * per < np ? p[(int64_t)(b + u * per) * R + r] : 0.0;
+    acc += tree_sum<8>(x);
+    for (int off = R; off < 64; off <<= 1) acc += __shfl_xor(acc, off, 64);
+    const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (lane < R) accs[wid * R + lane] = acc;
     __syncthreads();
     if (threadIdx.x < R) {
         double s = 0.0;
-        for (int q = 0; q < per; ++q) s += accs[q * R + threadIdx.x];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) s += accs[w * R + threadIdx.x];
         out[threadIdx.x] = s;
     }
     __syncthreads();
@@ -106,7 +124,7 @@ __device__ __forceinline__ void sum_rhs_all(const double *p, int np, int R, doub
 
 // Per-RHS sum of one value per thread (thread t holds right-hand side
 // t % RR, RR divides 64); result in out[0..RR), fixed order.
-template <int RR>
+template <int RR, int NW = kBlock / 64>
 __device__ __forceinline__ void block_sum_rhs(double v, double *accs, double *out)
 {
 #pragma unroll
@@ -115,8 +133,10 @@ __device__ __forceinline__ void block_sum_rhs(double v, double *accs, double *ou
     if (lane < RR) accs[wid * RR + lane] = v;
     __syncthreads();
     if (threadIdx.x < RR) {
-        const int r = threadIdx.x;
-        out[r] = ((accs[r] + accs[RR + r]) + accs[2 * RR + r]) + accs[3 * RR + r];
+        double s = accs[threadIdx.x];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) s += accs[w * RR + threadIdx.x];
+        out[threadIdx.x] = s;
     }
     __syncthreads();
 }
@@ -153,21 +173,20 @@ __global__ __launch_bounds__(kBlock) void k_binit(BArgs a)
 }
 
 // --------------------------------------------------------------- forward --
-// T = A_D V - U diag(alpha) with U = Tprev diag(1/beta), for the tile.
+// Prologue of a forward step: alpha and beta of the tile's right-hand sides
+// (sal, sbe); workgroup 0 sums the update's partials for eta of the previous
+// step and the per-RHS stop rules.  False when the launch has nothing to do.
 template <int RT>
-__global__ __launch_bounds__(kBlock) void k_bfwd(BArgs a)
+__device__ __forceinline__ bool bfwd_prologue(const BArgs &a, double *accs, double *vns, double *sal,
+                                              double *sbe)
 {
 #pragma clang fp contract(off)
-    __shared__ double accs[kBlock];
-    __shared__ double res[kMaxRhs];
-    __shared__ double vns[kMaxRhs];
-    __shared__ double sal[kMaxRhs], sbe[kMaxRhs];
     const bool op = a.mode == MODE_OPERATOR;       // plain product: alpha = 0, no state
     const int k = op ? 0 : a.ctl[C_CNT0 + a.parity];
-    if (!op && k > a.ctl[C_KMAX]) return;
+    if (!op && k > a.ctl[C_KMAX]) return false;
     if (op) {
         if (threadIdx.x < RT) { sal[threadIdx.x] = 0.0; sbe[threadIdx.x] = 1.0; }
-    } else {
+    } else if (blockIdx.x == 0) {
         sum_rhs_all(a.part_in, a.np_in, a.R, accs, vns);
     }
     if (!op && threadIdx.x < RT) {
@@ -176,7 +195,6 @@ __global__ __launch_bounds__(kBlock) void k_bfwd(BArgs a)
         sal[threadIdx.x] = Sp[S_ALPHA];
         sbe[threadIdx.x] = Sp[S_BETA];
         if (blockIdx.x == 0) {
-            // eta of the previous step and the per-RHS stop rules
             const double vn = sqrt(vns[r]);
             double *S0 = srow(a, 0, r);
             if (k == 1) {
@@ -195,6 +213,58 @@ __global__ __launch_bounds__(kBlock) void k_bfwd(BArgs a)
         }
     }
     __syncthreads();
+    return true;
+}
+
+// Smoothing and damping rows of the tile: one thread per (row, rhs).
+template <int RT>
+__device__ __forceinline__ double bfwd_reg_rows(const BArgs &a, double alpha, double beta)
+{
+#pragma clang fp contract(off)
+    const bool op = a.mode == MODE_OPERATOR;
+    const int R = a.R, cofs = a.r0 + threadIdx.x % RT;
+    double sq = 0.0;
+    const int64_t nreg = 2 * (int64_t)a.n;
+    for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < nreg * RT;
+         idx += (int64_t)gridDim.x * kBlock) {
+        const int64_t r = idx / RT;
+        float yv;
+        if (r < a.n) {
+            const int pp = (int)r;
+            const int iz = pp % a.nz, ixy = pp / a.nz, ix = ixy % a.nx, iy = ixy / a.nx;
+            const int sxy = a.nx * a.nz;
+            float acc = 0.f;
+            int deg = 0;
+            if (ix > 0) { acc += a.Z[(int64_t)(pp - a.nz) * R + cofs]; ++deg; }
+            if (ix < a.nx - 1) { acc += a.Z[(int64_t)(pp + a.nz) * R + cofs]; ++deg; }
+            if (iy > 0) { acc += a.Z[(int64_t)(pp - sxy) * R + cofs]; ++deg; }
+            if (iy < a.ny - 1) { acc += a.Z[(int64_t)(pp + sxy) * R + cofs]; ++deg; }
+            if (iz > 0) { acc += a.Z[(int64_t)(pp - 1) * R + cofs]; ++deg; }
+            if (iz < a.nz - 1) { acc += a.Z[(int64_t)(pp + 1) * R + cofs]; ++deg; }
+            yv = (acc - (float)deg * a.Z[(int64_t)pp * R + cofs]) * (float)a.w;
+        } else {
+            yv = (float)a.damp * a.Z[(r - a.n) * R + cofs];
+        }
+        const int64_t row = a.m + r;
+        const double u = op ? 0.0 : (double)a.Tprev[row * R + cofs] / beta;
+        const float t = (float)((double)yv - alpha * u);
+        a.Tcur[row * R + cofs] = t;
+        sq += (double)t * (double)t;
+    }
+    return sq;
+}
+
+// T = A_D V - U diag(alpha) with U = Tprev diag(1/beta), for the tile.
+template <int RT>
+__global__ __launch_bounds__(kBlock) void k_bfwd(BArgs a)
+{
+#pragma clang fp contract(off)
+    __shared__ double accs[kBlock];
+    __shared__ double res[kMaxRhs];
+    __shared__ double vns[kMaxRhs];
+    __shared__ double sal[kMaxRhs], sbe[kMaxRhs];
+    const bool op = a.mode == MODE_OPERATOR;       // plain product: alpha = 0, no state
+    if (!bfwd_prologue<RT>(a, accs, vns, sal, sbe)) return;
     constexpr int EPW = 64 / RT;
     const int lane = threadIdx.x & 63, er = lane / RT, rr = lane % RT;
     const double alpha = sal[rr], beta = sbe[rr] > 0.0 ? sbe[rr] : 1.0;
@@ -250,34 +320,7 @@ __global__ __launch_bounds__(kBlock) void k_bfwd(BArgs a)
             sq += (double)t * (double)t;
         }
     }
-    // smoothing and damping rows: one thread per (row, rhs)
-    const int64_t nreg = 2 * (int64_t)a.n;
-    for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < nreg * RT;
-         idx += (int64_t)gridDim.x * kBlock) {
-        const int64_t r = idx / RT;
-        float yv;
-        if (r < a.n) {
-            const int pp = (int)r;
-            const int iz = pp % a.nz, ixy = pp / a.nz, ix = ixy % a.nx, iy = ixy / a.nx;
-            const int sxy = a.nx * a.nz;
-            float acc = 0.f;
-            int deg = 0;
-            if (ix > 0) { acc += a.Z[(int64_t)(pp - a.nz) * R + cofs]; ++deg; }
-            if (ix < a.nx - 1) { acc += a.Z[(int64_t)(pp + a.nz) * R + cofs]; ++deg; }
-            if (iy > 0) { acc += a.Z[(int64_t)(pp - sxy) * R + cofs]; ++deg; }
-            if (iy < a.ny - 1) { acc += a.Z[(int64_t)(pp + sxy) * R + cofs]; ++deg; }
-            if (iz > 0) { acc += a.Z[(int64_t)(pp - 1) * R + cofs]; ++deg; }
-            if (iz < a.nz - 1) { acc += a.Z[(int64_t)(pp + 1) * R + cofs]; ++deg; }
-            yv = (acc - (float)deg * a.Z[(int64_t)pp * R + cofs]) * (float)a.w;
-        } else {
-            yv = (float)a.damp * a.Z[(r - a.n) * R + cofs];
-        }
-        const int64_t row = a.m + r;
-        const double u = op ? 0.0 : (double)a.Tprev[row * R + cofs] / beta;
-        const float t = (float)((double)yv - alpha * u);
-        a.Tcur[row * R + cofs] = t;
-        sq += (double)t * (double)t;
-    }
+    sq += bfwd_reg_rows<RT>(a, alpha, beta);
     block_sum_rhs<RT>(sq, accs, res);
     if (threadIdx.x < RT) a.part_out[(int64_t)blockIdx.x * a.R + a.r0 + threadIdx.x] = res[threadIdx.x];
 }
@@ -737,6 +780,388 @@ __global__ __launch_bounds__(kBlock) void k_badj_nruns(BArgs a)
     if (threadIdx.x < RT) a.part_out[(int64_t)blockIdx.x * a.R + a.r0 + threadIdx.x] = res[threadIdx.x];
 }
 
+// ------------------------------------------------------------ row blocks --
+// The block products over row blocks (RowBlocks), on the matrix cores.  Rows of
+// one path cross the same lateral nodes at all its periods, so a block's values
+// at a node are a small dense product: forward, [rows x depths] x [depths x
+// right-hand sides]; transposed, [depths x rows] x [rows x right-hand sides],
+// with v_mfma_f32_16x16x4f32 (A: m = lane mod 16, k = lane / 16; B: k = lane / 16,
+// n = lane mod 16; D register e: m = 4 (lane / 16) + e, n = lane mod 16).  A pair's
+// tiles are read as 16 bytes a lane, whole lines once, and the wave takes its A
+// operands from them in its LDS area (read straight into the operands, a line
+// was asked for by several loads: transposed 2,010 against 1,410 us).  Buffer loads
+// bring no address arithmetic and no clamps: 2,140 -> 1,650 us forward.  32 right-hand sides are read as pairs (column tile q,
+// column i holds right-hand side 2 i + q).  A node's rows of Z (a block's rows of
+// T) are read once per pair instead of once per run, and there are no partial
+// rows: k_bfwd_pr32 + k_bfwd<32> wrote and read back 128 bytes per run.  Two pairs'
+// products are summed from zero in FP32 and added up in FP64.
+// 32 right-hand sides, 565 M entries: forward 4,840 -> 1,650 us, transposed 3,010
+// -> 1,300 us; 8 right-hand sides, 95 M entries: 776 -> 220 and 638 -> 240 us.  What
+// bounds them: matrix and vector units share a wave's issue (a third of the time
+// each), and three waves a SIMD cover the latency of the rest; the bytes (2.7 GB of
+// values) would take 0.4 ms.
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+// A product that came out non-finite, again from its own entries: in a block's
+// product an infinity or NaN of the vector block also meets the zeros of rows
+// (depths) that have no entry there.
+__device__ __noinline__ float sparse_dot(const int64_t *ptr, const int32_t *idx, const double *val, int64_t i,
+                                         const float *x, int R, int c)
+{
+#pragma clang fp contract(off)
+    float y = 0.f;
+    for (int64_t p = ptr[i]; p < ptr[i + 1]; ++p) y += (float)val[p] * x[(int64_t)idx[p] * R + c];
+    return y;
+}
+
+// The workgroup's index in a scalar register.  Past a branch on workgroup 0 the
+// compiler keeps blockIdx.x in a vector register (a constant on one side of the
+// branch), and with it the loads of every pair it leads to.
+__device__ __forceinline__ int scalar_block()
+{
+    int b = (int)blockIdx.x;
+    asm volatile("" : "+s"(b));
+    return b;
+}
+
+// Raw buffer of `bytes` bytes at p (uniform): reads past its end return zeros,
+// so tiles and rows of any size are read with the same lane offsets and without
+// a comparison, and a lane past the end costs no traffic.
+typedef __amdgpu_buffer_rsrc_t Buf;
+__device__ __forceinline__ Buf buffer(const void *p, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+
+// NT neighbouring values at byte offset off.
+template <int NT>
+__device__ __forceinline__ void ld_rhs(float (&b)[NT], Buf r, int off)
+{
+    if constexpr (NT == 2) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+        b[0] = __uint_as_float(v[0]);
+        b[1] = __uint_as_float(v[1]);
+    } else {
+        b[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    }
+}
+
+// A pair's tiles, 16 bytes a lane (streamed), and from there into the wave's LDS
+// area.
+template <int LN>
+__device__ __forceinline__ void ld_tiles(floatx4 (&v)[LN], const RowBlocks &B, uint32_t pos, uint32_t units, int lane)
+{
+    const Buf r = buffer(B.val + 4 * (int64_t)pos, 16 * units);
+#pragma unroll
+    for (int l = 0; l < LN; ++l) {
+        const auto x = __builtin_amdgcn_raw_buffer_load_b128(r, 16 * lane + 1024 * l, 0, 2);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[l][e] = __uint_as_float(x[e]);
+    }
+}
+template <int LN>
+__device__ __forceinline__ void put_tiles(float *my, const floatx4 (&v)[LN], int lane)
+{
+#pragma unroll
+    for (int l = 0; l < LN; ++l) *(floatx4 *)(my + 4 * (lane + 64 * l)) = v[l];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// KS: products of four depths a tile can need.  MT: row tiles of 16.  The 4
+// waves of a workgroup share a block's pairs (a wave to a block: the longest path
+// decides: 2,450 against 2,140 us with 32 right-hand sides).  The tiles and
+// the rows of Z of the next pair are in flight.
+template <int RT, int KS, int MT>
+__global__ __launch_bounds__(kBlock, RT > 16 ? 3 : 4) void k_bfwd_rb(BArgs a)
+{
+#pragma clang fp contract(off)
+    constexpr int NT = RT > 16 ? 2 : 1, CT = RT > 16 ? 16 : RT, W = 16 * NT;
+    constexpr int LN = (4 * KS * (MT == 2 ? kQuads : 4) + 63) / 64;
+    __shared__ double accs[kBlock];
+    __shared__ double res[kMaxRhs];
+    __shared__ double vns[kMaxRhs];
+    __shared__ double sal[kMaxRhs], sbe[kMaxRhs];
+    __shared__ floatx4 tiles[4][64 * LN + 4 * KS];        // operands not used reach past the tiles
+    __shared__ float red[4 * 16 * MT * W];
+    const bool op = a.mode == MODE_OPERATOR;
+    const int blk = scalar_block();
+    if (!bfwd_prologue<RT>(a, accs, vns, sal, sbe)) return;
+    const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int R = a.R, nz = a.nz;
+    const RowBlocks &B = a.rb;
+    float *my = (float *)tiles[wid];
+    struct Set {
+        floatx4 v[LN];
+        float bv[KS][NT];
+        uint32_t nds;
+        int ks;
+    };
+    int zoff[KS];                                         // byte offsets of the lane's rows of Z
+#pragma unroll
+    for (int t = 0; t < KS; ++t) zoff[t] = 4 * ((4 * t + g) * R + NT * (i & (CT - 1)));
+    double sq = 0.0;
+    for (int b = blk; b < B.nb; b += (int)gridDim.x) {
+        const int row0 = ld_uniform(B.row0, b), nrow = ld_uniform(B.row0, b + 1) - row0;
+        const uint32_t p0 = ld_uniform(B.pptr, b), cnt = ld_uniform(B.pptr, b + 1) - p0;
+        uint32_t p = p0 + cnt * (uint32_t)wid / 4;
+        const uint32_t pe = p0 + cnt * (uint32_t)(wid + 1) / 4;
+        double acc[MT][NT][4] = {};
+        if (p < pe) {
+            floatx4 c[MT][NT] = {};
+            auto load = [&](Set &s, const uint4 &P) {
+                const int d0 = (int)((P.x >> 20) & 31u), nd = (int)(P.x >> 26);
+                s.ks = (nd + 3) >> 2;
+                s.nds = P.z;
+                // as many loads for any pair: a load skipped by a branch makes the
+                // wait for the set in use wait for this one too
+                ld_tiles(s.v, B, P.y, P.w, lane);
+                const Buf z = buffer(a.Z + (int64_t)((P.x & 0xfffffu) * (uint32_t)nz + (uint32_t)d0) * R + a.r0,
+                                     (uint32_t)(4 * (nd * R - a.r0)));
+#pragma unroll
+                for (int t = 0; t < KS; ++t) ld_rhs(s.bv[t], z, zoff[t]);
+            };
+            auto mul = [&](const Set &s) {
+                put_tiles(my, s.v, lane);
+                // position | depths << 16 of the lane's quad (row tile 0) and of quad 4
+                uint32_t q0 = s.nds & 63u, at = q0, mine = q0 << 16;
+#pragma unroll
+                for (int q = 1; q < 4; ++q) {
+                    const uint32_t nd = (s.nds >> (6 * q)) & 63u;
+                    mine = (i >> 2) == q ? at | nd << 16 : mine;
+                    at += nd;
+                }
+                // products the lane takes part in
+                const int t0 = ((int)(mine >> 16) - g + 3) >> 2, nd4 = (int)((s.nds >> 24) & 63u), t4 = (nd4 - g + 3) >> 2;
+                const float *a0 = my + 4 * ((mine & 0xffffu) + g) + (i & 3), *a1 = my + 4 * (at + g) + (i & 3);
+                float x0[KS], x1[KS];
+#pragma unroll
+                for (int t = 0; t < KS; ++t) {
+                    x0[t] = a0[16 * t];
+                    if (MT == 2) x1[t] = a1[16 * t];
+                }
+#pragma unroll
+                for (int t = 0; t < KS; ++t)
+                    if (t < s.ks) {
+                        const float x = t < t0 ? x0[t] : 0.f;
+#pragma unroll
+                        for (int q = 0; q < NT; ++q)
+                            c[0][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, s.bv[t][q], c[0][q], 0, 0, 0);
+                        if (MT == 2 && 4 * t < nd4) {
+                            const float y = t < t4 ? x1[t] : 0.f;
+#pragma unroll
+                            for (int q = 0; q < NT; ++q)
+                                c[MT - 1][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(y, s.bv[t][q], c[MT - 1][q], 0, 0, 0);
+                        }
+                    }
+                __builtin_amdgcn_wave_barrier();
+            };
+            auto flush = [&]() {
+#pragma unroll
+                for (int h = 0; h < MT; ++h)
+#pragma unroll
+                    for (int q = 0; q < NT; ++q) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[h][q][e] += (double)c[h][q][e];
+                        c[h][q] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    }
+            };
+            auto entry = [&](uint32_t q) {
+                const uint32_t *e = (const uint32_t *)(B.pair + (q < pe ? q : pe - 1));
+                return make_uint4(ld_uniform(e, 0), ld_uniform(e, 1), ld_uniform(e, 2), ld_uniform(e, 3));
+            };
+            Set s0, s1;
+            load(s0, entry(p));
+            uint4 e1 = entry(p + 1);
+            for (;;) {
+                load(s1, e1);
+                e1 = entry(p + 2);
+                mul(s0);
+                if (++p >= pe) break;
+                load(s0, e1);
+                e1 = entry(p + 2);
+                mul(s1);
+                if (++p >= pe) break;
+                flush();
+            }
+            flush();
+        }
+#pragma unroll
+        for (int h = 0; h < MT; ++h)
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    red[(wid * 16 * MT + 16 * h + 4 * g + e) * W + NT * i + q] = (float)acc[h][q][e];
+        __syncthreads();
+        for (int e = threadIdx.x; e < nrow * RT; e += kBlock) {
+            const int r = e / RT, c = e % RT, o = r * W + c;
+            constexpr int S = 16 * MT * W;
+            float y = ((red[o] + red[o + S]) + red[o + 2 * S]) + red[o + 3 * S];
+            if (!isfinite(y)) y = sparse_dot(a.rp, a.ci, a.va64, row0 + r, a.Z, R, a.r0 + c);
+            const int64_t at = (int64_t)(row0 + r) * R + a.r0 + c;
+            const double u = op ? 0.0 : (double)a.Tprev[at] / (sbe[c] > 0.0 ? sbe[c] : 1.0);
+            const float t = (float)((double)y - sal[c] * u);
+            a.Tcur[at] = t;
+            sq += (double)t * (double)t;
+        }
+        __syncthreads();
+    }
+    const int rr = threadIdx.x % RT;
+    sq += bfwd_reg_rows<RT>(a, sal[rr], sbe[rr] > 0.0 ? sbe[rr] : 1.0);
+    block_sum_rhs<RT>(sq, accs, res);
+    if (threadIdx.x < RT) a.part_out[(int64_t)blockIdx.x * R + a.r0 + threadIdx.x] = res[threadIdx.x];
+}
+
+// Transposed: a workgroup per node (decreasing number of pairs, boustrophedon),
+// its NW waves on fixed parts of the node's pairs.  MT: depth tiles of 16, QM: row
+// quads a block can have; a product takes one quad.
+template <int RT, int MT, int QM, int NW>
+__global__ __launch_bounds__(64 * NW, RT > 16 ? 3 : 4) void k_badj_rb(BArgs a)
+{
+#pragma clang fp contract(off)
+    constexpr int NT = RT > 16 ? 2 : 1, CT = RT > 16 ? 16 : RT, W = 16 * NT;
+    constexpr int LN = (16 * MT * QM + 63) / 64;
+    __shared__ double accs[NW * kMaxRhs];
+    __shared__ double res[kMaxRhs];
+    __shared__ double b2[kMaxRhs];
+    __shared__ floatx4 tiles[NW][64 * LN + 16 * MT];      // operands not used reach past the tiles
+    __shared__ float red[NW * 16 * MT * W];
+    const bool op = a.mode == MODE_OPERATOR;
+    const int blk = scalar_block();
+    int k = 0;
+    if (a.mode == MODE_ITER) {
+        k = a.ctl[C_CNT0 + a.parity];
+        if (k > a.ctl[C_KMAX]) return;
+    }
+    if (op) {
+        if (threadIdx.x < a.R) b2[threadIdx.x] = 1.0;
+        __syncthreads();
+    } else {
+        sum_rhs_all<NW>(a.part_in, a.np_in, a.R, accs, b2);
+    }
+    if (!op && blockIdx.x == 0 && threadIdx.x < RT) {
+        const int r = a.r0 + threadIdx.x;
+        srow(a, k, r)[S_BETA] = sqrt(b2[r]);
+    }
+    const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int R = a.R, nz = a.nz, nnodes = a.n / nz, G = gridDim.x;
+    const RowBlocks &B = a.rb;
+    float *my = (float *)tiles[wid];
+    struct Set {
+        floatx4 v[LN];
+        float bv[QM][NT];
+        uint32_t nds;
+        int d0;
+    };
+    int toff[QM];                                         // byte offsets of the lane's rows of T
+#pragma unroll
+    for (int t = 0; t < QM; ++t) toff[t] = 4 * ((4 * t + g) * R + NT * (i & (CT - 1)));
+    double sq = 0.0;
+    for (int s = 0; s * G < nnodes; ++s) {
+        const int idx = s * G + ((s & 1) ? G - 1 - blk : blk);
+        if (idx >= nnodes) continue;                        // uniform over the workgroup
+        const int node = ld_uniform(B.norder, idx);
+        const int64_t l0 = ld_uniform(B.nptr, node), cnt = ld_uniform(B.nptr, node + 1) - l0;
+        int64_t p = l0 + cnt * wid / NW;
+        const int64_t pe = l0 + cnt * (wid + 1) / NW;
+        double acc[MT][NT][4] = {};
+        if (p < pe) {
+            floatx4 c[MT][NT] = {};
+            auto entry = [&](int64_t q) {
+                const uint32_t *e = (const uint32_t *)(B.nlist + (q < pe ? q : pe - 1));
+                return make_uint4(ld_uniform(e, 0), ld_uniform(e, 1), ld_uniform(e, 2), ld_uniform(e, 3));
+            };
+            auto load = [&](Set &S, const uint4 &e) {
+                const int nrow = (int)(e.z & 255u);
+                S.d0 = (int)((e.z >> 8) & 255u);
+                S.nds = e.w;
+                ld_tiles(S.v, B, e.x, e.z >> 16, lane);
+                const Buf T = buffer(a.Tcur + (int64_t)e.y * R + a.r0, (uint32_t)(4 * (nrow * R - a.r0)));
+#pragma unroll
+                for (int t = 0; t < QM; ++t) ld_rhs(S.bv[t], T, toff[t]);
+            };
+            auto mul = [&](const Set &S) {
+                put_tiles(my, S.v, lane);
+                float x[QM][MT];
+                int at = 0;
+#pragma unroll
+                for (int t = 0; t < QM; ++t) {
+                    const int nd = (int)((S.nds >> (6 * t)) & 63u);
+#pragma unroll
+                    for (int h = 0; h < MT; ++h) {
+                        const int rel = 16 * h + i - S.d0;
+                        const float y = my[4 * (at + max(rel, 0)) + g];
+                        x[t][h] = (unsigned)rel < (unsigned)nd ? y : 0.f;
+                    }
+                    at += nd;
+                }
+#pragma unroll
+                for (int t = 0; t < QM; ++t) {
+                    const int nd = (int)((S.nds >> (6 * t)) & 63u);
+#pragma unroll
+                    for (int h = 0; h < MT; ++h)
+                        if (nd && S.d0 < 16 * h + 16 && S.d0 + nd > 16 * h) {
+#pragma unroll
+                            for (int q = 0; q < NT; ++q)
+                                c[h][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t][h], S.bv[t][q], c[h][q], 0, 0, 0);
+                        }
+                }
+                __builtin_amdgcn_wave_barrier();
+            };
+            auto flush = [&]() {
+#pragma unroll
+                for (int h = 0; h < MT; ++h)
+#pragma unroll
+                    for (int q = 0; q < NT; ++q) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[h][q][e] += (double)c[h][q][e];
+                        c[h][q] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    }
+            };
+            Set s0, s1;
+            load(s0, entry(p));
+            uint4 e1 = entry(p + 1);
+            for (;;) {
+                load(s1, e1);
+                e1 = entry(p + 2);
+                mul(s0);
+                if (++p >= pe) break;
+                load(s0, e1);
+                e1 = entry(p + 2);
+                mul(s1);
+                if (++p >= pe) break;
+                flush();
+            }
+            flush();
+        }
+#pragma unroll
+        for (int h = 0; h < MT; ++h)
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    red[(wid * 16 * MT + 16 * h + 4 * g + e) * W + NT * i + q] = (float)acc[h][q][e];
+        __syncthreads();
+        for (int cell = threadIdx.x; cell < nz * RT; cell += 64 * NW) {
+            const int cz = cell / RT, cr = cell % RT;
+            float y = red[cz * W + cr];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) y += red[(w * 16 * MT + cz) * W + cr];
+            const int c = a.r0 + cr;
+            if (!isfinite(y)) y = sparse_dot(a.cp, a.ri, a.cv64, (int64_t)node * nz + cz, a.Tcur, R, c);
+            const double bc = sqrt(b2[c]);
+            sq += badj_col_out(a, (int64_t)node * nz + cz, c, y, bc, bc > 0.0 ? bc : 1.0);
+        }
+        __syncthreads();
+    }
+    // per-RHS partial sums: thread t's squares belong to rhs lane t % RT
+    block_sum_rhs<RT, NW>(sq, accs, res);
+    if (threadIdx.x < RT) a.part_out[(int64_t)blockIdx.x * R + a.r0 + threadIdx.x] = res[threadIdx.x];
+}
+
 // ----------------------------------------------------------------- update --
 // All R right-hand sides: alpha_r, the Givens step per r (FP64) and the
 // x/w/v sweep over [n][R]; frozen right-hand sides keep x, w, v.  Writes the
@@ -799,11 +1224,12 @@ __global__ __launch_bounds__(kBlock) void k_bupdate(BArgs a)
     }
     __syncthreads();
     double sq = 0.0;
+    const int lg = __ffs(R) - 1;                // R is a power of two
     const int64_t tot = (int64_t)a.n * R;
     for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < tot;
          idx += (int64_t)gridDim.x * kBlock) {
-        const int r = (int)(idx % R);           // == threadIdx.x % R
-        const int64_t j = idx / R;
+        const int r = threadIdx.x & (R - 1);    // R divides the workgroup's threads
+        const int64_t j = idx >> lg;
         double vj;
         if (live[r] && als[r] > 0.0) {
             const float vv = (float)((double)a.Q[idx] / als[r]);
@@ -824,12 +1250,12 @@ __global__ __launch_bounds__(kBlock) void k_bupdate(BArgs a)
         sq += dv * dv;
     }
     // per-RHS sum over the workgroup in a fixed order
-    accs[threadIdx.x] = sq;
+    for (int off = R; off < 64; off <<= 1) sq += __shfl_xor(sq, off, 64);
+    if ((threadIdx.x & 63) < R) accs[(threadIdx.x >> 6) * R + (threadIdx.x & 63)] = sq;
     __syncthreads();
     if (threadIdx.x < R) {
-        double s2 = 0.0;
-        for (int q = 0; q < kBlock / R; ++q) s2 += accs[q * R + threadIdx.x];
-        a.part_out[(int64_t)blockIdx.x * R + threadIdx.x] = s2;
+        const int r = threadIdx.x;
+        a.part_out[(int64_t)blockIdx.x * R + r] = ((accs[r] + accs[R + r]) + accs[2 * R + r]) + accs[3 * R + r];
     }
     if (blockIdx.x == 0 && threadIdx.x == 0 && a.mode == MODE_ITER) {
         a.ctl[C_ITERS] = k;
@@ -863,7 +1289,7 @@ __global__ __launch_bounds__(kBlock) void k_bfinal(BArgs a, double *dm)
     const int64_t tot = (int64_t)a.n * R;
     for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < tot;
          idx += (int64_t)gridDim.x * kBlock)
-        dm[idx] = a.d[idx / R] * a.Y[idx];
+        dm[idx] = a.d[idx >> (__ffs(R) - 1)] * a.Y[idx];
 }
 
 }  // namespace lsqr

@@ -388,6 +388,189 @@ __global__ __launch_bounds__(kBlock) void k_group_cols(int ng, int words, const 
     }
 }
 
+// ------------------------------------------------------------ row blocks --
+// Segments of row i: its entries at one lateral node.  cnt[i] (EMIT = false),
+// else node, row, position of the first entry at srp[i] on.
+template <bool EMIT>
+__global__ __launch_bounds__(kBlock) void k_segments(int64_t m, int nz, const int64_t *rp, const int32_t *ci,
+                                                     uint32_t *cnt, const int64_t *srp, uint32_t *node,
+                                                     uint32_t *row_of, uint32_t *pos)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t waves = (int64_t)gridDim.x * (kBlock / 64);
+    for (int64_t row = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); row < m; row += waves) {
+        const int64_t s = rp[row], e = rp[row + 1];
+        int64_t base = EMIT ? srp[row] : 0;
+        for (int64_t p0 = s; p0 < e; p0 += 64) {
+            const int64_t p = p0 + lane;
+            bool start = false;
+            int k = 0;
+            if (p < e) {
+                k = ci[p] / nz;
+                start = p == s || ci[p - 1] / nz != k;
+            }
+            const uint64_t mask = __ballot(start);
+            if (EMIT && start) {
+                const int64_t q = base + __popcll(mask & (((uint64_t)1 << lane) - 1));
+                node[q] = (uint32_t)k;
+                row_of[q] = (uint32_t)row;
+                pos[q] = (uint32_t)p;
+            }
+            base += __popcll(mask);
+        }
+        if (!EMIT && lane == 0) cnt[row] = (uint32_t)base;
+    }
+}
+
+// cut[i] = 1 when rows i - 1 and i share fewer than half of the larger one's
+// nodes (a wave per row; both lists ascend).
+__global__ __launch_bounds__(kBlock) void k_row_cuts(int64_t m, const int64_t *srp, const uint32_t *node,
+                                                     uint8_t *cut)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t waves = (int64_t)gridDim.x * (kBlock / 64);
+    for (int64_t row = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); row < m; row += waves) {
+        if (row == 0) {
+            if (lane == 0) cut[0] = 1;
+            continue;
+        }
+        const int64_t a0 = srp[row - 1], a1 = srp[row], b1 = srp[row + 1];
+        int common = 0;
+        for (int64_t q = a1 + lane; q < b1; q += 64) {
+            const uint32_t k = node[q];
+            int64_t lo = a0, hi = a1;
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) / 2;
+                if (node[mid] < k) lo = mid + 1;
+                else hi = mid;
+            }
+            common += lo < a1 && node[lo] == k;
+        }
+        common = group_sum<64>(common);
+        if (lane == 0) cut[row] = 2 * (int64_t)common < max(a1 - a0, b1 - a1);
+    }
+}
+
+// A workgroup per block.  FILL = false: its pairs (ucnt).  FILL = true: its
+// pairs' nodes and blocks, and the pair of every segment (slot).
+template <bool FILL>
+__global__ __launch_bounds__(kBlock) void k_blocks(int nb, int nwords, const int32_t *row0, const int64_t *srp,
+                                                   const uint32_t *node, uint32_t *ucnt, const uint32_t *pptr,
+                                                   uint32_t *pnode, uint32_t *pblk, uint32_t *slot)
+{
+    extern __shared__ uint32_t bits[];
+    uint32_t *rank = bits + nwords;
+    __shared__ int ws[kBlock / 64];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int per = (nwords + kBlock - 1) / kBlock;
+    for (int b = blockIdx.x; b < nb; b += gridDim.x) {
+        const int64_t q0 = srp[row0[b]], q1 = srp[row0[b + 1]];
+        for (int w = threadIdx.x; w < nwords; w += kBlock) bits[w] = 0u;
+        __syncthreads();
+        for (int64_t q = q0 + threadIdx.x; q < q1; q += kBlock) atomicOr(&bits[node[q] >> 5], 1u << (node[q] & 31u));
+        __syncthreads();
+        const int w0 = min(nwords, (int)threadIdx.x * per), w1 = min(nwords, w0 + per);
+        int set = 0;
+        for (int w = w0; w < w1; ++w) set += __popc(bits[w]);
+        const int incl = wave_incl_scan(set);
+        if (lane == 63) ws[wid] = incl;
+        __syncthreads();
+        if (!FILL) {
+            if (threadIdx.x == 0) ucnt[b] = (uint32_t)(ws[0] + ws[1] + ws[2] + ws[3]);
+        } else {
+            const uint32_t p0 = pptr[b];
+            int at = incl - set;
+            for (int w = 0; w < wid; ++w) at += ws[w];
+            for (int w = w0; w < w1; ++w) {
+                rank[w] = (uint32_t)at;
+                for (uint32_t v = bits[w]; v; v &= v - 1, ++at) {
+                    pnode[p0 + at] = (uint32_t)(32 * w + __ffs((int)v) - 1);
+                    pblk[p0 + at] = (uint32_t)b;
+                }
+            }
+            __syncthreads();
+            for (int64_t q = q0 + threadIdx.x; q < q1; q += kBlock) {
+                const uint32_t k = node[q];
+                slot[q] = p0 + rank[k >> 5] + (uint32_t)__popc(bits[k >> 5] & ((1u << (k & 31u)) - 1u));
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// First depth of every pair (lo, from 32 on) and end of the depths of each of
+// its row quads (hi, from 0 on).
+__global__ void k_windows(int64_t ns, int nz, const int64_t *rp, const int32_t *ci, const uint32_t *row_of,
+                          const uint32_t *pos, const uint32_t *slot, const uint32_t *pblk, const int32_t *row0,
+                          uint32_t *lo, uint32_t *hi)
+{
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < ns;
+         q += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t row = row_of[q], p = slot[q];
+        const int64_t end = q + 1 < ns && row_of[q + 1] == row ? (int64_t)pos[q + 1] : rp[row + 1];
+        atomicMin(&lo[p], (uint32_t)(ci[pos[q]] % nz));
+        atomicMax(&hi[(int64_t)p * kQuads + ((int)row - row0[pblk[p]]) / 4], (uint32_t)(ci[end - 1] % nz + 1));
+    }
+}
+
+// 16-byte units of every pair: the depths of its quads.
+__global__ void k_tile_size(int64_t np, const uint32_t *lo, const uint32_t *hi, uint32_t *size)
+{
+    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < np; p += (int64_t)gridDim.x * blockDim.x) {
+        uint32_t u = 0;
+        for (int q = 0; q < kQuads; ++q) u += max(hi[p * kQuads + q], lo[p]) - lo[p];
+        size[p] = u;
+    }
+}
+
+__global__ void k_pairs(int64_t np, const uint32_t *pnode, const uint32_t *lo, const uint32_t *hi,
+                        const uint32_t *size, const int64_t *off, uint4 *pair, uint32_t *key, uint32_t *idx)
+{
+    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < np; p += (int64_t)gridDim.x * blockDim.x) {
+        uint32_t nds = 0, most = 0;
+        for (int q = 0; q < kQuads; ++q) {
+            const uint32_t nd = max(hi[p * kQuads + q], lo[p]) - lo[p];
+            nds |= nd << (6 * q);
+            most = max(most, nd);
+        }
+        pair[p] = make_uint4(pnode[p] | lo[p] << 20 | most << 26, (uint32_t)off[p], nds, size[p]);
+        key[p] = pnode[p];
+        idx[p] = (uint32_t)p;
+    }
+}
+
+// Values of the segments (16 lanes each) into the tiles, zeroed before.
+__global__ __launch_bounds__(256) void k_tile_values(int64_t ns, int nz, const int64_t *rp, const int32_t *ci,
+                                                     const double *va, const uint32_t *row_of,
+                                                     const uint32_t *pos, const uint32_t *slot,
+                                                     const uint32_t *pblk, const int32_t *row0,
+                                                     const uint4 *pair, float *val)
+{
+    const int l = threadIdx.x & 15;
+    for (int64_t q = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 4; q < ns; q += (int64_t)gridDim.x * 16) {
+        const uint32_t row = row_of[q], p = slot[q];
+        const uint4 t = pair[p];
+        const int r = (int)row - row0[pblk[p]], d0 = (int)((t.x >> 20) & 31u);
+        int64_t u = t.y;
+        for (int c = 0; c < r / 4; ++c) u += (t.z >> (6 * c)) & 63u;
+        const int64_t end = q + 1 < ns && row_of[q + 1] == row ? (int64_t)pos[q + 1] : rp[row + 1];
+        float *o = val + 4 * u + (r & 3);
+        for (int64_t k = pos[q] + l; k < end; k += 16) o[4 * (ci[k] % nz - d0)] = (float)va[k];
+    }
+}
+
+__global__ void k_node_pairs(int64_t np, const uint32_t *perm, const uint32_t *pblk, const uint4 *pair,
+                             const int32_t *row0, uint4 *nlist)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < np; i += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t p = perm[i], b = pblk[p];
+        const uint4 t = pair[p];
+        const int r0 = row0[b];
+        nlist[i] = make_uint4(t.y, (uint32_t)r0,
+                              (uint32_t)(row0[b + 1] - r0) | ((t.x >> 20) & 31u) << 8 | t.w << 16, t.z);
+    }
+}
+
 // Temporary device memory of one planning call, given back when it ends (after
 // the stream has finished with it).
 struct Temps {
@@ -578,6 +761,135 @@ hipError_t plan_group_lists(hipStream_t st, int64_t n, int ng, const int32_t *gp
     hipLaunchKernelGGL((k_group_cols<true>), dim3(blocks(ng, 1, 1 << 20)), dim3(kBlock), words * 6 + 4, st, ng, words,
                        gp, R.rrp, R.col0, R.len, rp, ci, (uint32_t *)nullptr, gcp, gcol, slot);
     return hipGetLastError();
+}
+
+// Blocks pay where a pair serves at least 4.5 (row, node) segments: a pair costs
+// its nodes' rows and its products whatever its rows hold.  Both products of 32
+// right-hand sides at 3 and 5 periods a path: 1,690 and 1,870 us, over runs and
+// entries 1,290 and 2,000; of 8: 332 and 351 us against 349 and 526.  And where the
+// tiles hold at most two values per entry: past that they are more to read than
+// the entries with their columns.
+constexpr int64_t kMinSegmentsPer2Pairs = 9, kMaxTileFill = 2;
+
+hipError_t plan_row_blocks(hipStream_t st, Allocator &al, int64_t m, int64_t n, int nz, const int64_t *rp,
+                           const int32_t *ci, const double *va, RowBlocks &B,
+                           const std::function<void *(size_t)> &keep)
+{
+    B = RowBlocks{};
+    const int64_t nn = n / nz;
+    if (m < 1 || nz > 32 || nn > kPlanMaxNodes) return hipSuccess;
+    Temps tm(st, al);
+    uint32_t *cnt = tm.get<uint32_t>(m + 1);
+    int64_t *srp = tm.get<int64_t>(m + 1);
+    uint8_t *cut = tm.get<uint8_t>(m);
+    PL_OK(tm);
+    const int gr = blocks(m, kBlock / 64, 16384);
+    hipLaunchKernelGGL((k_segments<false>), dim3(gr), dim3(kBlock), 0, st, m, nz, rp, ci, cnt,
+                       (const int64_t *)nullptr, (uint32_t *)nullptr, (uint32_t *)nullptr, (uint32_t *)nullptr);
+    PL_TRY(scan_exclusive(tm, cnt, srp, (int64_t)0, m + 1));
+    int64_t ends[2] = {0, 0};                              // segments, entries
+    PL_TRY(hipMemcpyAsync(&ends[0], srp + m, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    PL_TRY(hipMemcpyAsync(&ends[1], rp + m, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    PL_TRY(hipStreamSynchronize(st));
+    const int64_t ns = ends[0];
+    if (ns == 0) return hipSuccess;
+    uint32_t *node = tm.get<uint32_t>(ns), *row_of = tm.get<uint32_t>(ns), *pos = tm.get<uint32_t>(ns);
+    uint32_t *slot = tm.get<uint32_t>(ns);
+    PL_OK(tm);
+    hipLaunchKernelGGL((k_segments<true>), dim3(gr), dim3(kBlock), 0, st, m, nz, rp, ci, (uint32_t *)nullptr, srp,
+                       node, row_of, pos);
+    hipLaunchKernelGGL(k_row_cuts, dim3(gr), dim3(kBlock), 0, st, m, srp, node, cut);
+    // blocks: the rows between two cuts in equal parts, of at most 20 where most
+    // rows lie in runs of 17 to 20 (one block instead of two), else of at most 16
+    // (the kernels of one row tile).  32 right-hand sides, 19 rows a path, both
+    // products: 2.95 ms with 20, 3.62 with 16; 8, 13 rows a path: 494 and 471 us.
+    std::vector<uint8_t> hc((size_t)m);
+    PL_TRY(hipMemcpyAsync(hc.data(), cut, (size_t)m, hipMemcpyDeviceToHost, st));
+    PL_TRY(hipStreamSynchronize(st));
+    std::vector<int32_t> r0;
+    int rows_max = 0;
+    int64_t between = 0;
+    for (int64_t i = 0, e = 0; i < m; i = e) {
+        for (e = i + 1; e < m && !hc[(size_t)e];) ++e;
+        if (e - i > 16 && e - i <= kBlockRows) between += e - i;
+    }
+    const int64_t limit = 2 * between > m ? kBlockRows : 16;
+    for (int64_t i = 0; i < m;) {
+        int64_t e = i + 1;
+        while (e < m && !hc[(size_t)e]) ++e;
+        const int64_t parts = (e - i + limit - 1) / limit;
+        for (int64_t k = 0; k < parts; ++k) r0.push_back((int32_t)(i + (e - i) * k / parts));
+        rows_max = std::max(rows_max, (int)((e - i + parts - 1) / parts));
+        i = e;
+    }
+    const int nb = (int)r0.size();
+    r0.push_back((int32_t)m);
+    int32_t *row0 = tm.get<int32_t>(nb + 1);
+    uint32_t *ucnt = tm.get<uint32_t>(nb + 1);
+    uint32_t *pptr = tm.get<uint32_t>(nb + 1);
+    PL_OK(tm);
+    PL_TRY(hipMemcpyAsync(row0, r0.data(), (nb + 1) * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    const int nw = (int)((nn + 31) / 32);
+    const int gb = blocks(nb, 1, 1 << 20);
+    hipLaunchKernelGGL((k_blocks<false>), dim3(gb), dim3(kBlock), nw * 8, st, nb, nw, row0, srp, node, ucnt,
+                       (const uint32_t *)nullptr, (uint32_t *)nullptr, (uint32_t *)nullptr, (uint32_t *)nullptr);
+    PL_TRY(scan_exclusive(tm, ucnt, pptr, (uint32_t)0, (int64_t)nb + 1));
+    uint32_t hp = 0;
+    PL_TRY(hipMemcpyAsync(&hp, pptr + nb, sizeof(hp), hipMemcpyDeviceToHost, st));
+    PL_TRY(hipStreamSynchronize(st));
+    const int64_t np = hp;
+    if (2 * ns < kMinSegmentsPer2Pairs * np) return hipSuccess;
+    uint32_t *pnode = tm.get<uint32_t>(np), *pblk = tm.get<uint32_t>(np), *lo = tm.get<uint32_t>(np);
+    uint32_t *hi = tm.get<uint32_t>(np * kQuads), *size = tm.get<uint32_t>(np + 1);
+    int64_t *off = tm.get<int64_t>(np + 1);
+    PL_OK(tm);
+    PL_TRY(hipMemsetAsync(lo, 0x7f, np * sizeof(uint32_t), st));
+    PL_TRY(hipMemsetAsync(hi, 0, np * kQuads * sizeof(uint32_t), st));
+    hipLaunchKernelGGL((k_blocks<true>), dim3(gb), dim3(kBlock), nw * 8, st, nb, nw, row0, srp, node,
+                       (uint32_t *)nullptr, pptr, pnode, pblk, slot);
+    const int gp = blocks(np, 256, 16384);
+    hipLaunchKernelGGL(k_windows, dim3(blocks(ns, 256, 16384)), dim3(256), 0, st, ns, nz, rp, ci, row_of, pos, slot, pblk,
+                       row0, lo, hi);
+    hipLaunchKernelGGL(k_tile_size, dim3(gp), dim3(256), 0, st, np, lo, hi, size);
+    PL_TRY(scan_exclusive(tm, size, off, (int64_t)0, np + 1));
+    int64_t units = 0;
+    PL_TRY(hipMemcpyAsync(&units, off + np, sizeof(units), hipMemcpyDeviceToHost, st));
+    PL_TRY(hipStreamSynchronize(st));
+    if (units >= ((int64_t)1 << 32) || 4 * units > kMaxTileFill * ends[1] + 4 * np) return hipSuccess;
+    const size_t vbytes = (size_t)units * 16;
+    B.row0 = (int32_t *)keep((nb + 1) * sizeof(int32_t));
+    B.pptr = (uint32_t *)keep((nb + 1) * sizeof(uint32_t));
+    B.pair = (uint4 *)keep(np * sizeof(uint4));
+    B.val = (float *)keep(vbytes);
+    B.nptr = (int64_t *)keep((nn + 1) * sizeof(int64_t));
+    B.nlist = (uint4 *)keep(np * sizeof(uint4));
+    B.norder = (int32_t *)keep(nn * sizeof(int32_t));
+    uint32_t *k0 = tm.get<uint32_t>(np), *k1 = tm.get<uint32_t>(np);
+    uint32_t *i0 = tm.get<uint32_t>(np), *i1 = tm.get<uint32_t>(np);
+    uint32_t *ok0 = tm.get<uint32_t>(nn), *ok1 = tm.get<uint32_t>(nn), *on0 = tm.get<uint32_t>(nn);
+    PL_OK(tm);
+    if (!B.row0 || !B.pptr || !B.pair || !B.val || !B.nptr || !B.nlist || !B.norder) return hipErrorOutOfMemory;
+    PL_TRY(hipMemcpyAsync(B.row0, row0, (nb + 1) * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
+    PL_TRY(hipMemcpyAsync(B.pptr, pptr, (nb + 1) * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
+    PL_TRY(hipMemsetAsync(B.val, 0, vbytes, st));
+    hipLaunchKernelGGL(k_pairs, dim3(gp), dim3(256), 0, st, np, pnode, lo, hi, size, off, B.pair, k0, i0);
+    hipLaunchKernelGGL(k_tile_values, dim3(blocks(ns, 16, 65536)), dim3(256), 0, st, ns, nz, rp, ci, va, row_of, pos,
+                       slot, pblk, row0, B.pair, B.val);
+    rocprim::double_buffer<uint32_t> keys(k0, k1), idx(i0, i1);
+    PL_TRY(sort_pairs(tm, keys, idx, np, bits_for(nn)));
+    launch_key_ptr(st, np, nn, keys.current(), B.nptr);
+    hipLaunchKernelGGL(k_node_pairs, dim3(gp), dim3(256), 0, st, np, idx.current(), pblk, B.pair, row0, B.nlist);
+    hipLaunchKernelGGL(k_order_keys, dim3(blocks(nn, 256, 1024)), dim3(256), 0, st, nn, B.nptr, ok0, on0);
+    rocprim::double_buffer<uint32_t> okey(ok0, ok1), onode(on0, (uint32_t *)B.norder);
+    PL_TRY(sort_pairs(tm, okey, onode, nn, 32));
+    if (onode.current() != (uint32_t *)B.norder)
+        PL_TRY(hipMemcpyAsync(B.norder, onode.current(), nn * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
+    PL_TRY(hipGetLastError());
+    PL_TRY(hipStreamSynchronize(st));
+    B.nb = nb;
+    B.rows_max = rows_max;
+    B.np = np;
+    return hipSuccess;
 }
 
 }  // namespace lsqr
