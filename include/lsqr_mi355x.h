@@ -558,8 +558,8 @@ lsqr_status lsqr_mlp_scale(lsqr_ctx *ctx, const float *params, const float *mean
  * (code under stream capture, tight serving loops, harnesses that forbid
  * allocation): the same operation, arguments and result as lsqr_mlp_scale
  * (the same kernels, so d is bitwise the same), with its temporary (the
- * Jacobi scale and the feature means, n + 6 doubles) in a static device
- * array of LSQR_NOALLOC_MAX_COLS + 6 doubles (8 MiB) that the library holds
+ * Jacobi scale and the feature sums, n + 384 doubles) in a static device
+ * array of LSQR_NOALLOC_MAX_COLS + 384 doubles (8 MiB) that the library holds
  * on each device it runs on until the process ends, instead of an
  * allocation.  It calls no device allocator.
  * Errors: LSQR_E_INVALID_ARG as lsqr_mlp_scale, and when ctx's system has

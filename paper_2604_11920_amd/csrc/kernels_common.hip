@@ -283,7 +283,16 @@ __global__ __launch_bounds__(kBlock) void k_jacobi(int n, int nx, int ny, int nz
     for (int j = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); j < n;
          j += gridDim.x * (kBlock / 64)) {
         double acc = 0.0;
-        for (int64_t p = cp[j] + lane; p < cp[j + 1]; p += 64) acc += cv[p] * cv[p];
+        // four loads a lane in flight, sums in the order of the entries
+        const int64_t end = cp[j + 1];
+        for (int64_t p = cp[j] + lane; p < end; p += 256) {
+            double v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = __builtin_nontemporal_load(cv + min(p + 64 * u, end - 1));
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (p + 64 * u < end) acc += v[u] * v[u];
+        }
         acc = group_sum<64>(acc);
         if (lane == 0) {
             const int iz = j % nz, ixy = j / nz, ix = ixy % nx, iy = ixy / nx;
