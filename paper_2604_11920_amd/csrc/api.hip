@@ -343,7 +343,10 @@ lsqr_status read_state(lsqr_ctx *c, Engine &E, int iters, std::vector<double> &h
 {
     hipStream_t st = c->st;
     HIP_TRY(c, hipMemcpyAsync(c->hctl, E.ctl, C_WORDS * sizeof(int), hipMemcpyDeviceToHost, st));
-    hs.resize((size_t)(iters + 1) * kStateWords);
+    HIP_TRY(c, hipStreamSynchronize(st));
+    // the rows of the iterations that ran: with a limit of 20,000 iterations all
+    // rows are 5 MB, a fifth of a small solve's time
+    hs.resize((size_t)(std::min(std::max(c->hctl[C_ITERS], 0), iters) + 1) * kStateWords);
     HIP_TRY(c, hipMemcpyAsync(hs.data(), E.S, hs.size() * sizeof(double), hipMemcpyDeviceToHost, st));
     HIP_TRY(c, hipStreamSynchronize(st));
     if (c->hctl[C_ERR]) return fail(c, LSQR_E_NONFINITE, "a solver scalar became non-finite");
