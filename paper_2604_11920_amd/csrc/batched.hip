@@ -250,22 +250,7 @@ void batch_iter(lsqr_ctx *c, hipStream_t st, int p, double tol)
 
 __global__ void k_set_kmax(int *ctl, int kmax) { ctl[C_KMAX] = kmax; }
 
-// Column r of a row-major [rows][R] FP64 block: read into v, write from v
-// (v == nullptr: zeros), or add the whole block src to dst.
-__global__ void k_col_get(int64_t rows, int R, int r, const double *blk, double *v)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < rows;
-         i += (int64_t)gridDim.x * blockDim.x)
-        v[i] = blk[i * R + r];
-}
-
-__global__ void k_col_put(int64_t rows, int R, int r, const double *v, double *blk)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < rows;
-         i += (int64_t)gridDim.x * blockDim.x)
-        blk[i * R + r] = v ? v[i] : 0.0;
-}
-
+// dst += src.
 __global__ void k_blk_add(int64_t count, const double *src, double *dst)
 {
 #pragma clang fp contract(off)
@@ -465,16 +450,12 @@ lsqr_status batch_state(lsqr_ctx *c0, lsqr_ctx *c, int nrhs, int &err, std::vect
 // FP64 refinement scratch of a context (allocated on first use).
 lsqr_status ensure_refine_buffers(lsqr_ctx *c)
 {
-    const int64_t m = c->P.m, n = c->P.n, mb = m + 2 * n;
-    if (!c->xbuf) c->xbuf = ctx_alloc<double>(c, n);
-    if (!c->rbar) c->rbar = ctx_alloc<double>(c, mb);
-    if (!c->gbuf) c->gbuf = ctx_alloc<double>(c, n);
-    if (!c->fbuf) c->fbuf = ctx_alloc<double>(c, mb);
+    const int64_t n = c->P.n, mb = c->P.m + 2 * n;
     BatchEngine &B = c->beng;
     if (!B.X) B.X = ctx_alloc<double>(c, n * B.R);
     if (!B.F) B.F = ctx_alloc<double>(c, mb * B.R);
     if (!B.rsum) B.rsum = ctx_alloc<double>(c, (size_t)4 * B.R);
-    if (!c->xbuf || !c->rbar || !c->gbuf || !c->fbuf || !B.X || !B.F || !B.rsum)
+    if (!B.X || !B.F || !B.rsum)
         return fail(c, LSQR_E_OOM, "device allocation failed");
     return LSQR_OK;
 }
@@ -574,75 +555,50 @@ lsqr_status lsqr_solve_batched_refined(lsqr_ctx *const *ctxs, int nsys, int nrhs
     for (int s = 0; s < nsys; ++s) {
         lsqr_ctx *c = ctxs[s];
         if ((e = ensure_refine_buffers(c)) != LSQR_OK) return fail(c0, e, c->err);
-        BatchEngine &B = c->beng;
-        const Problem &P = c->P;
-        const int gadj = std::min(2048, c->eng.g_adj);
-        launch_fill(st, P.n * R, 0.0, B.X);
-        launch_fill(st, (P.m + 2 * P.n) * R, 0.0, B.F);
-        for (int r = 0; r < nrhs; ++r) {
-            if (P.m > 0)
-                hipLaunchKernelGGL(k_col_get, dim3(grid_for(P.m)), dim3(256), 0, st, P.m, R, r, B.rhs, c->dtbuf);
-            launch_adj(st, P, gadj, VT_F64, c->C64, c->ones, nullptr, c->dtbuf, nullptr, c->gbuf, c->Pa,
-                       nullptr, 0, nullptr, nullptr, 0, MODE_OPERATOR, 1);
-            launch_sum_partials(st, c->Pa, gadj, B.rsum + 4 * r);
-        }
-        HIP_TRY(c0, hipMemcpyAsync(hsum.data(), B.rsum, 4 * R * sizeof(double), hipMemcpyDeviceToHost, st));
-        HIP_TRY(c0, hipStreamSynchronize(st));
-        for (int r = 0; r < nrhs; ++r) {
-            const size_t k = (size_t)s * nrhs + r;
-            arnorm[k] = sqrt(hsum[4 * (size_t)r]);
-            if (!(arnorm[k] > 0.0)) { istop[k] = 0; live[k] = 0; eta[k] = 0.0; }
-        }
+        launch_fill(st, c->P.n * R, 0.0, c->beng.X);
     }
     for (int sw = 0;; ++sw) {
-        // FP64 residual of every live right-hand side and the next inner
-        // right-hand side f = [0; 0; (Abar^T rbar) / damp] (refine.hip)
+        // FP64 residual rbar of every right-hand side (in F) and Abar^T rbar (in dm)
         for (int s = 0; s < nsys; ++s) {
             lsqr_ctx *c = ctxs[s];
             BatchEngine &B = c->beng;
             const Problem &P = c->P;
-            const int64_t mb = P.m + 2 * P.n;
-            const int gadj = std::min(2048, c->eng.g_adj);
-            for (int r = 0; r < nrhs; ++r) {
-                const size_t k = (size_t)s * nrhs + r;
-                if (!live[k]) {
-                    hipLaunchKernelGGL(k_col_put, dim3(grid_for(mb)), dim3(256), 0, st, mb, R, r,
-                                       (const double *)nullptr, B.F);
-                    continue;
-                }
-                if (P.m > 0)
-                    hipLaunchKernelGGL(k_col_get, dim3(grid_for(P.m)), dim3(256), 0, st, P.m, R, r, B.rhs, c->dtbuf);
-                if (sw > 0) {
-                    hipLaunchKernelGGL(k_col_get, dim3(grid_for(P.n)), dim3(256), 0, st, P.n, R, r, B.X, c->xbuf);
-                    launch_fwd(st, P, c->eng.g_fwd, VT_F64, c->R64, c->xbuf, nullptr, c->ybuf, nullptr,
-                               c->Pf, nullptr, 0, nullptr, nullptr, 0, 0.0, MODE_OPERATOR);
-                }
-                launch_residual(st, P, c->g_ref, c->dtbuf, sw > 0 ? c->ybuf : nullptr, c->rbar, c->Pr);
-                launch_sum_partials(st, c->Pr, c->g_ref, B.rsum + 4 * r + 1);
-                launch_adj(st, P, gadj, VT_F64, c->C64, c->ones, nullptr, c->rbar, nullptr, c->gbuf,
-                           c->Pa, nullptr, 0, nullptr, nullptr, 0, MODE_OPERATOR, 1);
-                launch_normal_rhs(st, P, c->g_ref, c->rbar, c->gbuf, c->fbuf, c->Pr);
-                launch_sum_partials(st, c->Pr, c->g_ref, B.rsum + 4 * r + 2);
-                hipLaunchKernelGGL(k_col_put, dim3(grid_for(mb)), dim3(256), 0, st, mb, R, r,
-                                   (const double *)c->fbuf, B.F);
-            }
-            HIP_TRY(c0, hipGetLastError());
+            RefArgs a{c->rp, c->ci, c->va, P.m, (int)P.n, P.nx, P.ny, P.nz, R, P.w, P.damp,
+                      B.rhs, sw > 0 ? B.X : nullptr, B.F, B.dm, B.P1};
+            const int gf = cap(P.m + 2 * P.n, 4, 2048), ga = cap(P.n, 4, 2048);
+            hipLaunchKernelGGL(k_ref_fwd, dim3(gf), dim3(kBlock), 0, st, a);
+            hipLaunchKernelGGL(k_ref_sum, dim3(1), dim3(kBlock), 0, st, gf, R, (const double *)B.P1, B.rsum);
+            a.ptr = c->cp; a.idx = c->ri; a.val = c->cv; a.part = B.P2;
+            hipLaunchKernelGGL(k_ref_adj, dim3(ga), dim3(kBlock), 0, st, a);
+            hipLaunchKernelGGL(k_ref_sum, dim3(1), dim3(kBlock), 0, st, ga, R, (const double *)B.P2, B.rsum + 1);
+        }
+        HIP_TRY(c0, hipGetLastError());
+        for (int s = 0; s < nsys; ++s) {
+            lsqr_ctx *c = ctxs[s];
+            BatchEngine &B = c->beng;
             HIP_TRY(c0, hipMemcpyAsync(hsum.data(), B.rsum, 4 * R * sizeof(double), hipMemcpyDeviceToHost, st));
             HIP_TRY(c0, hipStreamSynchronize(st));
+            uint32_t mask = 0;
             for (int r = 0; r < nrhs; ++r) {
                 const size_t k = (size_t)s * nrhs + r;
                 if (!live[k]) continue;
-                rn[k] = sqrt(hsum[4 * (size_t)r + 1]);
-                eta[k] = sqrt(hsum[4 * (size_t)r + 2]) / arnorm[k];
+                const double an = sqrt(hsum[4 * (size_t)r + 1]);
+                if (sw == 0) {                     // rbar = bbar: |Abar^T bbar|
+                    arnorm[k] = an;
+                    if (!(an > 0.0)) { istop[k] = 0; live[k] = 0; eta[k] = 0.0; continue; }
+                }
+                rn[k] = sqrt(hsum[4 * (size_t)r]);
+                eta[k] = an / arnorm[k];
                 if (!isfinite(eta[k])) return fail(c0, LSQR_E_NONFINITE, "refinement residual became non-finite");
                 if (eta[k] <= tol) { istop[k] = 1; live[k] = 0; }
                 else if (sw >= sweeps) { istop[k] = 2; live[k] = 0; }
                 else if (sw > 0 && eta[k] > 0.5 * eta_prev[k]) { istop[k] = 4; live[k] = 0; }
-                if (!live[k])          // no further correction for it
-                    hipLaunchKernelGGL(k_col_put, dim3(grid_for(mb)), dim3(256), 0, st, mb, R, r,
-                                       (const double *)nullptr, B.F);
+                if (live[k]) mask |= 1u << r;
                 eta_prev[k] = eta[k];
             }
+            // the next inner right-hand side f = [0; 0; (Abar^T rbar) / damp] (refine.hip)
+            hipLaunchKernelGGL(k_ref_rhs, dim3(grid_for((c->P.m + 2 * c->P.n) * R)), dim3(256), 0, st,
+                               (c->P.m + c->P.n) * R, c->P.n * (int64_t)R, R, c->P.damp, mask, (const double *)B.dm, B.F);
         }
         int any = 0;
         for (size_t k = 0; k < NR; ++k) any |= live[k];

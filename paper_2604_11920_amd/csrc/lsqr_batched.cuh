@@ -1292,4 +1292,143 @@ __global__ __launch_bounds__(kBlock) void k_bfinal(BArgs a, double *dm)
         dm[idx] = a.d[idx >> (__ffs(R) - 1)] * a.Y[idx];
 }
 
+// ------------------------------------------------- FP64 refinement blocks --
+// The FP64 residual and its normal-equation image of a block of right-hand sides
+// (row-major [rows][R], R a power of two <= 32): lane r + R e of a wave takes
+// entry e, e + 64 / R, ... of its row or column for right-hand side r, four loads
+// in flight.  One right-hand side after the other took seven launches each: 224 a
+// sweep and system of 32, 3.6 -> REFB ms a sweep of 3 systems.
+struct RefArgs {
+    const int64_t *ptr;
+    const int32_t *idx;
+    const double *val;
+    int64_t m;
+    int n, nx, ny, nz, R;
+    double w, damp;
+    const double *rhs, *X;  // forward: [m][R] and x, nullptr: x = 0
+    double *F;              // residual [m+2n][R]
+    double *at;             // transposed: Abar^T F [n][R]
+    double *part;           // [grid][R] sums of squares
+};
+
+__device__ __forceinline__ double ref_dot(const RefArgs &a, int64_t i, const double *x, int lane)
+{
+#pragma clang fp contract(off)
+    constexpr int U = 4;
+    const int R = a.R, r = lane & (R - 1), step = 64 / R;
+    const int64_t end = a.ptr[i + 1];
+    double acc[U] = {};
+    for (int64_t p = a.ptr[i] + lane / R; p < end; p += U * step) {
+        double v[U], y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t q = min(p + u * step, end - 1);
+            v[u] = a.val[q];
+            y[u] = x[(int64_t)a.idx[q] * R + r];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (p + u * step < end) acc[u] += v[u] * y[u];
+    }
+    double s = tree_sum<U>(acc);
+    for (int off = R; off < 64; off <<= 1) s += __shfl_xor(s, off, 64);
+    return s;
+}
+
+// Smoothing stencil of column j, right-hand side r, of a block x.
+__device__ __forceinline__ double ref_stencil(const RefArgs &a, int64_t j, int r, const double *x)
+{
+#pragma clang fp contract(off)
+    const int R = a.R, pp = (int)j, iz = pp % a.nz, ixy = pp / a.nz, ix = ixy % a.nx, iy = ixy / a.nx;
+    const int64_t sx = (int64_t)a.nz * R, sy = sx * a.nx;
+    const double *c = x + j * R + r;
+    double acc = 0.0;
+    int deg = 0;
+    if (ix > 0) { acc += c[-sx]; ++deg; }
+    if (ix < a.nx - 1) { acc += c[sx]; ++deg; }
+    if (iy > 0) { acc += c[-sy]; ++deg; }
+    if (iy < a.ny - 1) { acc += c[sy]; ++deg; }
+    if (iz > 0) { acc += c[-R]; ++deg; }
+    if (iz < a.nz - 1) { acc += c[R]; ++deg; }
+    return acc - (double)deg * c[0];
+}
+
+// The workgroup's squares per right-hand side (thread t holds t mod R).
+__device__ __forceinline__ void ref_partials(const RefArgs &a, double sq, double *lds)
+{
+    const int R = a.R;
+    for (int off = R; off < 64; off <<= 1) sq += __shfl_xor(sq, off, 64);
+    if ((threadIdx.x & 63) < R) lds[(threadIdx.x >> 6) * R + (threadIdx.x & 63)] = sq;
+    __syncthreads();
+    if (threadIdx.x < R) {
+        const int r = threadIdx.x;
+        a.part[(int64_t)blockIdx.x * R + r] = ((lds[r] + lds[R + r]) + lds[2 * R + r]) + lds[3 * R + r];
+    }
+}
+
+// F = [rhs; 0; 0] - Abar x.
+__global__ __launch_bounds__(kBlock) void k_ref_fwd(RefArgs a)
+{
+#pragma clang fp contract(off)
+    __shared__ double lds[4 * kMaxRhs];
+    const int lane = threadIdx.x & 63, R = a.R, lg = __ffs(R) - 1;
+    double sq = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < a.m; i += (int64_t)gridDim.x * 4) {
+        const double y = a.X ? ref_dot(a, i, a.X, lane) : 0.0;
+        if (lane < R) {
+            const double t = a.rhs[i * R + lane] - y;
+            a.F[i * R + lane] = t;
+            sq += t * t;
+        }
+    }
+    const int64_t tot = 2 * (int64_t)a.n * R;
+    for (int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x; q < tot; q += (int64_t)gridDim.x * kBlock) {
+        const int64_t j = q >> lg;
+        const int r = (int)q & (R - 1);
+        double y = 0.0;
+        if (a.X) y = j < a.n ? a.w * ref_stencil(a, j, r, a.X) : a.damp * a.X[(j - a.n) * R + r];
+        const double t = 0.0 - y;
+        a.F[a.m * R + q] = t;
+        sq += t * t;
+    }
+    ref_partials(a, sq, lds);
+}
+
+// at = Abar^T F (F = [rhs; 0; 0] where x = 0: its other rows are zeros).
+__global__ __launch_bounds__(kBlock) void k_ref_adj(RefArgs a)
+{
+#pragma clang fp contract(off)
+    __shared__ double lds[4 * kMaxRhs];
+    const int lane = threadIdx.x & 63, R = a.R;
+    const double *FL = a.F + a.m * R, *FD = FL + (int64_t)a.n * R;
+    double sq = 0.0;
+    for (int j = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6); j < a.n; j += (int)gridDim.x * 4) {
+        const double g = ref_dot(a, j, a.F, lane);
+        if (lane < R) {
+            const double t = g + a.w * ref_stencil(a, j, lane, FL) + a.damp * FD[(int64_t)j * R + lane];
+            a.at[(int64_t)j * R + lane] = t;
+            sq += t * t;
+        }
+    }
+    ref_partials(a, sq, lds);
+}
+
+// out[4 r] = sum over the workgroups' partials of right-hand side r.
+__global__ __launch_bounds__(kBlock) void k_ref_sum(int np, int R, const double *part, double *out)
+{
+    __shared__ double accs[kBlock], res[kMaxRhs];
+    sum_rhs_all(part, np, R, accs, res);
+    if (threadIdx.x < R) out[4 * threadIdx.x] = res[threadIdx.x];
+}
+
+// The inner right-hand side: F = [0; 0; at / damp], zeros for right-hand sides
+// that are done (bit r of live clear).
+__global__ void k_ref_rhs(int64_t zeros, int64_t count, int R, double damp, uint32_t live, const double *at,
+                          double *F)
+{
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = t0; i < zeros; i += step) F[i] = 0.0;
+    for (int64_t i = t0; i < count; i += step) F[zeros + i] = (live >> (i & (R - 1))) & 1u ? at[i] / damp : 0.0;
+}
+
 }  // namespace lsqr
