@@ -23,6 +23,15 @@ int pow2_at_least(int x)
     return p;
 }
 
+// Row blocks, but for one right-hand side where a node has fewer than 2.5 pairs:
+// a workgroup per node has little to do (both products of 3,185 nodes and 66
+// paths of 13 periods: 23.5 us, over runs and entries 19.3; of two right-hand
+// sides 23.7 and 23.9; of one with 253 paths 27.3 and 29.0).
+bool use_row_blocks(const lsqr_ctx *c, int R)
+{
+    return c->rb.nb && (R > 1 || 2 * c->rb.np >= 5 * (c->P.n / c->P.nz));
+}
+
 BArgs base_args(lsqr_ctx *c, BatchEngine &B)
 {
     BArgs a{};
@@ -33,7 +42,8 @@ BArgs base_args(lsqr_ctx *c, BatchEngine &B)
         a.norder = c->norder; a.nval = c->nval32;
         if (B.Pr) { a.rrp = c->rrp; a.rrid = c->rrid; a.Pr = B.Pr; a.g_pr = B.g_adj; }
     }
-    a.rb = c->rb; a.va64 = c->va; a.cv64 = c->cv;
+    if (use_row_blocks(c, B.R)) a.rb = c->rb;
+    a.va64 = c->va; a.cv64 = c->cv;
     a.d = c->d;
     a.m = c->P.m; a.n = (int)c->P.n; a.nx = c->P.nx; a.ny = c->P.ny; a.nz = c->P.nz;
     a.w = c->P.w; a.damp = c->P.damp;
@@ -42,13 +52,19 @@ BArgs base_args(lsqr_ctx *c, BatchEngine &B)
     return a;
 }
 
+// Few blocks (a workgroup each, up to two to a compute unit): 8 waves share a
+// block's pairs.
+constexpr int kFewBlocks = 1024;
 // Few nodes: 8 waves share a node's pairs.
 constexpr int kBatchWideNodes = 1024;
 
 template <int RT, int KS, int MT>
 void launch_fwd_rb(hipStream_t st, int grid, const BArgs &a)
 {
-    hipLaunchKernelGGL((k_bfwd_rb<RT, KS, MT>), dim3(grid), dim3(kBlock), 0, st, a);
+    if (a.rb.nb <= kFewBlocks)
+        hipLaunchKernelGGL((k_bfwd_rb<RT, KS, MT, 8>), dim3(grid), dim3(512), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_bfwd_rb<RT, KS, MT, 4>), dim3(grid), dim3(256), 0, st, a);
 }
 
 template <int RT, int MT, int QM>
@@ -109,7 +125,7 @@ void launch_tiled(hipStream_t st, int kind, int grid, BArgs a, int R, int rt)
 
 // FP32 copies of the values (the batched kernels read FP32): in row blocks where
 // the rows share their nodes, else row-major, column-major and node-major.
-lsqr_status ensure_fp32(lsqr_ctx *c, hipStream_t st)
+lsqr_status ensure_fp32(lsqr_ctx *c, hipStream_t st, int R)
 {
     const int64_t nnz = c->P.nnz;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -132,7 +148,7 @@ lsqr_status ensure_fp32(lsqr_ctx *c, hipStream_t st)
         }
         c->rb_tried = true;
     }
-    if (c->rb.nb) return LSQR_OK;
+    if (use_row_blocks(c, R)) return LSQR_OK;
     if (!c->va32 || !c->cv32) {
         c->va32 = ctx_alloc<float>(c, nnz);
         c->cv32 = ctx_alloc<float>(c, nnz);
@@ -160,7 +176,7 @@ lsqr_status ensure_batch(lsqr_ctx *c, hipStream_t st, int R, int iters)
 {
     BatchEngine &B = c->beng;
     const int64_t m = c->P.m, n = c->P.n, mb = m + 2 * n;
-    lsqr_status s = ensure_fp32(c, st);
+    lsqr_status s = ensure_fp32(c, st, R);
     if (s != LSQR_OK) return s;
     if (B.R != R) {
         for (void *p : {(void *)B.T[0], (void *)B.T[1], (void *)B.V, (void *)B.Q, (void *)B.Z,
@@ -192,7 +208,7 @@ lsqr_status ensure_batch(lsqr_ctx *c, hipStream_t st, int R, int iters)
             !B.P1 || !B.P2 || !B.P3 || !B.act || !B.why || !B.ctl)
             return fail(c, LSQR_E_OOM, "device allocation failed");
         // per-run partial rows of the two-phase forward product (node runs)
-        if (!c->rb.nb && c->rrid && c->nval32 && c->P.nz <= kMaxNzBatched) {
+        if (!use_row_blocks(c, R) && c->rrid && c->nval32 && c->P.nz <= kMaxNzBatched) {
             B.Pr = ctx_alloc<float>(c, std::max<int64_t>(c->nnruns, 1) * R);
             if (!B.Pr) return fail(c, LSQR_E_OOM, "device allocation failed");
         }
@@ -205,8 +221,11 @@ lsqr_status ensure_batch(lsqr_ctx *c, hipStream_t st, int R, int iters)
         if (!B.S) return fail(c, LSQR_E_OOM, "state allocation failed");
     }
     B.g_fwd = cap(m * 64, kBlock, B.grid);
-    if (c->rb.nb) B.g_fwd = cap(c->rb.nb, 1, B.grid);             // a workgroup per row block
-    if (c->rb.nb || (c->nval32 && c->P.nz <= kMaxNzBatched))      // a workgroup per lateral node
+    // a workgroup per row block, and enough of them for the smoothing and damping
+    // rows (4 a thread: 60 blocks, 18,000 unknowns and 32 right-hand sides took
+    // 86 us for both products, now 37)
+    if (use_row_blocks(c, R)) B.g_fwd = cap(std::max<int64_t>(c->rb.nb, (2 * n * R + 1023) / 1024), 1, B.grid);
+    if (use_row_blocks(c, R) || (c->nval32 && c->P.nz <= kMaxNzBatched))      // a workgroup per lateral node
         B.g_adj = (int)std::max<int64_t>(1, std::min<int64_t>(n / c->P.nz, B.grid));
     else
         B.g_adj = cap(n * 64, kBlock, B.grid);

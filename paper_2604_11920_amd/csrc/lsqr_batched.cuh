@@ -15,6 +15,8 @@
 // in every grid-stride loop over (row, rhs) pairs.
 #pragma once
 
+#include <type_traits>
+
 #include "lsqr_kernels.cuh"
 
 namespace lsqr {
@@ -176,7 +178,7 @@ __global__ __launch_bounds__(kBlock) void k_binit(BArgs a)
 // Prologue of a forward step: alpha and beta of the tile's right-hand sides
 // (sal, sbe); workgroup 0 sums the update's partials for eta of the previous
 // step and the per-RHS stop rules.  False when the launch has nothing to do.
-template <int RT>
+template <int RT, int NW = kBlock / 64>
 __device__ __forceinline__ bool bfwd_prologue(const BArgs &a, double *accs, double *vns, double *sal,
                                               double *sbe)
 {
@@ -187,7 +189,7 @@ __device__ __forceinline__ bool bfwd_prologue(const BArgs &a, double *accs, doub
     if (op) {
         if (threadIdx.x < RT) { sal[threadIdx.x] = 0.0; sbe[threadIdx.x] = 1.0; }
     } else if (blockIdx.x == 0) {
-        sum_rhs_all(a.part_in, a.np_in, a.R, accs, vns);
+        sum_rhs_all<NW>(a.part_in, a.np_in, a.R, accs, vns);
     }
     if (!op && threadIdx.x < RT) {
         const int r = a.r0 + threadIdx.x;
@@ -217,7 +219,7 @@ __device__ __forceinline__ bool bfwd_prologue(const BArgs &a, double *accs, doub
 }
 
 // Smoothing and damping rows of the tile: one thread per (row, rhs).
-template <int RT>
+template <int RT, int NW = kBlock / 64>
 __device__ __forceinline__ double bfwd_reg_rows(const BArgs &a, double alpha, double beta)
 {
 #pragma clang fp contract(off)
@@ -225,8 +227,8 @@ __device__ __forceinline__ double bfwd_reg_rows(const BArgs &a, double alpha, do
     const int R = a.R, cofs = a.r0 + threadIdx.x % RT;
     double sq = 0.0;
     const int64_t nreg = 2 * (int64_t)a.n;
-    for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < nreg * RT;
-         idx += (int64_t)gridDim.x * kBlock) {
+    for (int64_t idx = (int64_t)blockIdx.x * (64 * NW) + threadIdx.x; idx < nreg * RT;
+         idx += (int64_t)gridDim.x * (64 * NW)) {
         const int64_t r = idx / RT;
         float yv;
         if (r < a.n) {
@@ -793,13 +795,14 @@ __global__ __launch_bounds__(kBlock) void k_badj_nruns(BArgs a)
 // bring no address arithmetic and no clamps: 2,140 -> 1,650 us forward.  32 right-hand sides are read as pairs (column tile q,
 // column i holds right-hand side 2 i + q).  A node's rows of Z (a block's rows of
 // T) are read once per pair instead of once per run, and there are no partial
-// rows: k_bfwd_pr32 + k_bfwd<32> wrote and read back 128 bytes per run.  Two pairs'
-// products are summed from zero in FP32 and added up in FP64.
-// 32 right-hand sides, 565 M entries: forward 4,840 -> 1,650 us, transposed 3,010
-// -> 1,300 us; 8 right-hand sides, 95 M entries: 776 -> 220 and 638 -> 240 us.  What
-// bounds them: matrix and vector units share a wave's issue (a third of the time
-// each), and three waves a SIMD cover the latency of the rest; the bytes (2.7 GB of
-// values) would take 0.4 ms.
+// rows: k_bfwd_pr32 + k_bfwd<32> wrote and read back 128 bytes per run.  The
+// pairs' products are summed from zero in FP32 and added up in FP64.
+// 32 right-hand sides, 565 M entries: forward 4,840 -> 1,420 us, transposed 3,010
+// -> 1,280 us; 8 right-hand sides, 95 M entries: 776 -> 215 and 638 -> 230 us.  What
+// bounds them with 32: values (2.7 GB) and the rows of Z or T (7.5 GB, most past
+// the 4 MB of an XCD's L2) arrive at 7.2 to 7.6 TB/s; deeper prefetch, entries
+// read earlier, contiguous blocks per XCD and neighbouring nodes per XCD gave
+// nothing, the matrix cores are busy half the time.
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 // A product that came out non-finite, again from its own entries: in a block's
 // product an infinity or NaN of the vector block also meets the zeros of rows
@@ -868,25 +871,35 @@ __device__ __forceinline__ void put_tiles(float *my, const floatx4 (&v)[LN], int
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// KS: products of four depths a tile can need.  MT: row tiles of 16.  The 4
+// Pairs summed in FP32 before they are added in FP64, and the waves' sums in LDS.
+// 32 right-hand sides: forward 1,420 us, of 2 pairs 1,480; error against 64 bits
+// 2.2e-7 and 1.4e-7, over runs and entries 9.3e-7.  Narrower blocks went over
+// entries with a sum per lane (9e-8 with one right-hand side of 253 paths), and
+// keep that: every pair and the waves' sums in FP64.
+template <int NT>
+constexpr int kPairsFp32 = NT == 2 ? 8 : 1;
+template <int NT>
+using PartSum = typename std::conditional<NT == 2, float, double>::type;
+
+// KS: products of four depths a tile can need.  MT: row tiles of 16.  The NW
 // waves of a workgroup share a block's pairs (a wave to a block: the longest path
 // decides: 2,450 against 2,140 us with 32 right-hand sides).  The tiles and
 // the rows of Z of the next pair are in flight.
-template <int RT, int KS, int MT>
-__global__ __launch_bounds__(kBlock, RT > 16 ? 3 : 4) void k_bfwd_rb(BArgs a)
+template <int RT, int KS, int MT, int NW>
+__global__ __launch_bounds__(64 * NW, RT > 16 ? 3 : 4) void k_bfwd_rb(BArgs a)
 {
 #pragma clang fp contract(off)
     constexpr int NT = RT > 16 ? 2 : 1, CT = RT > 16 ? 16 : RT, W = 16 * NT;
     constexpr int LN = (4 * KS * (MT == 2 ? kQuads : 4) + 63) / 64;
-    __shared__ double accs[kBlock];
+    __shared__ double accs[NW * kMaxRhs];
     __shared__ double res[kMaxRhs];
     __shared__ double vns[kMaxRhs];
     __shared__ double sal[kMaxRhs], sbe[kMaxRhs];
-    __shared__ floatx4 tiles[4][64 * LN + 4 * KS];        // operands not used reach past the tiles
-    __shared__ float red[4 * 16 * MT * W];
+    __shared__ floatx4 tiles[NW][64 * LN + 4 * KS];        // operands not used reach past the tiles
+    __shared__ PartSum<NT> red[NW * 16 * MT * W];
     const bool op = a.mode == MODE_OPERATOR;
     const int blk = scalar_block();
-    if (!bfwd_prologue<RT>(a, accs, vns, sal, sbe)) return;
+    if (!bfwd_prologue<RT, NW>(a, accs, vns, sal, sbe)) return;
     const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
     const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int R = a.R, nz = a.nz;
@@ -905,8 +918,8 @@ __global__ __launch_bounds__(kBlock, RT > 16 ? 3 : 4) void k_bfwd_rb(BArgs a)
     for (int b = blk; b < B.nb; b += (int)gridDim.x) {
         const int row0 = ld_uniform(B.row0, b), nrow = ld_uniform(B.row0, b + 1) - row0;
         const uint32_t p0 = ld_uniform(B.pptr, b), cnt = ld_uniform(B.pptr, b + 1) - p0;
-        uint32_t p = p0 + cnt * (uint32_t)wid / 4;
-        const uint32_t pe = p0 + cnt * (uint32_t)(wid + 1) / 4;
+        uint32_t p = p0 + cnt * (uint32_t)wid / NW;
+        const uint32_t pe = p0 + cnt * (uint32_t)(wid + 1) / NW;
         double acc[MT][NT][4] = {};
         if (p < pe) {
             floatx4 c[MT][NT] = {};
@@ -971,21 +984,21 @@ __global__ __launch_bounds__(kBlock, RT > 16 ? 3 : 4) void k_bfwd_rb(BArgs a)
                 const uint32_t *e = (const uint32_t *)(B.pair + (q < pe ? q : pe - 1));
                 return make_uint4(ld_uniform(e, 0), ld_uniform(e, 1), ld_uniform(e, 2), ld_uniform(e, 3));
             };
-            Set s0, s1;
-            load(s0, entry(p));
-            uint4 e1 = entry(p + 1);
-            for (;;) {
-                load(s1, e1);
-                e1 = entry(p + 2);
-                mul(s0);
-                if (++p >= pe) break;
-                load(s0, e1);
-                e1 = entry(p + 2);
-                mul(s1);
-                if (++p >= pe) break;
-                flush();
+            constexpr int FL = kPairsFp32<NT>;
+            Set set[2];
+            load(set[0], entry(p));
+            uint4 e = entry(p + 1);
+            for (bool more = true; more;) {
+#pragma unroll
+                for (int t = 0; t < (FL > 1 ? FL : 2); ++t) {          // an even count: the sets alternate
+                    load(set[(t + 1) & 1], e);
+                    e = entry(p + 2);
+                    mul(set[t & 1]);
+                    if (FL == 1) flush();
+                    if (++p >= pe) { more = false; break; }
+                }
+                if (FL > 1) flush();
             }
-            flush();
         }
 #pragma unroll
         for (int h = 0; h < MT; ++h)
@@ -993,12 +1006,15 @@ __global__ __launch_bounds__(kBlock, RT > 16 ? 3 : 4) void k_bfwd_rb(BArgs a)
             for (int q = 0; q < NT; ++q)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    red[(wid * 16 * MT + 16 * h + 4 * g + e) * W + NT * i + q] = (float)acc[h][q][e];
+                    red[(wid * 16 * MT + 16 * h + 4 * g + e) * W + NT * i + q] = (PartSum<NT>)acc[h][q][e];
         __syncthreads();
-        for (int e = threadIdx.x; e < nrow * RT; e += kBlock) {
+        for (int e = threadIdx.x; e < nrow * RT; e += 64 * NW) {
             const int r = e / RT, c = e % RT, o = r * W + c;
             constexpr int S = 16 * MT * W;
-            float y = ((red[o] + red[o + S]) + red[o + 2 * S]) + red[o + 3 * S];
+            double ys = (double)red[o];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) ys += (double)red[o + w * S];
+            float y = (float)ys;
             if (!isfinite(y)) y = sparse_dot(a.rp, a.ci, a.va64, row0 + r, a.Z, R, a.r0 + c);
             const int64_t at = (int64_t)(row0 + r) * R + a.r0 + c;
             const double u = op ? 0.0 : (double)a.Tprev[at] / (sbe[c] > 0.0 ? sbe[c] : 1.0);
@@ -1009,8 +1025,8 @@ __global__ __launch_bounds__(kBlock, RT > 16 ? 3 : 4) void k_bfwd_rb(BArgs a)
         __syncthreads();
     }
     const int rr = threadIdx.x % RT;
-    sq += bfwd_reg_rows<RT>(a, sal[rr], sbe[rr] > 0.0 ? sbe[rr] : 1.0);
-    block_sum_rhs<RT>(sq, accs, res);
+    sq += bfwd_reg_rows<RT, NW>(a, sal[rr], sbe[rr] > 0.0 ? sbe[rr] : 1.0);
+    block_sum_rhs<RT, NW>(sq, accs, res);
     if (threadIdx.x < RT) a.part_out[(int64_t)blockIdx.x * R + a.r0 + threadIdx.x] = res[threadIdx.x];
 }
 
@@ -1027,7 +1043,7 @@ __global__ __launch_bounds__(64 * NW, RT > 16 ? 3 : 4) void k_badj_rb(BArgs a)
     __shared__ double res[kMaxRhs];
     __shared__ double b2[kMaxRhs];
     __shared__ floatx4 tiles[NW][64 * LN + 16 * MT];      // operands not used reach past the tiles
-    __shared__ float red[NW * 16 * MT * W];
+    __shared__ PartSum<NT> red[NW * 16 * MT * W];
     const bool op = a.mode == MODE_OPERATOR;
     const int blk = scalar_block();
     int k = 0;
@@ -1121,21 +1137,21 @@ __global__ __launch_bounds__(64 * NW, RT > 16 ? 3 : 4) void k_badj_rb(BArgs a)
                         c[h][q] = floatx4{0.f, 0.f, 0.f, 0.f};
                     }
             };
-            Set s0, s1;
-            load(s0, entry(p));
-            uint4 e1 = entry(p + 1);
-            for (;;) {
-                load(s1, e1);
-                e1 = entry(p + 2);
-                mul(s0);
-                if (++p >= pe) break;
-                load(s0, e1);
-                e1 = entry(p + 2);
-                mul(s1);
-                if (++p >= pe) break;
-                flush();
+            constexpr int FL = kPairsFp32<NT>;
+            Set set[2];
+            load(set[0], entry(p));
+            uint4 e = entry(p + 1);
+            for (bool more = true; more;) {
+#pragma unroll
+                for (int t = 0; t < (FL > 1 ? FL : 2); ++t) {          // an even count: the sets alternate
+                    load(set[(t + 1) & 1], e);
+                    e = entry(p + 2);
+                    mul(set[t & 1]);
+                    if (FL == 1) flush();
+                    if (++p >= pe) { more = false; break; }
+                }
+                if (FL > 1) flush();
             }
-            flush();
         }
 #pragma unroll
         for (int h = 0; h < MT; ++h)
@@ -1143,13 +1159,14 @@ __global__ __launch_bounds__(64 * NW, RT > 16 ? 3 : 4) void k_badj_rb(BArgs a)
             for (int q = 0; q < NT; ++q)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    red[(wid * 16 * MT + 16 * h + 4 * g + e) * W + NT * i + q] = (float)acc[h][q][e];
+                    red[(wid * 16 * MT + 16 * h + 4 * g + e) * W + NT * i + q] = (PartSum<NT>)acc[h][q][e];
         __syncthreads();
         for (int cell = threadIdx.x; cell < nz * RT; cell += 64 * NW) {
             const int cz = cell / RT, cr = cell % RT;
-            float y = red[cz * W + cr];
+            double ys = (double)red[cz * W + cr];
 #pragma unroll
-            for (int w = 1; w < NW; ++w) y += red[(w * 16 * MT + cz) * W + cr];
+            for (int w = 1; w < NW; ++w) ys += (double)red[(w * 16 * MT + cz) * W + cr];
+            float y = (float)ys;
             const int c = a.r0 + cr;
             if (!isfinite(y)) y = sparse_dot(a.cp, a.ri, a.cv64, (int64_t)node * nz + cz, a.Tcur, R, c);
             const double bc = sqrt(b2[c]);
