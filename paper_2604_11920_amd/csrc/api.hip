@@ -29,6 +29,31 @@ lsqr_status fail(lsqr_ctx *c, lsqr_status s, const std::string &msg)
     return s;
 }
 
+lsqr_status ensure_values32(lsqr_ctx *c, hipStream_t st, bool runs)
+{
+    const int64_t nnz = c->P.nnz;
+    runs = runs && c->nval;
+    if (c->va32_made && (c->nval32_made || !runs)) return LSQR_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(c, hipStreamIsCapturing(st, &cap));
+    const bool eager = cap == hipStreamCaptureStatusNone;
+    // true when dst holds, or may hold, a copy that is not made yet
+    auto room = [&](float *&dst, int64_t count, bool made) {
+        const bool fresh = !dst;
+        if (fresh) dst = ctx_alloc<float>(c, count);
+        return dst && (fresh || (eager && !made));
+    };
+    const bool a = room(c->va32, nnz + 8, c->va32_made), b = room(c->cv32, nnz, c->va32_made);
+    const bool r = runs && room(c->nval32, nnz, c->nval32_made);
+    if (a) launch_convert_f32(st, nnz + 8, c->va, c->va32);
+    if (b) launch_convert_f32(st, nnz, c->cv, c->cv32);
+    if (r) launch_convert_f32(st, nnz, c->nval, c->nval32);
+    if (!c->va32 || !c->cv32 || (runs && !c->nval32)) return fail(c, LSQR_E_OOM, "device allocation failed");
+    c->va32_made |= eager;
+    c->nval32_made |= eager && runs;
+    return LSQR_OK;
+}
+
 }  // namespace lsqr
 
 namespace {
@@ -740,17 +765,11 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
     }
     int vec = VT_F64;
     if (o.precision == LSQR_FP32) {
-        c->va32 = ctx_alloc<float>(c, nnz + 8);     // with va's padding elements
-        c->cv32 = ctx_alloc<float>(c, nnz);
-        if (!c->va32 || !c->cv32) return bail(LSQR_E_OOM, "device allocation failed");
-        launch_convert_f32(st, nnz + 8, c->va, c->va32);
-        launch_convert_f32(st, nnz, c->cv, c->cv32);
+        lsqr_status q32 = ensure_values32(c, st, use_nruns);
+        if (q32 != LSQR_OK) { const std::string msg = c->err; return bail(q32, msg); }
         F.vt = VT_F32; F.val = c->va32;
         C.vt = VT_F32; C.val = c->cv32;
         if (use_nruns) {
-            c->nval32 = ctx_alloc<float>(c, nnz);
-            if (!c->nval32) return bail(LSQR_E_OOM, "device allocation failed");
-            launch_convert_f32(st, nnz, c->nval, c->nval32);
             C.val = c->nval32;
             if (c->nvalp && kF32FourDepths) {   // four depths to a word (one 16-byte load)
                 lsqr_status q4 = wide_layout(4, c->va32, 4, (void **)&c->nvalp4f);
@@ -865,12 +884,8 @@ static lsqr_status solve_mixed(lsqr_ctx *c, const double *ddt, const double *dx0
 static lsqr_status ensure_fp32_engine(lsqr_ctx *c)
 {
     if (c->have_eng32) return LSQR_OK;
-    const int64_t nnz = c->P.nnz;
-    if (!c->va32) c->va32 = ctx_alloc<float>(c, nnz + 8);   // with va's padding elements
-    if (!c->cv32) c->cv32 = ctx_alloc<float>(c, nnz);
-    if (!c->va32 || !c->cv32) return fail(c, LSQR_E_OOM, "device allocation failed");
-    launch_convert_f32(c->st, nnz + 8, c->va, c->va32);
-    launch_convert_f32(c->st, nnz, c->cv, c->cv32);
+    lsqr_status s = ensure_values32(c, c->st, false);
+    if (s != LSQR_OK) return s;
     RowFmt R = c->R64;
     R.vt = VT_F32;
     R.val = c->va32;

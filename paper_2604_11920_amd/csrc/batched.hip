@@ -149,18 +149,8 @@ lsqr_status ensure_fp32(lsqr_ctx *c, hipStream_t st, int R)
         c->rb_tried = true;
     }
     if (use_row_blocks(c, R)) return LSQR_OK;
-    if (!c->va32 || !c->cv32) {
-        c->va32 = ctx_alloc<float>(c, nnz);
-        c->cv32 = ctx_alloc<float>(c, nnz);
-        if (!c->va32 || !c->cv32) return fail(c, LSQR_E_OOM, "device allocation failed");
-        launch_convert_f32(st, nnz, c->va, c->va32);
-        launch_convert_f32(st, nnz, c->cv, c->cv32);
-    }
-    if (c->nval && !c->nval32) {     // node-run values for the transposed block product
-        c->nval32 = ctx_alloc<float>(c, nnz);
-        if (!c->nval32) return fail(c, LSQR_E_OOM, "device allocation failed");
-        launch_convert_f32(st, nnz, c->nval, c->nval32);
-    }
+    const lsqr_status s = ensure_values32(c, st, true);       // nval32: the transposed block product
+    if (s != LSQR_OK) return s;
     HIP_TRY(c, hipGetLastError());
     return LSQR_OK;
 }

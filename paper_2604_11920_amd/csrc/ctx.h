@@ -109,6 +109,7 @@ struct lsqr_ctx {
     lsqr::ColFmt C64;
     // reduced-precision copies
     float *va32 = nullptr, *cv32 = nullptr;
+    bool va32_made = false, nval32_made = false;   // converted (not only recorded by a capture)
     float *sigma = nullptr;
     uint16_t *qrow = nullptr, *qcol = nullptr;
     lsqr::Engine eng;               // the solver's kernel set
@@ -182,3 +183,9 @@ inline void ctx_release(lsqr_ctx *c, void *p)
 }
 
 }  // namespace lsqr
+// The FP32 copies va32 (with va's 8 padding elements: the kernels read entries
+// up to eight at a time), cv32 and, with runs set, nval32, made on first use: the
+// only place that makes them, whichever path asks first.  A conversion that a
+// stream capture only records is made again by the next call outside it.
+lsqr_status ensure_values32(lsqr_ctx *c, hipStream_t st, bool runs);
+
