@@ -227,6 +227,7 @@ lsqr_status ensure_state(lsqr_ctx *c, Engine &E, int iters)
     const int64_t need = (int64_t)iters + 2;
     if (E.s_rows >= need) return LSQR_OK;
     if (E.S) ctx_release(c, E.S);
+    E.s_rows = 0;
     const int64_t rows = std::max<int64_t>(need, 512);
     E.S = ctx_alloc<double>(c, (size_t)rows * kStateWords);
     if (!E.S) return fail(c, LSQR_E_OOM, "state allocation failed");

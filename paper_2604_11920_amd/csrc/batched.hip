@@ -161,21 +161,33 @@ int cap(int64_t work, int per, int lim)
     return (int)std::max<int64_t>(1, std::min<int64_t>(b, lim));
 }
 
-// Buffers for R right-hand sides and `iters` iterations.
+// Gives back the batch buffers.
+void release_batch(lsqr_ctx *c)
+{
+    BatchEngine &B = c->beng;
+    for (void *p : {(void *)B.T[0], (void *)B.T[1], (void *)B.V, (void *)B.Q, (void *)B.Z,
+                    (void *)B.W, (void *)B.Y, (void *)B.rhs, (void *)B.dm, (void *)B.P1,
+                    (void *)B.P2, (void *)B.P3, (void *)B.S, (void *)B.act, (void *)B.why, (void *)B.ctl,
+                    (void *)B.Pr, (void *)B.X, (void *)B.F, (void *)B.rsum})
+        if (p) ctx_release(c, p);
+    B = BatchEngine{};
+}
+
+// Buffers for R right-hand sides and `iters` iterations; all or none.
 lsqr_status ensure_batch(lsqr_ctx *c, hipStream_t st, int R, int iters)
 {
     BatchEngine &B = c->beng;
     const int64_t m = c->P.m, n = c->P.n, mb = m + 2 * n;
     lsqr_status s = ensure_fp32(c, st, R);
     if (s != LSQR_OK) return s;
+    const int keep_rt = B.tuned || B.R == R ? B.rt : 0, keep_grid = B.tuned || B.R == R ? B.grid : 0;
+    auto refuse = [&]() {             // nothing half made; the schedule stays for the next call
+        release_batch(c);
+        if (keep_rt) { B.rt = keep_rt; B.grid = keep_grid; B.tuned = 1; }
+        return fail(c, LSQR_E_OOM, "device allocation failed");
+    };
     if (B.R != R) {
-        for (void *p : {(void *)B.T[0], (void *)B.T[1], (void *)B.V, (void *)B.Q, (void *)B.Z,
-                        (void *)B.W, (void *)B.Y, (void *)B.rhs, (void *)B.dm, (void *)B.P1,
-                        (void *)B.P2, (void *)B.P3, (void *)B.act, (void *)B.why, (void *)B.ctl,
-                        (void *)B.Pr, (void *)B.X, (void *)B.F, (void *)B.rsum})
-            if (p) ctx_release(c, p);
-        const int keep_rt = B.tuned ? B.rt : 0, keep_grid = B.tuned ? B.grid : 0;
-        B = BatchEngine{};
+        release_batch(c);
         B.R = R;
         B.rt = keep_rt && keep_rt <= R ? keep_rt : std::min(R, 32);
         B.grid = keep_grid ? keep_grid : 2048;
@@ -196,19 +208,21 @@ lsqr_status ensure_batch(lsqr_ctx *c, hipStream_t st, int R, int iters)
         B.ctl = ctx_alloc<int>(c, C_WORDS);
         if (!B.T[0] || !B.T[1] || !B.V || !B.Q || !B.Z || !B.W || !B.Y || !B.rhs || !B.dm ||
             !B.P1 || !B.P2 || !B.P3 || !B.act || !B.why || !B.ctl)
-            return fail(c, LSQR_E_OOM, "device allocation failed");
+            return refuse();
         // per-run partial rows of the two-phase forward product (node runs)
         if (!use_row_blocks(c, R) && c->rrid && c->nval32 && c->P.nz <= kMaxNzBatched) {
             B.Pr = ctx_alloc<float>(c, std::max<int64_t>(c->nnruns, 1) * R);
-            if (!B.Pr) return fail(c, LSQR_E_OOM, "device allocation failed");
+            if (!B.Pr) return refuse();
         }
     }
     const int64_t need = (int64_t)iters + 2;
     if (B.s_rows < need) {
         if (B.S) ctx_release(c, B.S);
-        B.s_rows = std::max<int64_t>(need, 512);
-        B.S = ctx_alloc<double>(c, (size_t)B.s_rows * R * kStateWords);
-        if (!B.S) return fail(c, LSQR_E_OOM, "state allocation failed");
+        B.s_rows = 0;
+        const int64_t rows = std::max<int64_t>(need, 512);
+        B.S = ctx_alloc<double>(c, (size_t)rows * R * kStateWords);
+        if (!B.S) return refuse();
+        B.s_rows = rows;
     }
     B.g_fwd = cap(m * 64, kBlock, B.grid);
     // a workgroup per row block, and enough of them for the smoothing and damping
