@@ -157,7 +157,7 @@ lsqr_status setup_engine(lsqr_ctx *c, Engine &E, int vec, const RowFmt &R, const
         // contiguous group ranges balanced in entries
         E.g_fwd = gl;
         E.wrow = ctx_alloc<int32_t>(c, (int64_t)gl + 1);
-        if (!E.wrow) return fail(c, LSQR_E_OOM, "device allocation failed");
+        if (!E.wrow) return fail(nullptr, LSQR_E_OOM, "device allocation failed");
         launch_group_parts(c->st, R.rp, R.gp, R.ngroups, gl, E.wrow);
         E.R.wrow = E.wrow;
         E.R.wgrid = gl;
@@ -165,7 +165,7 @@ lsqr_status setup_engine(lsqr_ctx *c, Engine &E, int vec, const RowFmt &R, const
         E.g_fwd = gp;
         const int parts = fwd_pipe_parts(gp);
         E.wrow = ctx_alloc<int32_t>(c, (int64_t)parts + 1);
-        if (!E.wrow) return fail(c, LSQR_E_OOM, "device allocation failed");
+        if (!E.wrow) return fail(nullptr, LSQR_E_OOM, "device allocation failed");
         launch_wave_rows(c->st, R.rp, m, parts, E.wrow);
         E.R.wrow = E.wrow;
         E.R.wgrid = gp;
@@ -191,7 +191,7 @@ lsqr_status setup_engine(lsqr_ctx *c, Engine &E, int vec, const RowFmt &R, const
     E.y = ctx_alloc<double>(c, n);
     if (c->method == 1) {
         E.hbar = ctx_alloc<double>(c, n);
-        if (!E.hbar) return fail(c, LSQR_E_OOM, "device allocation failed");
+        if (!E.hbar) return fail(nullptr, LSQR_E_OOM, "device allocation failed");
     }
     E.P1 = ctx_alloc<double>(c, std::max(E.g_fwd, 1024));
     E.P2 = ctx_alloc<double>(c, E.g_adj);
@@ -212,7 +212,7 @@ lsqr_status setup_engine(lsqr_ctx *c, Engine &E, int vec, const RowFmt &R, const
                                                (n + E.t_small - 1) / E.t_small);
             E.cur = ctx_alloc<double>(c, 2 * kStateWords);
             E.srow = ctx_alloc<int32_t>(c, E.g_small + 1);
-            if (!E.cur || !E.srow) return fail(c, LSQR_E_OOM, "device allocation failed");
+            if (!E.cur || !E.srow) return fail(nullptr, LSQR_E_OOM, "device allocation failed");
             launch_wave_rows(c->st, R.rp, m, E.g_small, E.srow);
         }
     }
@@ -513,7 +513,7 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
 #define CR_TRY(expr)                                                                        \
     do {                                                                                    \
         hipError_t _e = (expr);                                                             \
-        if (_e != hipSuccess) return bail(LSQR_E_DEVICE, std::string(#expr) + ": " + hipGetErrorString(_e)); \
+        if (_e != hipSuccess) return bail(hip_status(_e), std::string(#expr) + ": " + hipGetErrorString(_e)); \
     } while (0)
 
     c->rp = ctx_alloc<int64_t>(c, m + 1);
@@ -665,8 +665,7 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
         hipError_t e = build_transpose(st, c->al, m, n, nnz, c->rp, c->ci, c->va, c->cp, c->ri,
                                        c->cv, terr);
         if (e != hipSuccess)
-            return bail(e == hipErrorOutOfMemory ? LSQR_E_OOM : LSQR_E_DEVICE,
-                        terr + ": " + hipGetErrorString(e));
+            return bail(hip_status(e), terr + ": " + hipGetErrorString(e));
     }
     if (groups_fit && !device_groups) {   // grids past the device planner's: grouped on the host
         std::vector<int64_t> hrp;
@@ -893,7 +892,7 @@ static lsqr_status ensure_fp32_engine(lsqr_ctx *c)
     ColFmt C = c->C64;
     C.vt = VT_F32;
     C.val = c->cv32;
-    lsqr_status s = setup_engine(c, c->eng32, VT_F32, R, C);
+    s = setup_engine(c, c->eng32, VT_F32, R, C);
     if (s != LSQR_OK) return fail(c, s, g_err);
     HIP_TRY(c, hipGetLastError());
     c->have_eng32 = true;

@@ -138,11 +138,15 @@ namespace lsqr {
 
 lsqr_status fail(lsqr_ctx *c, lsqr_status s, const std::string &msg);
 
+// The status of a HIP error: the planning and set-up functions return
+// hipErrorOutOfMemory when an allocator refuses.
+inline lsqr_status hip_status(hipError_t e) { return e == hipErrorOutOfMemory ? LSQR_E_OOM : LSQR_E_DEVICE; }
+
 #define HIP_TRY(ctx, expr)                                                                  \
     do {                                                                                    \
         hipError_t _e = (expr);                                                             \
         if (_e != hipSuccess)                                                               \
-            return lsqr::fail(ctx, LSQR_E_DEVICE, std::string(#expr) + ": " + hipGetErrorString(_e)); \
+            return lsqr::fail(ctx, lsqr::hip_status(_e), std::string(#expr) + ": " + hipGetErrorString(_e)); \
     } while (0)
 
 struct DeviceGuard {
@@ -182,10 +186,10 @@ inline void ctx_release(lsqr_ctx *c, void *p)
         }
 }
 
-}  // namespace lsqr
 // The FP32 copies va32 (with va's 8 padding elements: the kernels read entries
 // up to eight at a time), cv32 and, with runs set, nval32, made on first use: the
 // only place that makes them, whichever path asks first.  A conversion that a
 // stream capture only records is made again by the next call outside it.
 lsqr_status ensure_values32(lsqr_ctx *c, hipStream_t st, bool runs);
 
+}  // namespace lsqr

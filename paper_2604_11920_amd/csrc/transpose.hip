@@ -15,9 +15,12 @@ namespace lsqr {
 void *Allocator::get(size_t bytes)
 {
     if (bytes == 0) bytes = 256;
-    if (alloc) return alloc(bytes, user);
     void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+    if (alloc) p = alloc(bytes, user);
+    else if (hipMalloc(&p, bytes) != hipSuccess) p = nullptr;
+    // a refusal is reported by the null pointer alone: left behind as the last
+    // HIP error, it would fail the path that does without the memory
+    if (!p) (void)hipGetLastError();
     return p;
 }
 

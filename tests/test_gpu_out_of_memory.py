@@ -1,5 +1,8 @@
-"""An allocator that refuses: the call reports LSQR_E_OOM, and the context goes on
-working when there is memory again."""
+"""An allocator that refuses: every entry point reports LSQR_E_OOM (or does
+without the memory), whichever of its allocations it is, gives back what it had,
+and the context goes on working when there is memory again."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -16,6 +19,28 @@ def make(monkeypatch, s, blocks, **kw):
     return Solver.from_system(s, **kw)
 
 
+CASES = [dict(precision="fp64", precond="jacobi"), dict(precision="fp32"), dict(precision="bf16", method="lsqr"),
+         dict(precision="bf16", col_format="runs"), dict(precision="fp64", row_format="groups", method="lsmr"),
+         dict(precision="fp32", col_format="csc", row_format="csr")]
+
+
+@pytest.mark.parametrize("kw", CASES)
+def test_create(monkeypatch, kw):
+    from paper_2604_11920_amd import lsqr
+    s = synth.random_system(60, 5, 4, 6, row_len=(0, 30), seed=1)
+    whole = Blocks()
+    with make(monkeypatch, s, whole, **kw):
+        pass
+    assert whole.count > 15
+    for i in range(whole.count):
+        for on in (False, True):
+            blocks = Blocks(fail_at=i, fail_on=on)
+            with pytest.raises(lsqr.LsqrError) as e:
+                make(monkeypatch, s, blocks, **kw)
+            assert e.value.status == lsqr.LSQR_E_OOM, (i, str(e.value))
+            assert not blocks.live and blocks.damaged == 0
+
+
 def shared_paths(seed):
     """Paths of 12 rows over the same nodes: row blocks."""
     rng = np.random.default_rng(seed)
@@ -30,6 +55,65 @@ def shared_paths(seed):
     return synth.RandomSystem(m=m, n=nx * ny * nz, nx=nx, ny=ny, nz=nz, row_ptr=np.array(ptr, dtype=np.int64),
                               col=np.array(col, dtype=np.int32), val=rng.integers(1, 6, len(col)).astype(float),
                               dt=rng.standard_normal(m), damp=0.25, smooth=0.5)
+
+
+def last_error_allocator(blocks):
+    """The refusals come from hipMalloc, which leaves its error behind."""
+    def factory(device, stream):
+        from paper_2604_11920_amd import lsqr
+        hip = ctypes.CDLL("libamdhip64.so")
+        inner, free = blocks(device, stream)
+
+        def alloc(nbytes, user):
+            p = inner(nbytes, None)
+            if not p:
+                q = ctypes.c_void_p()
+                assert hip.hipMalloc(ctypes.byref(q), ctypes.c_size_t(1 << 50)) != 0
+            return p
+
+        return lsqr._ALLOC_FN(alloc), free
+    return factory
+
+
+@pytest.mark.parametrize("hip_error", [False, True])
+def test_block_products(monkeypatch, hip_error):
+    """The planning of the row blocks does without them; the rest is refused.
+    Afterwards both products are right, with the memory and on the other layouts
+    (integers: every sum is exact)."""
+    from paper_2604_11920_amd import lsqr
+    s = shared_paths(3)
+    rng = np.random.default_rng(4)
+    X = rng.integers(-4, 5, size=(s.n, 8)).astype(np.float32)
+    Y = rng.integers(-4, 5, size=(s.m, 8)).astype(np.float32)
+    G = s.dense()
+    Xg, Yg = torch.from_numpy(X).cuda(), torch.zeros(s.m + 2 * s.n, 8, device="cuda")
+    Yg[:s.m] = torch.from_numpy(Y).cuda()
+
+    def check(sol):
+        y = sol.apply_block(Xg).cpu().numpy()
+        x = sol.apply_t_block(Yg).cpu().numpy()
+        assert np.array_equal(y[:s.m], G @ X) and np.array_equal(x, G.T @ Y)
+
+    blocks = Blocks()
+    with make(monkeypatch, s, blocks) as sol:
+        first = blocks.count
+        check(sol)
+        last = blocks.count
+    other = refused = 0
+    for i in range(first, last):
+        blocks = Blocks(fail_at=i)
+        factory = last_error_allocator(blocks) if hip_error else blocks
+        with make(monkeypatch, s, factory) as sol:
+            try:
+                check(sol)
+                other += 1
+            except lsqr.LsqrError as e:
+                assert e.status == lsqr.LSQR_E_OOM, (i, str(e))
+                refused += 1
+            check(sol)
+            assert blocks.intact()
+        assert not blocks.live and blocks.intact()
+    assert other > 10 and refused > 10
 
 
 def test_solves(monkeypatch):
