@@ -287,15 +287,54 @@ __device__ __forceinline__ int add_run(uint32_t *bits, uint32_t c, uint32_t len,
     return n;
 }
 
+// One wave adds the runs from q on to a set of `cnt` columns, 64 at a time while
+// the set stays within cap (rows play no part in the size of a union); the 64
+// that overflow it are taken out again and added row by row.  The row that no
+// longer fits, m past the last run, or -1 when qend comes first (cnt is then the
+// size of the set).
+__device__ __forceinline__ int32_t wave_extent(uint32_t *bits, int64_t q, int64_t qend, int64_t nr, int cap, int &cnt,
+                                               int64_t m, const uint32_t *col0, const uint8_t *len,
+                                               const uint32_t *row_of)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t c = 0, l = 0;
+    if (q + lane < nr) { c = col0[q + lane]; l = len[q + lane]; }
+    while (q < qend) {
+        uint32_t cn = 0, ln = 0;
+        if (q + 64 + lane < nr) { cn = col0[q + 64 + lane]; ln = len[q + 64 + lane]; }
+        Fresh F;
+        const int tot = group_sum<64>(add_run(bits, c, l, F));
+        if (cnt + tot > cap) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if (F.f[i]) atomicAnd(&bits[(c >> 5) + i], ~F.f[i]);
+            const uint32_t row = q + lane < nr ? row_of[q + lane] : 0u;
+            uint64_t todo = __ballot(q + lane < nr);
+            while (todo) {
+                const uint32_t ri = (uint32_t)__builtin_amdgcn_readlane((int)row, __ffsll((unsigned long long)todo) - 1);
+                const bool mine = q + lane < nr && row == ri;
+                cnt += group_sum<64>(mine ? add_run(bits, c, l, F) : 0);
+                todo &= ~__ballot(mine);
+                if (cnt > cap) return (int32_t)ri;
+            }
+        }
+        else cnt += tot;
+        q += 64;
+        c = cn;
+        l = ln;
+    }
+    return q < nr ? -1 : (int32_t)m;
+}
+
 // ext[s] = first row that no longer fits the group that starts at row s (the
 // union of the columns of rows s .. ext[s] - 1 holds at most cap, with row
-// ext[s] more), for every row s: the greedy boundaries are then the chain 0,
-// ext[0], ext[ext[0]], ...  One wave per start, its column set as bits in LDS;
-// the rows' runs are one stream, added 64 at a time while the set stays within
-// cap (rows play no part in the size of a union), and the 64 that overflow it
-// are taken out again and added row by row.  Every start is tried because the
-// chain itself is serial: at 100 M entries, 1.4 ms for all of them.
-__global__ __launch_bounds__(64) void k_group_extent(int64_t m, int words, int cap, const int64_t *rrp,
+// ext[s] more): the greedy boundaries are then the chain 0, ext[0], ext[ext[0]],
+// ...  One wave per start, its column set as bits in LDS.  Every start is tried
+// because the chain itself is serial: at 100 M entries, 1.4 ms for all of them.
+// A start whose group is longer than `most` runs gets -1: without that limit
+// the work grows with the square of the rows where few columns are met (one
+// group of all rows on a grid of cap + 1 unknowns).
+__global__ __launch_bounds__(64) void k_group_extent(int64_t m, int words, int cap, int64_t most, const int64_t *rrp,
                                                      const uint32_t *col0, const uint8_t *len,
                                                      const uint32_t *row_of, int32_t *ext)
 {
@@ -306,44 +345,79 @@ __global__ __launch_bounds__(64) void k_group_extent(int64_t m, int words, int c
         for (int w = lane; w < words; w += 64) bits[w] = 0u;
         __syncthreads();
         int cnt = 0;
-        int32_t e = (int32_t)m;
-        int64_t q = rrp[s];
-        uint32_t c = 0, l = 0;
-        if (q + lane < nr) { c = col0[q + lane]; l = len[q + lane]; }
-        while (q < nr) {
-            uint32_t cn = 0, ln = 0;
-            if (q + 64 + lane < nr) { cn = col0[q + 64 + lane]; ln = len[q + 64 + lane]; }
-            Fresh F;
-            const int tot = group_sum<64>(add_run(bits, c, l, F));
-            if (cnt + tot > cap) {
-#pragma unroll
-                for (int i = 0; i < 3; ++i)
-                    if (F.f[i]) atomicAnd(&bits[(c >> 5) + i], ~F.f[i]);
-                const uint32_t row = q + lane < nr ? row_of[q + lane] : 0u;
-                uint64_t todo = __ballot(q + lane < nr);
-                while (todo) {
-                    const uint32_t ri = (uint32_t)__builtin_amdgcn_readlane((int)row, __ffsll((unsigned long long)todo) - 1);
-                    const bool mine = q + lane < nr && row == ri;
-                    cnt += group_sum<64>(mine ? add_run(bits, c, l, F) : 0);
-                    todo &= ~__ballot(mine);
-                    if (cnt > cap) { e = (int32_t)ri; break; }
-                }
-                break;
-            }
-            cnt += tot;
-            q += 64;
-            c = cn;
-            l = ln;
-        }
+        const int64_t q = rrp[s];
+        const int32_t e = wave_extent(bits, q, min(nr, q + most), nr, cap, cnt, m, col0, len, row_of);
         if (lane == 0) ext[s] = e;
         __syncthreads();
     }
 }
 
+// The chain from row s on, for starts without an extent: one workgroup adds a
+// group's runs 1,024 at a time, and its first wave finds the row in the 1,024
+// that overflow.  Ends at the first start that has one (or m); *count ends of
+// groups in `ends`.  Linear in the runs, since the groups do not overlap.
+__global__ __launch_bounds__(1024) void k_group_walk(int64_t m, int words, int cap, int64_t s, const int64_t *rrp,
+                                                     const uint32_t *col0, const uint8_t *len,
+                                                     const uint32_t *row_of, const int32_t *ext, int32_t *ends,
+                                                     int32_t *count)
+{
+    extern __shared__ uint32_t bits[];
+    __shared__ int sums[16];
+    __shared__ int32_t end;
+    const int tid = threadIdx.x;
+    const int64_t nr = rrp[m];
+    int groups = 0;
+    do {
+        for (int w = tid; w < words; w += 1024) bits[w] = 0u;
+        __syncthreads();
+        int cnt = 0;
+        int64_t q = rrp[s];
+        uint32_t c = 0, l = 0;
+        if (q + tid < nr) { c = col0[q + tid]; l = len[q + tid]; }
+        bool over = false;
+        while (q < nr) {
+            uint32_t cn = 0, ln = 0;
+            if (q + 1024 + tid < nr) { cn = col0[q + 1024 + tid]; ln = len[q + 1024 + tid]; }
+            Fresh F;
+            const int t = group_sum<64>(add_run(bits, c, l, F));
+            if ((tid & 63) == 0) sums[tid >> 6] = t;
+            __syncthreads();
+            int tot = 0;
+#pragma unroll
+            for (int w = 0; w < 16; ++w) tot += sums[w];
+            __syncthreads();
+            if (cnt + tot > cap) {                        // uniform
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    if (F.f[i]) atomicAnd(&bits[(c >> 5) + i], ~F.f[i]);
+                over = true;
+                break;
+            }
+            cnt += tot;
+            q += 1024;
+            c = cn;
+            l = ln;
+        }
+        __syncthreads();
+        if (tid < 64) {
+            const int32_t e = over ? wave_extent(bits, q, nr, nr, cap, cnt, m, col0, len, row_of) : (int32_t)m;
+            if (tid == 0) {
+                end = e;
+                ends[groups] = e;
+            }
+        }
+        ++groups;
+        __syncthreads();
+        s = end;
+        __syncthreads();
+    } while (s < m && ext[s] < 0);
+    if (tid == 0) *count = groups;
+}
+
 // A workgroup per group: its columns as bits in LDS.  EMIT = false: their
 // number to gcnt.  EMIT = true: the sorted list at gcol[gcp[g]] and, for every
 // entry of the group's rows, the rank of its column (bits below it in its word
-// plus the rank of the word).
+// plus the rank of the word); gridDim.y workgroups share the entries of a group.
 template <bool EMIT>
 __global__ __launch_bounds__(kBlock) void k_group_cols(int ng, int words, const int32_t *gp,
                                                        const int64_t *rrp, const uint32_t *col0,
@@ -383,10 +457,12 @@ __global__ __launch_bounds__(kBlock) void k_group_cols(int ng, int words, const 
             const int64_t base = gcp[g];
             for (int w = w0; w < w1; ++w) {
                 rank[w] = (uint16_t)at;
-                for (uint32_t b = bits[w]; b; b &= b - 1) gcol[base + at++] = 32 * w + __ffs((int)b) - 1;
+                for (uint32_t b = bits[w]; b; b &= b - 1, ++at)
+                    if (blockIdx.y == 0) gcol[base + at] = 32 * w + __ffs((int)b) - 1;
             }
             __syncthreads();
-            for (int64_t p = rp[r0] + threadIdx.x; p < rp[r1]; p += kBlock) {
+            const int64_t p0 = rp[r0], np = rp[r1] - p0, pe = p0 + np * (blockIdx.y + 1) / gridDim.y;
+            for (int64_t p = p0 + np * blockIdx.y / gridDim.y + threadIdx.x; p < pe; p += kBlock) {
                 const int c = ci[p];
                 slot[p] = (uint16_t)(rank[c >> 5] + __popc(bits[c >> 5] & ((1u << (c & 31)) - 1u)));
             }
@@ -724,23 +800,53 @@ hipError_t plan_csc(hipStream_t st, Allocator &al, int64_t n, int nz, int64_t nn
 
 bool plan_groups_fit(int64_t n, int nz) { return n <= kPlanMaxCols && nz <= 64; }
 
+// Runs that all starts of k_group_extent may look at together: 64 times the runs
+// there are, or this many where that is more (about 25 ms).
+constexpr int64_t kExtentRuns = (int64_t)1 << 31;
+
 hipError_t plan_group_bounds(hipStream_t st, Allocator &al, int64_t m, int64_t n, int cap, const RunPlan &R,
                              std::vector<int32_t> &gp)
 {
+    gp.assign(1, 0);
+    if (n <= cap) {                                        // every set of rows fits
+        gp.push_back((int32_t)m);
+        return hipSuccess;
+    }
     Temps tm(st, al);
     int32_t *ext = tm.get<int32_t>(m);
     PL_OK(tm);
     const int words = (int)((n + 31) / 32);
-    hipLaunchKernelGGL(k_group_extent, dim3(blocks(m, 1, 1 << 20)), dim3(64), words * 4, st, m, words, cap,
+    const int64_t most = std::max(64 * ((R.nr + m - 1) / m), kExtentRuns / m);
+    hipLaunchKernelGGL(k_group_extent, dim3(blocks(m, 1, 1 << 20)), dim3(64), words * 4, st, m, words, cap, most,
                        R.rrp, R.col0, R.len, R.row, ext);
     PL_TRY(hipGetLastError());
     std::vector<int32_t> h((size_t)m);
     PL_TRY(hipMemcpyAsync(h.data(), ext, m * sizeof(int32_t), hipMemcpyDeviceToHost, st));
     PL_TRY(hipStreamSynchronize(st));
-    gp.assign(1, 0);
-    for (int64_t s = 0; s < m; s = h[(size_t)s]) {
-        if (h[(size_t)s] <= s || h[(size_t)s] > m) return hipErrorUnknown;
-        gp.push_back(h[(size_t)s]);
+    int32_t *ends = nullptr;                               // [1 + m]: their number, then the ends
+    std::vector<int32_t> walked;
+    for (int64_t s = 0; s < m; s = gp.back()) {
+        if (h[(size_t)s] >= 0) {
+            if (h[(size_t)s] <= s || h[(size_t)s] > m) return hipErrorUnknown;
+            gp.push_back(h[(size_t)s]);
+            continue;
+        }
+        if (!ends) ends = tm.get<int32_t>(1 + m);
+        PL_OK(tm);
+        hipLaunchKernelGGL(k_group_walk, dim3(1), dim3(1024), words * 4, st, m, words, cap, s, R.rrp, R.col0, R.len,
+                           R.row, ext, ends + 1, ends);
+        PL_TRY(hipGetLastError());
+        int32_t count = 0;
+        PL_TRY(hipMemcpyAsync(&count, ends, sizeof(count), hipMemcpyDeviceToHost, st));
+        PL_TRY(hipStreamSynchronize(st));
+        if (count < 1 || count > m - s) return hipErrorUnknown;
+        walked.resize((size_t)count);
+        PL_TRY(hipMemcpyAsync(walked.data(), ends + 1, count * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+        PL_TRY(hipStreamSynchronize(st));
+        for (int32_t e : walked) {
+            if (e <= gp.back() || e > m) return hipErrorUnknown;
+            gp.push_back(e);
+        }
     }
     return hipSuccess;
 }
@@ -765,7 +871,9 @@ hipError_t plan_group_lists(hipStream_t st, int64_t n, int ng, const int32_t *gp
                             const int64_t *rp, const int32_t *ci, const int64_t *gcp, int32_t *gcol, uint16_t *slot)
 {
     const int words = (int)((n + 31) / 32);
-    hipLaunchKernelGGL((k_group_cols<true>), dim3(blocks(ng, 1, 1 << 20)), dim3(kBlock), words * 6 + 4, st, ng, words,
+    // long groups: their entries (not their runs) are shared by up to 256 workgroups
+    const int parts = blocks(R.nr / std::max(ng, 1), 1 << 15, 256);
+    hipLaunchKernelGGL((k_group_cols<true>), dim3(blocks(ng, 1, 1 << 20), parts), dim3(kBlock), words * 6 + 4, st, ng, words,
                        gp, R.rrp, R.col0, R.len, rp, ci, (uint32_t *)nullptr, gcp, gcol, slot);
     return hipGetLastError();
 }

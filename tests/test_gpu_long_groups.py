@@ -46,7 +46,7 @@ def greedy(rp, col, n, cap):
 @pytest.mark.parametrize("grid,stretches", [
     ((10, 10, 10), [(60000, 0, 1000)]),
     ((11, 10, 10), [(60000, 40, 1000)]),
-    ((50, 20, 10), [(20000, 0, 800), (20000, 2000, 1000), (300, 0, 10000), (25000, 7000, 1016), (1, 9992, 8 * 6)]),
+    ((50, 20, 10), [(20000, 0, 800), (20000, 2000, 1000), (300, 0, 10000), (25000, 7000, 1016), (1, 9992, 8 * 7)]),
 ])
 def test_groups(monkeypatch, grid, stretches):
     from paper_2604_11920_amd import Solver, lsqr
