@@ -330,29 +330,6 @@ lsqr_status batch_load_rhs(lsqr_ctx *const *ctxs, int nsys, int nrhs, int R, con
     return LSQR_OK;
 }
 
-constexpr int kBranches = 4;           // hardware queues of a process
-
-// Branches of the captured graph: 1 when a context is given twice (its two runs
-// share buffers and stay in order).
-int branches(lsqr_ctx *const *ctxs, int nsys)
-{
-    for (int a = 0; a < nsys; ++a)
-        for (int b = 0; b < a; ++b)
-            if (ctxs[a] == ctxs[b]) return 1;
-    return std::min(nsys, kBranches);
-}
-
-struct Event {
-    hipEvent_t e = nullptr;
-    Event() = default;
-    Event(const Event &) = delete;
-    Event &operator=(const Event &) = delete;
-    ~Event()
-    {
-        if (e) (void)hipEventDestroy(e);
-    }
-};
-
 // Runs every system's batch from its start (B.rhs, or B.F when full) for up
 // to `iters` iterations: a captured graph of a block of iterations of all
 // systems, replayed while any right-hand side is active, then single
@@ -387,29 +364,12 @@ lsqr_status batch_run(lsqr_ctx *const *ctxs, int nsys, int nrhs, int R, int iter
         if (!c0->cap_st) HIP_TRY(c0, hipStreamCreateWithFlags(&c0->cap_st, hipStreamNonBlocking));
         hipGraph_t graph = nullptr;
         hipGraphExec_t exec = nullptr;
-        // a branch per system, up to kBranches: small systems leave most of the
-        // device idle (3 systems of 2,304 unknowns, 32 right-hand sides: 168 -> 99 ms)
-        std::vector<hipStream_t> bst((size_t)branches(ctxs, nsys), c0->cap_st);
-        for (size_t b = 1; b < bst.size(); ++b) {
-            lsqr_ctx *c = ctxs[b];
-            if (!c->cap_st) HIP_TRY(c0, hipStreamCreateWithFlags(&c->cap_st, hipStreamNonBlocking));
-            bst[b] = c->cap_st;
-        }
-        std::vector<Event> ev(bst.size());
-        for (Event &q : ev) HIP_TRY(c0, hipEventCreateWithFlags(&q.e, hipEventDisableTiming));
         HIP_TRY(c0, hipStreamBeginCapture(c0->cap_st, hipStreamCaptureModeThreadLocal));
-        hipError_t ge = hipEventRecord(ev[0].e, c0->cap_st);
-        for (size_t b = 1; b < bst.size() && ge == hipSuccess; ++b) ge = hipStreamWaitEvent(bst[b], ev[0].e, 0);
-        for (int i = 0; i < gb && ge == hipSuccess; ++i)
-            for (int s = 0; s < nsys; ++s) batch_iter(ctxs[s], bst[(size_t)s % bst.size()], i & 1, tol);
-        for (size_t b = 1; b < bst.size() && ge == hipSuccess; ++b) {
-            ge = hipEventRecord(ev[b].e, bst[b]);
-            if (ge == hipSuccess) ge = hipStreamWaitEvent(c0->cap_st, ev[b].e, 0);
-        }
-        const hipError_t ce = hipStreamEndCapture(c0->cap_st, &graph);
-        if (ge == hipSuccess) ge = ce;
-        if (ge == hipSuccess) ge = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-        if (graph) (void)hipGraphDestroy(graph);
+        for (int i = 0; i < gb; ++i)
+            for (int s = 0; s < nsys; ++s) batch_iter(ctxs[s], c0->cap_st, i & 1, tol);
+        HIP_TRY(c0, hipStreamEndCapture(c0->cap_st, &graph));
+        hipError_t ge = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+        (void)hipGraphDestroy(graph);
         if (ge != hipSuccess) return fail(c0, LSQR_E_DEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(ge));
         while (!stopped && iters - done >= gb) {
             hipError_t le = hipGraphLaunch(exec, st);
