@@ -441,6 +441,7 @@ lsqr_status ensure_refine_buffers(lsqr_ctx *c)
     if (!B.X || !B.F || !B.rsum)
         return fail(c, LSQR_E_OOM, "device allocation failed");
     return LSQR_OK;
+    HIP_TRY(c0, hipStreamSynchronize(c0->st));     // the copies below are not on it
 }
 
 }  // namespace
