@@ -189,13 +189,14 @@ typedef struct lsqr_ctx lsqr_ctx;
 
 /* Kernel timing (LSQR_FLAG_TIMING): totals over the last solve. */
 typedef struct {
-    double fwd_ms;              /* forward products Abar D v (grids of at most 6,144   */
-                                /* unknowns with short rows: with the previous         */
-                                /* iteration's update, which shares their launch)      */
+    double fwd_ms;              /* forward products Abar D v (small grids with short   */
+                                /* rows: with the previous iteration's update, which  */
+                                /* shares their launch)                               */
     double adj_ms;              /* transposed products D Abar^T u                      */
     int fwd_launches;
     int adj_launches;
-    double fwd_bytes;           /* algorithmic bytes of one forward launch            */
+    double fwd_bytes;           /* algorithmic bytes of one forward launch (with the   */
+                                /* update's where it shares the launch)                */
     double adj_bytes;           /* algorithmic bytes of one transposed launch         */
     int row_format;             /* format the solver's forward product reads: 1 CSR,  */
                                 /* 4 row groups                                       */

@@ -1345,6 +1345,8 @@ lsqr_status lsqr_kernel_stats(const lsqr_ctx *c, lsqr_kstats *out)
     else fwd += nnz * 4.0;
     if (E.R.sigma) fwd += m * 4.0 + m * sx;
     out->fwd_bytes = fwd;
+    else if (E.g_small)      // 16-bit columns, and the update's vectors: d, v; w, y and h twice (q stands for x)
+        fwd += nnz * 2.0 + n * (8.0 + sx + 32.0 + (E.hbar ? 16.0 : 0.0));
     out->row_format = E.R.slot ? 4 : 1;
     out->col_format = E.C.nrp ? (E.C.pairs ? 4 : 2) : 1;
     out->fwd_entries_per_load = !E.R.slot            ? 0
@@ -1362,7 +1364,7 @@ lsqr_status lsqr_kernel_stats(const lsqr_ctx *c, lsqr_kstats *out)
         // format overhead, not algorithmic bytes (they show in the counters)
         const double nn = n / (double)c->P.nz;
         out->adj_bytes = nnz * (double)vt_size(E.C.vt) + (double)c->nnruns * 6.0 +
-                         (nn + 1) * 8.0 + (4 * nn + 1) * 8.0 + nn * 4.0 + mb * sx +
+                         (nn + 1) * 8.0 + (double)E.C.waves * nn * 8.0 + nn * 4.0 + mb * sx +
                          n * (8.0 + 2.0 * sx);
     } else {
         out->adj_bytes = nnz * ((double)vt_size(E.C.vt) + 4.0) + (n + 1) * 8.0 + mb * sx +
