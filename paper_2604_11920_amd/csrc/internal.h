@@ -144,15 +144,22 @@ static inline bool lcol_octs_ok(const RowFmt &R)
 constexpr int kNodeParts = 16;
 // Waves that share a node's runs in the transposed product (depth-pair
 // layouts): 16 on grids of up to kWideNodes nodes, where a workgroup of 4 waves
-// per node leaves most of the device idle, if a node has runs for more than 4
-// waves of one chunk (64 runs) each; else 4.  Transposed product, 4 -> 16 waves
-// (us): 256 nodes, 5,300 runs each, FP64 65 -> 30, BF16 51 -> 19; 484 nodes,
-// 1,340 runs 24 -> 17, 17 -> 14; 729 nodes 45 -> 36, 32 -> 27; 1,024 nodes 60 -> 60,
-// 34 -> 40; 3,136 nodes 152 -> 179, 69 -> 106.
+// per node leaves most of the device idle, if a node has runs for them: at least
+// 400, and twice as many as there are nodes (the more nodes, the more waves of
+// the 4-wave workgroups are in flight already); else 4.  Transposed product, 4 ->
+// 16 waves (us, FP64 / BF16): 64 nodes, 573 runs each 8.1 -> 6.6 / 7.2 -> 6.9; 256
+// nodes, 274 runs 8.3 -> 7.6 / 6.8 -> 7.3, 561 runs 11 -> 8.4 / 8.7 -> 8.2, 3,825
+// runs 50 -> 24 / 40 -> 16; 484 nodes, 375 runs 14.1 -> 14.4 / 9.2 -> 12.4, 1,366
+// runs 38 -> 22 / 24 -> 16; 625 nodes, 752 runs 18.9 -> 18.9 / 15 -> 19, 1,254 runs
+// 27 -> 22 / 20 -> 21; 729 nodes, 317 runs 9.7 -> 17 / 8.2 -> 18, 1,149 runs 24 -> 23
+// / 19 -> 21, 2,095 runs 45 -> 31 / 33 -> 25; 784 nodes, 1,082 runs 31 -> 32 / 19 ->
+// 25, 2,119 runs 59 -> 44 / 35 -> 30, 127 M entries 310 -> 208 / 171 -> 91; 1,024
+// nodes 60 -> 60 / 34 -> 40; 3,136 nodes 152 -> 179 / 69 -> 106.
 constexpr int64_t kWideNodes = 800;
 static inline int adj_node_waves(int64_t nodes, int64_t runs)
 {
-    return nodes <= kWideNodes && runs > 4 * 64 * nodes ? 16 : 4;
+    const int64_t each = nodes <= 200 ? 400 : 2 * nodes;
+    return nodes <= kWideNodes && runs > each * nodes ? 16 : 4;
 }
 
 // Unknowns of the fused small step (k_fwd_small): D v sits in LDS (48 KB in

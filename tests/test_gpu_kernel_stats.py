@@ -37,3 +37,22 @@ def test_bytes(precision, sv, sx, method, m, nx, ny, nz, waves):
             st = sol.kernel_stats()
             fwd, adj = expected(s, sol, sv, sx, rf == "auto", method == "lsmr", precision == "bf16", waves)
             assert st["row_format"] == 1 and (st["fwd_bytes"], st["adj_bytes"]) == (fwd, adj)
+
+
+@pytest.mark.parametrize("nx,ny,per,waves", [(8, 8, 390, 4), (8, 8, 410, 16), (16, 16, 500, 4), (16, 16, 525, 16),
+                                             (27, 27, 700, 4), (27, 27, 1470, 16), (28, 29, 4000, 4)])
+def test_waves_of_a_node(nx, ny, per, waves):
+    """16 waves share a node's runs where there are enough of them: `per` rows of
+    two depths at every node, on either side of the rule."""
+    import numpy as np
+    from paper_2604_11920_amd import Solver
+    nn, nz = nx * ny, 3
+    n, m = nn * nz, nn * per
+    col = (np.repeat(np.arange(nn), per)[:, None] * nz + [0, 1]).reshape(-1).astype(np.int32)
+    rp = 2 * np.arange(m + 1, dtype=np.int64)
+    with Solver(rp, col, np.ones(2 * m), nx, ny, nz, 0.1, 0.5) as sol:
+        got = sol.kernel_stats()["adj_bytes"]
+        q = sol.apply_t(torch.cat([torch.ones(m, dtype=torch.float64), torch.zeros(2 * n, dtype=torch.float64)]).cuda())
+    adj = 16 * m + 6 * m + 8 * (nn + 1) + 8 * waves * nn + 4 * nn + 8 * (m + 2 * n) + 24 * n
+    assert got == adj
+    assert np.array_equal(q.cpu().numpy().reshape(nn, nz), np.tile([per, per, 0.0], (nn, 1)))
