@@ -1342,11 +1342,11 @@ lsqr_status lsqr_kernel_stats(const lsqr_ctx *c, lsqr_kstats *out)
     const double sv = (double)vt_size(E.R.vt), sx = (double)vt_size(E.vec);
     double fwd = nnz * sv + (m + 1) * 8.0 + n * sx + 2.0 * mb * sx;
     if (E.R.slot) fwd += nnz * 2.0 + (double)c->ngcols * 4.0 + (double)(c->ngroups + 1) * 12.0;
+    else if (E.g_small)      // 16-bit columns, and the update's vectors: d, v; w, y and h twice (q stands for x)
+        fwd += nnz * 2.0 + n * (8.0 + sx + 32.0 + (E.hbar ? 16.0 : 0.0));
     else fwd += nnz * 4.0;
     if (E.R.sigma) fwd += m * 4.0 + m * sx;
     out->fwd_bytes = fwd;
-    else if (E.g_small)      // 16-bit columns, and the update's vectors: d, v; w, y and h twice (q stands for x)
-        fwd += nnz * 2.0 + n * (8.0 + sx + 32.0 + (E.hbar ? 16.0 : 0.0));
     out->row_format = E.R.slot ? 4 : 1;
     out->col_format = E.C.nrp ? (E.C.pairs ? 4 : 2) : 1;
     out->fwd_entries_per_load = !E.R.slot            ? 0
