@@ -197,7 +197,7 @@ lsqr_status setup_engine(lsqr_ctx *c, Engine &E, int vec, const RowFmt &R, const
     E.P2 = ctx_alloc<double>(c, E.g_adj);
     E.P3 = ctx_alloc<double>(c, E.g_upd);
     E.ctl = ctx_alloc<int>(c, C_WORDS);
-    if (c->col16 && m > 0 && !R.slot) {
+    if (c->col16 && !R.slot && small_pays(R.vt, n, m, c->P.nnz)) {
         // fused iterations: workgroups of 256 threads where all rows fit one
         // turn of them (and n their 6 elements per thread), else of 1,024; one
         // per compute unit at most, rows balanced in entries, at most one
@@ -713,7 +713,9 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
     c->C64.lpc = o.lanes_per_col ? o.lanes_per_col : pick_lanes(avg_col);
     // rows too short for the pipelined kernels of a small grid: the fused step's
     // 16-bit columns (col_format and lanes_per_col do not matter to it)
-    if (o.row_format == 0 && !o.lanes_per_row && c->R64.lpr < 64 && nnz > 0 && n <= kSmallCols) {
+    const int vt = o.precision == LSQR_FP64 ? VT_F64 : o.precision == LSQR_FP32 ? VT_F32
+                   : o.precision == LSQR_BF16 ? VT_BF16 : VT_F16;
+    if (o.row_format == 0 && !o.lanes_per_row && c->R64.lpr < 64 && nnz > 0 && small_pays(vt, n, m, nnz)) {
         c->col16 = ctx_alloc<uint16_t>(c, nnz + 8);   // zeros past the end (entries four at a time)
         if (!c->col16) return bail(LSQR_E_OOM, "device allocation failed");
         launch_col16(st, nnz, c->ci, c->col16);
@@ -783,7 +785,6 @@ lsqr_status lsqr_create(const lsqr_csr *G, double damp, double smooth_weight,
         }
         vec = VT_F32;
     } else if (mixed) {
-        const int vt = o.precision == LSQR_BF16 ? VT_BF16 : VT_F16;
         c->sigma = ctx_alloc<float>(c, std::max<int64_t>(m, 1));
         c->qrow = ctx_alloc<uint16_t>(c, nnz + 8);  // zero codes past the end
         c->qcol = ctx_alloc<uint16_t>(c, nnz);

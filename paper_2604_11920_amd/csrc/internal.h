@@ -165,12 +165,33 @@ static inline int adj_node_waves(int64_t nodes, int64_t runs)
 // Unknowns of the fused small step (k_fwd_small): D v sits in LDS (48 KB in
 // FP64) and every workgroup forms all of it, 6 elements per thread.
 constexpr int kSmallCols = 6144;
-// Lanes per row of the fused small step, four entries each (eight 16-bit codes:
-// the longest class takes 32 lanes): a row past the lanes' reach of 256, 64 or 16
-// entries is loaded in further turns.
+// Lanes per row of the fused small step, four entries each (eight 16-bit codes):
+// the fewest whose reach holds 1.25 average rows; a longer row is loaded in
+// further turns.  Lanes past a row's end are lost: FP64 rows of 44 entries on 64
+// lanes 515 us an iteration (2,304 unknowns, 50 M entries; separate launches 414),
+// on 16 lanes 328; FP32 rows of 92 on 64 lanes 294 (262), on 32 lanes 221; BF16
+// rows of 20 on 16 lanes 441 (344), on 4 lanes 237.
+static inline int small_reach(int vt) { return vt_size(vt) == 2 ? 8 : 4; }
 static inline int small_lanes(int vt, double avg_row)
 {
-    return avg_row > 32 ? (vt_size(vt) == 2 ? 32 : 64) : avg_row > 8 ? 16 : 4;
+    const int E = small_reach(vt);
+    const double lanes = 1.25 * avg_row / E;
+    return lanes <= 4 ? 4 : lanes <= 16 ? 16 : lanes <= 32 || E == 8 ? 32 : 64;
+}
+// Where the fused step pays.  Up to 1,536 unknowns (6 for each of 256 threads)
+// always: separate launches over fused, 192 to 1,440 unknowns, 30 k to 50 M
+// entries, 1.0 to 1.3.  Past that every workgroup's pass over all unknowns has to
+// be worth the launch it saves, so the entries decide: 6,144 unknowns in FP64 0.95
+// with 100 k entries, 1.04 with 1 M, 1.2 with 50 M; FP32 0.90, 0.99, 1.2 (1.07 with
+// 3 M); BF16 0.84, 0.95, 1.3 (1.07 with 3 M); 2,304 unknowns 0.98, 1.07, 1.2; 0.98,
+// 1.05, 1.2; 0.93, 1.0, 1.3.  FP32 rows that fill less than 0.6 of their lanes'
+// reach stay separate past 16 M entries (50 M: 0.86 to 0.95).
+static inline bool small_pays(int vt, int64_t n, int64_t m, int64_t nnz)
+{
+    if (m < 1 || n > kSmallCols) return false;
+    if (n > 1536 && nnz < (vt == VT_F64 ? 100 : vt == VT_F32 ? 200 : 300) * n) return false;
+    const double avg = (double)nnz / (double)m;
+    return vt != VT_F32 || nnz <= ((int64_t)1 << 24) || avg >= 0.6 * small_reach(vt) * small_lanes(vt, avg);
 }
 
 // Stored transpose (CSC) for the transposed product.

@@ -2245,7 +2245,10 @@ static void small_launch_t(hipStream_t st, const SmallStep &q, const FwdArgs &a,
     switch (q.lanes) {
     case 4: hipLaunchKernelGGL((k_fwd_small<M, V, 4, NT>), g, b, sh, st, a, u); break;
     case 16: hipLaunchKernelGGL((k_fwd_small<M, V, 16, NT>), g, b, sh, st, a, u); break;
-    default: hipLaunchKernelGGL((k_fwd_small<M, V, 256 / SmallE<M>::value, NT>), g, b, sh, st, a, u); break;
+    case 32: hipLaunchKernelGGL((k_fwd_small<M, V, 32, NT>), g, b, sh, st, a, u); break;
+    default:
+        if constexpr (SmallE<M>::value == 4) hipLaunchKernelGGL((k_fwd_small<M, V, 64, NT>), g, b, sh, st, a, u);
+        break;
     }
 }
 
