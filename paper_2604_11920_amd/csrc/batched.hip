@@ -173,6 +173,15 @@ void release_batch(lsqr_ctx *c)
     B = BatchEngine{};
 }
 
+// Workgroups at most, where no schedule is set: 2,048 over row blocks, over the
+// entries of up to this many rows, and for the transposed product over node runs;
+// else 1,024.  1,024 -> 2,048 workgroups (us): entries of 13,366 rows and 8
+// right-hand sides 73 -> 62, of 20,920 rows 249 -> 204, of 44,891 rows 442 -> 415, but
+// of 53,464 rows 631 -> 666 and of 73,306 rows 606 -> 645; node runs with 32 531 ->
+// 418 and 269 -> 202, with 8 156 -> 160 and 450 -> 444; columns (more than 32
+// depths) 2,026 -> 2,274, 436 -> 479 and 58 -> 62.
+constexpr int64_t kMoreRows = 49152;
+
 // Buffers for R right-hand sides and `iters` iterations; all or none.
 lsqr_status ensure_batch(lsqr_ctx *c, hipStream_t st, int R, int iters)
 {
@@ -190,7 +199,7 @@ lsqr_status ensure_batch(lsqr_ctx *c, hipStream_t st, int R, int iters)
         release_batch(c);
         B.R = R;
         B.rt = keep_rt && keep_rt <= R ? keep_rt : std::min(R, 32);
-        B.grid = keep_grid ? keep_grid : 2048;
+        B.grid = keep_grid;
         B.T[0] = ctx_alloc<float>(c, mb * R);
         B.T[1] = ctx_alloc<float>(c, mb * R);
         B.V = ctx_alloc<float>(c, n * R);
@@ -224,15 +233,16 @@ lsqr_status ensure_batch(lsqr_ctx *c, hipStream_t st, int R, int iters)
         if (!B.S) return refuse();
         B.s_rows = rows;
     }
-    B.g_fwd = cap(m * 64, kBlock, B.grid);
+    const bool rb = use_row_blocks(c, R), runs = c->nval32 && c->P.nz <= kMaxNzBatched;
+    const int gf = B.grid ? B.grid : rb || m <= kMoreRows ? 2048 : 1024;
+    const int ga = B.grid ? B.grid : rb || runs ? 2048 : 1024;
     // a workgroup per row block, and enough of them for the smoothing and damping
     // rows (4 a thread: 60 blocks, 18,000 unknowns and 32 right-hand sides took
     // 86 us for both products, now 37)
-    if (use_row_blocks(c, R)) B.g_fwd = cap(std::max<int64_t>(c->rb.nb, (2 * n * R + 1023) / 1024), 1, B.grid);
-    if (use_row_blocks(c, R) || (c->nval32 && c->P.nz <= kMaxNzBatched))      // a workgroup per lateral node
-        B.g_adj = (int)std::max<int64_t>(1, std::min<int64_t>(n / c->P.nz, B.grid));
-    else
-        B.g_adj = cap(n * 64, kBlock, B.grid);
+    if (rb) B.g_fwd = cap(std::max<int64_t>(c->rb.nb, (2 * n * R + 1023) / 1024), 1, gf);
+    else B.g_fwd = cap(m * 64, kBlock, gf);
+    if (rb || runs) B.g_adj = (int)std::max<int64_t>(1, std::min<int64_t>(n / c->P.nz, ga));   // a workgroup per lateral node
+    else B.g_adj = cap(n * 64, kBlock, ga);
     B.g_upd = cap(n * R, kBlock, 512);
     return LSQR_OK;
 }

@@ -41,7 +41,7 @@ struct Engine {
 struct BatchEngine {
     int R = 0;                     // padded right-hand sides (power of two <= 32)
     int rt = 32;                   // right-hand side tile of the sparse kernels
-    int grid = 1024;               // workgroups of the sparse kernels (cap)
+    int grid = 0;                  // workgroups of the sparse kernels (cap); 0: each kernel's default
     int g_fwd = 1, g_adj = 1, g_upd = 1;
     float *T[2] = {nullptr, nullptr};
     float *V = nullptr, *Q = nullptr, *Z = nullptr;
