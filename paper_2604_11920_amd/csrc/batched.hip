@@ -52,16 +52,37 @@ BArgs base_args(lsqr_ctx *c, BatchEngine &B)
     return a;
 }
 
-// Few blocks (a workgroup each, up to two to a compute unit): 8 waves share a
-// block's pairs.
-constexpr int kFewBlocks = 1024;
-// Few nodes: 8 waves share a node's pairs.
-constexpr int kBatchWideNodes = 1024;
+// Forward: 8 waves share a block's pairs up to this many blocks (a workgroup
+// each), where 4 waves each leave compute units idle.  4 -> 8 waves (us; nodes,
+// depths): 32 right-hand sides, 177 blocks 9.2 -> 7.4 (256, 9) and 24.6 -> 17.4
+// (3,136, 12); 494 blocks 8.5 -> 8.0 and 20.0 -> 19.2 (1,122, 16); 658 blocks 9.9
+// -> 9.3 and 21.7 -> 22.4 (900, 20); 968 blocks 11.5 -> 12.5 and 21.7 -> 25.4 (528,
+// 20).  16 and fewer: 658 blocks 8.7 -> 8.4 and 18.7 -> 14.8; 968 blocks 10.1 ->
+// 10.5, 15.5 -> 16.9 and 47.0 -> 45.8 (6,400, 20); 2,007 blocks 14.9 -> 16.7.
+template <int RT>
+constexpr int kFewBlocks = RT > 16 ? 576 : 768;
+
+// Transposed: 8 waves share a node's pairs where the nodes are at most the
+// workgroups of 4 waves that the device holds at once (768 for 32 right-hand
+// sides and more than 16 depths, else 1,024; of 8 waves it holds
+// 256 and 512) and a node has pairs for them.  4 -> 8 waves (us; nodes,
+// pairs a node): 32 right-hand sides of 20 depths 33.6 -> 28.0 (528, 46), 15.3 ->
+// 15.5 (528, 8), 55.2 -> 60.5 (900, 101), 34.9 -> 44.3 (1,024, 40); of 9 depths
+// 18.0 -> 13.2 (256, 38), 19.8 -> 15.3 (841, 35), 18.3 -> 16.9 (1,024, 31), 13.2 ->
+// 13.7 (1,024, 19).  16 and fewer: 7.1 -> 6.6 (256, 9), 8.8 -> 8.1 (756, 8), 8.1 ->
+// 8.8 (841, 9), 14.4 -> 12.2 (1,024, 25), 9.6 -> 10.2 (1,024, 13), 58.9 -> 67.0
+// (3,136, 100).
+template <int RT, int MT>
+bool few_nodes(const BArgs &a)
+{
+    const int64_t nn = a.n / a.nz;
+    return nn <= (RT > 16 && MT == 2 ? 768 : 1024) && a.rb.np >= (nn > 768 ? 20 : 6) * nn;
+}
 
 template <int RT, int KS, int MT>
 void launch_fwd_rb(hipStream_t st, int grid, const BArgs &a)
 {
-    if (a.rb.nb <= kFewBlocks)
+    if (a.rb.nb <= kFewBlocks<RT>)
         hipLaunchKernelGGL((k_bfwd_rb<RT, KS, MT, 8>), dim3(grid), dim3(512), 0, st, a);
     else
         hipLaunchKernelGGL((k_bfwd_rb<RT, KS, MT, 4>), dim3(grid), dim3(256), 0, st, a);
@@ -70,7 +91,7 @@ void launch_fwd_rb(hipStream_t st, int grid, const BArgs &a)
 template <int RT, int MT, int QM>
 void launch_adj_rb(hipStream_t st, int grid, const BArgs &a)
 {
-    if (a.n / a.nz <= kBatchWideNodes)
+    if (few_nodes<RT, MT>(a))
         hipLaunchKernelGGL((k_badj_rb<RT, MT, QM, 8>), dim3(grid), dim3(512), 0, st, a);
     else
         hipLaunchKernelGGL((k_badj_rb<RT, MT, QM, 4>), dim3(grid), dim3(256), 0, st, a);
