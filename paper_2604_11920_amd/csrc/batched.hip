@@ -441,6 +441,7 @@ lsqr_status batch_state(lsqr_ctx *c0, lsqr_ctx *c, int nrhs, int &err, std::vect
     int ctl[C_WORDS];
     why.assign((size_t)R, 0);
     klast.assign((size_t)nrhs, 0);
+    HIP_TRY(c0, hipStreamSynchronize(c0->st));     // the copies below are not on it
     HIP_TRY(c0, hipMemcpy(ctl, B.ctl, sizeof(ctl), hipMemcpyDeviceToHost));
     HIP_TRY(c0, hipMemcpy(why.data(), B.why, R * sizeof(int), hipMemcpyDeviceToHost));
     kdone = ctl[C_ITERS];
@@ -472,7 +473,6 @@ lsqr_status ensure_refine_buffers(lsqr_ctx *c)
     if (!B.X || !B.F || !B.rsum)
         return fail(c, LSQR_E_OOM, "device allocation failed");
     return LSQR_OK;
-    HIP_TRY(c0, hipStreamSynchronize(c0->st));     // the copies below are not on it
 }
 
 }  // namespace
