@@ -125,7 +125,9 @@ constexpr int kQDepths = LSQR_Q_DEPTHS;
 // The node-run values of `src` (CSR order, elem_bytes each) in the layout of
 // W depths to a word: every run from a position that is a multiple of W,
 // zeros before its first depth's offset in the word and after its end, W
-// zeros after the last run (total positions before them).  *vals and *nvq
+// zeros after the last run (total positions before them).  *vals and *nvq (the
+// value offset of each part of a node's runs) stay with the context; start takes
+// the runs' positions.
 static lsqr_status build_layout(lsqr_ctx *c, const RunPlan &R, int W, int64_t total, uint32_t *start,
                                 const void *src, int elem_bytes, int64_t **nvq, void **vals)
 {

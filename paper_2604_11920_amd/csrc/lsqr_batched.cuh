@@ -1314,7 +1314,7 @@ __global__ __launch_bounds__(kBlock) void k_bfinal(BArgs a, double *dm)
 // (row-major [rows][R], R a power of two <= 32): lane r + R e of a wave takes
 // entry e, e + 64 / R, ... of its row or column for right-hand side r, four loads
 // in flight.  One right-hand side after the other took seven launches each: 224 a
-// sweep and system of 32, 3.6 -> REFB ms a sweep of 3 systems.
+// sweep and system of 32, 3.6 -> 0.4 ms a sweep of 3 systems.
 struct RefArgs {
     const int64_t *ptr;
     const int32_t *idx;

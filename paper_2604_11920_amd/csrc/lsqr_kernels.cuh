@@ -458,9 +458,6 @@ template <class M> struct PipeU { static constexpr int value = sizeof(M) >= 8 ? 
 #define LSQR_FWD_WG_ROWS 1
 #endif
 
-// A load through the constant address space: with a wave-uniform index it
-// becomes a scalar load, whose wait does not hold up the vector loads in
-// flight.  Only for memory that no kernel of the launch writes.
 // x / d and x mod d for a fixed d >= 1 and 0 <= x < 2^31, by a multiplication: with
 // 2^k >= d and M = floor(2^(31+k) / d) + 1, floor(x M / 2^(31+k)) = floor(x / d).
 struct FastDiv {
@@ -477,6 +474,9 @@ struct FastDiv {
     __host__ __device__ __forceinline__ uint32_t mod(uint32_t x) const { return x - div(x) * d; }
 };
 
+// A load through the constant address space: with a wave-uniform index it
+// becomes a scalar load, whose wait does not hold up the vector loads in
+// flight.  Only for memory that no kernel of the launch writes.
 template <class T>
 __device__ __forceinline__ T ld_uniform(const T *p, int64_t i)
 {
