@@ -615,8 +615,8 @@ def rays_size(rays):
     return int(m.value), int(nnz.value)
 
 
-# Nodes (12 bytes each) of the one-call split's temporary arrays at most: 384 MB.
-_SPLIT_ONE_CALL = 1 << 25
+# Nodes (12 bytes each) of the one-call split's temporary arrays at most: 600 MB.
+_SPLIT_ONE_CALL = 3 << 24
 
 
 def split_polylines(poly, stream=None):
@@ -644,10 +644,10 @@ def split_polylines(poly, stream=None):
         return (torch.empty(max(count, 1), dtype=torch.int32, device=dev),
                 torch.empty(max(count, 1), dtype=torch.float64, device=dev))
 
-    # A piece is shorter than a cell in x and y: it crosses at most two by two
-    # cells and adds to at most nine nodes (their corners).  Where that bound is
-    # small, one call writes into arrays of that size; else a first call counts.
-    bound, room = 9 * len(keep[1]), None
+    # A piece is cut into at most three, each of which adds to the four corners of
+    # one cell: at most 12 nodes.  Where that bound is small, one call writes into
+    # arrays of that size; else a first call counts.
+    bound, room = 12 * len(keep[1]), None
     if 0 < bound <= _SPLIT_ONE_CALL:
         try:
             room = arrays(bound)
