@@ -36,3 +36,31 @@ def test_block_products_then_fp32_inner_solves(monkeypatch, nx, ny, nz, row_len)
         assert blocks.intact()
     (a, ya, xa), (b, yb, xb) = out
     assert np.array_equal(a, b) and torch.equal(ya, yb) and torch.equal(xa, xb)
+
+
+def test_first_call_under_capture():
+    """A capture only records the conversion: an eager call before the first replay
+    makes the copies itself."""
+    from paper_2604_11920_amd import Solver
+    s = synth.random_system(301, 9, 8, 6, row_len=(1, 30), seed=2, integer=True)
+    G = s.dense()
+    rng = np.random.default_rng(1)
+    Xs = [rng.integers(-4, 5, size=(s.n, 4)).astype(np.float32) for _ in range(4)]
+    st = torch.cuda.Stream()
+    x = torch.from_numpy(Xs[0]).cuda()
+    y, eager = (torch.zeros(s.m + 2 * s.n, 4, device="cuda") for _ in range(2))
+    torch.cuda.synchronize()
+    sol = Solver.from_system(s, stream=st)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        sol.apply_block(x, y)
+    sol.apply_block(x, eager)
+    torch.cuda.synchronize()
+    assert np.array_equal(eager.cpu().numpy()[:s.m], G @ Xs[0])
+    for X in Xs:
+        x.copy_(torch.from_numpy(X))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy()[:s.m], G @ X)
+    sol.close()
