@@ -53,36 +53,44 @@ BArgs base_args(lsqr_ctx *c, BatchEngine &B)
 }
 
 // Forward: 8 waves share a block's pairs up to this many blocks (a workgroup
-// each), where 4 waves each leave compute units idle.  4 -> 8 waves (us; nodes,
-// depths): 32 right-hand sides, 177 blocks 9.2 -> 7.4 (256, 9) and 24.6 -> 17.4
-// (3,136, 12); 494 blocks 8.5 -> 8.0 and 20.0 -> 19.2 (1,122, 16); 658 blocks 9.9
-// -> 9.3 and 21.7 -> 22.4 (900, 20); 968 blocks 11.5 -> 12.5 and 21.7 -> 25.4 (528,
-// 20).  16 and fewer: 658 blocks 8.7 -> 8.4 and 18.7 -> 14.8; 968 blocks 10.1 ->
-// 10.5, 15.5 -> 16.9 and 47.0 -> 45.8 (6,400, 20); 2,007 blocks 14.9 -> 16.7.
+// each), where 4 waves each leave compute units idle.  4 -> 8 waves, us of a
+// batched iteration (nodes, depths): 32 right-hand sides, 177 blocks 32.8 -> 30.5
+// (256, 9) and 140 -> 134 (3,136, 12); 494 blocks 43.5 -> 42.3 and 68 -> 66 (528, 20);
+// 658 blocks 50.0 -> 48.8, 82.5 -> 84.9 (528, 20), 90.3 -> 91.7 (1,122, 16); 968 blocks
+// 60.1 -> 61.6 and 88 -> 94.  Of 128,000 unknowns (6,400, 20), where the smoothing and
+// damping rows are most of the launch, 177 blocks 282 -> 290, 968 blocks 351 -> 358.
+// 8 right-hand sides: 177 blocks 25.4 -> 24.7 and 105 -> 92 (6,400, 20); 767 blocks
+// 38.9 -> 39.1, 55.4 -> 54.6 (900, 20), 130 -> 124 (6,400, 20); 968 blocks 44.1 ->
+// 45.3, 56 -> 59 (528, 20), 144 -> 142.
 template <int RT>
-constexpr int kFewBlocks = RT > 16 ? 576 : 768;
+bool few_blocks(const BArgs &a)
+{
+    return a.rb.nb <= (RT > 16 ? 576 : 768) && (RT <= 16 || a.n <= 65536);
+}
 
 // Transposed: 8 waves share a node's pairs where the nodes are at most the
 // workgroups of 4 waves that the device holds at once (768 for 32 right-hand
-// sides and more than 16 depths, else 1,024; of 8 waves it holds
-// 256 and 512) and a node has pairs for them.  4 -> 8 waves (us; nodes,
-// pairs a node): 32 right-hand sides of 20 depths 33.6 -> 28.0 (528, 46), 15.3 ->
-// 15.5 (528, 8), 55.2 -> 60.5 (900, 101), 34.9 -> 44.3 (1,024, 40); of 9 depths
-// 18.0 -> 13.2 (256, 38), 19.8 -> 15.3 (841, 35), 18.3 -> 16.9 (1,024, 31), 13.2 ->
-// 13.7 (1,024, 19).  16 and fewer: 7.1 -> 6.6 (256, 9), 8.8 -> 8.1 (756, 8), 8.1 ->
-// 8.8 (841, 9), 14.4 -> 12.2 (1,024, 25), 9.6 -> 10.2 (1,024, 13), 58.9 -> 67.0
-// (3,136, 100).
+// sides and more than 16 depths, else 1,024; of 8 waves it holds 256 and 512) and
+// a node has pairs for them.  4 -> 8 waves, us of a batched iteration (nodes,
+// pairs a node): 32 right-hand sides of 20 depths 65.8 -> 69.7 (528, 33), 84.9 ->
+// 76.3 (528, 41), 154 -> 131 (528, 141), 92 -> 102 (900, 31), 150 -> 167 (900, 101);
+// of 9 depths 30.5 -> 27.0 (256, 18), 48.8 -> 39.9 (256, 69), 60.9 -> 61.0 (1,024,
+// 25), 75.6 -> 72.1 (1,024, 33).  8 of them: 24.7 -> 22.9 (256, 18), 29.8 -> 27.3 (528,
+// 11), 33.6 -> 35.8 (900, 10), 42.0 -> 42.2 (900, 25), 48.8 -> 44.9 (900, 31), 35.3 ->
+// 36.3 (1,024, 25), 47.1 -> 41.2 (1,024, 33), 110.5 -> 115.4 (3,136, 53); the product
+// alone of 16 on 256 nodes of 9 pairs 7.1 -> 6.6, on 756 of 8 8.8 -> 8.1.
 template <int RT, int MT>
 bool few_nodes(const BArgs &a)
 {
-    const int64_t nn = a.n / a.nz;
-    return nn <= (RT > 16 && MT == 2 ? 768 : 1024) && a.rb.np >= (nn > 768 ? 20 : 6) * nn;
+    const bool big = RT > 16 && MT == 2;
+    const int64_t nn = a.n / a.nz, pairs = nn > 768 ? 28 : big ? 40 : 6;
+    return nn <= (big ? 768 : 1024) && a.rb.np >= pairs * nn;
 }
 
 template <int RT, int KS, int MT>
 void launch_fwd_rb(hipStream_t st, int grid, const BArgs &a)
 {
-    if (a.rb.nb <= kFewBlocks<RT>)
+    if (few_blocks<RT>(a))
         hipLaunchKernelGGL((k_bfwd_rb<RT, KS, MT, 8>), dim3(grid), dim3(512), 0, st, a);
     else
         hipLaunchKernelGGL((k_bfwd_rb<RT, KS, MT, 4>), dim3(grid), dim3(256), 0, st, a);

@@ -74,10 +74,12 @@ def test_tiles_of_row_blocks(monkeypatch, nz, rows):
     check(monkeypatch, path_system(nz, rows, 40, 0), WIDTHS, True)
 
 
-# one and two row tiles; 1,100 blocks and 1,110 nodes: 4 waves to each; many paths
-# on few nodes: 4 waves to a block, 8 to a node
+# one and two tiles of rows and of depths; 1,100 blocks and 1,110 nodes: 4 waves to
+# each; many paths on few nodes: 8 waves to a node (and, of 500 blocks, to a block)
 @pytest.mark.parametrize("nz,rows,npath,nx,ny", [(12, 6, 1100, 37, 30), (20, 18, 1100, 37, 30), (9, 17, 1100, 37, 30),
-                                                 (32, 12, 1100, 37, 30), (17, 8, 1100, 9, 7), (32, 19, 1100, 37, 30)])
+                                                 (32, 12, 1100, 37, 30), (17, 8, 1100, 9, 7), (32, 19, 1100, 37, 30),
+                                                 (4, 16, 500, 9, 7), (16, 18, 500, 9, 7), (20, 19, 500, 9, 7),
+                                                 (32, 7, 500, 9, 7)])
 def test_row_blocks_of_many_paths_and_nodes(monkeypatch, nz, rows, npath, nx, ny):
     check(monkeypatch, path_system(nz, rows, npath, 0, nx=nx, ny=ny), [(1, None), (8, None), (32, None), (32, 8)], True)
 
