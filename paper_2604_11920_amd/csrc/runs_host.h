@@ -1,8 +1,9 @@
 // Host-side builders of the index formats (plain C++, no HIP): row groups of
 // the data rows (forward product), node runs of the data block and their
 // padded layouts (transposed product).  All read only the CSR structure.  The
-// library plans them on the device (plan.hip) to the same results; it calls the
-// row-group builder here for grids past the device planner's size.
+// library plans them on the device (plan.hip); the builders here are what the
+// device's arrays are compared with, element by element, and the row groups of
+// grids past the device planner's size.
 #pragma once
 
 #include <stdint.h>
